@@ -35,13 +35,32 @@ int scratch_of_current_device(void** out) {
 
 thread_local const char* g_last_kernel = "";
 
-enum Kernel { K_GENERAL = 0, K_DECODE_MFMA_BF16 = 1, K_DECODE_MFMA_F8 = 2, K_PREFILL_MFMA_BF16 = 3 };
+enum Kernel { K_GENERAL = 0, K_DECODE_MFMA_BF16 = 1, K_DECODE_MFMA_F8 = 2, K_PREFILL_MFMA_BF16 = 3, K_PREFILL_SPLIT = 4 };
 
 struct Plan {
   Kernel kernel;
-  int n_splits, blocks_per_split;
-  size_t workspace_bytes;
+  int n_splits, blocks_per_split, row_tiles;
+  size_t workspace_bytes;      // what the size query reports
+  size_t min_workspace_bytes;  // what a call must bring; with less than workspace_bytes it cuts the KV into fewer splits
 };
+
+size_t partial_bytes(const mepic_attn_params* p, long n_splits) {
+  return (size_t)p->n_q_tokens * p->Hq * n_splits * (p->D + 2) * sizeof(float);
+}
+
+// Cut n_blocks into at most `want` splits of whole 256-slot tiles.
+void cut_kv(const mepic_attn_params* p, int n_blocks, long want, Plan* pl) {
+  const int tile_blocks = 256 / p->P;
+  const int max_splits = (n_blocks + tile_blocks - 1) / tile_blocks;
+  if (want > max_splits) want = max_splits;
+  if (want > 1024) want = 1024;
+  if (want < 1) want = 1;
+  int bps = (int)((n_blocks + want - 1) / want);
+  bps = (bps + tile_blocks - 1) / tile_blocks * tile_blocks;
+  if (bps < tile_blocks) bps = tile_blocks;
+  pl->blocks_per_split = bps;
+  pl->n_splits = n_blocks > 0 ? (n_blocks + bps - 1) / bps : 1;
+}
 
 int check_shapes(const mepic_attn_params* p, bool prefill) {
   if (!p) return MEPIC_ERR_INVALID;
@@ -79,6 +98,7 @@ Plan make_plan(const mepic_attn_params* p, bool prefill) {
     decode_mfma_plan(p->B, p->Hkv, max_kv, mfma_fp8, &pl.n_splits, &pl.blocks_per_split);
     pl.workspace_bytes = (size_t)p->n_q_tokens * p->Hq * pl.n_splits * (p->D + 2) * sizeof(float) +
                          (size_t)(p->B + 2) * sizeof(int32_t);
+    pl.min_workspace_bytes = pl.workspace_bytes;
     return pl;
   }
 
@@ -93,25 +113,39 @@ Plan make_plan(const mepic_attn_params* p, bool prefill) {
     pl.blocks_per_split = n_blocks;
     // the per-position rotary table the call builds for itself: 32 entries of 16 bytes per position
     pl.workspace_bytes = (size_t)prefill_mfma_table_positions(n_blocks * p->P) * 16 * sizeof(uint4) + 16;  // table + clock sample
+    pl.min_workspace_bytes = pl.workspace_bytes;
     return pl;
   }
 
   // General path: one workgroup per (query token, KV head, split); a split is a whole number of
   // 256-slot tiles. Enough splits to put ~8 workgroups on each of the 256 compute units.
-  const int tile_blocks = 256 / p->P;
   const long rows = (long)p->n_q_tokens * p->Hkv;
-  int want = rows > 0 ? (int)((2048 + rows - 1) / rows) : 1;
-  const int max_splits = (n_blocks + tile_blocks - 1) / tile_blocks;
-  if (want > max_splits) want = max_splits;
-  if (want > 1024) want = 1024;
-  if (want < 1) want = 1;
-  int bps = (n_blocks + want - 1) / want;
-  bps = (bps + tile_blocks - 1) / tile_blocks * tile_blocks;
-  if (bps < tile_blocks) bps = tile_blocks;
-  pl.blocks_per_split = bps;
-  pl.n_splits = n_blocks > 0 ? (n_blocks + bps - 1) / bps : 1;
-  pl.workspace_bytes = (size_t)p->n_q_tokens * p->Hq * pl.n_splits * (p->D + 2) * sizeof(float);
+  cut_kv(p, n_blocks, rows > 0 ? (2048 + rows - 1) / rows : 1, &pl);
+  pl.workspace_bytes = pl.min_workspace_bytes = partial_bytes(p, pl.n_splits);
+  const long n_rows = (long)p->n_q_tokens * G, per_wg = prefill_split_rows_per_workgroup();
+  if (prefill && p->kv_dtype != MEPIC_F32 && n_rows >= 5L * p->B) {
+    // 16- and 8-bit pages: matrix-core kernel of the general path, a workgroup per 256 query rows. One workgroup fills a
+    // compute unit, so split the KV until there are two for each. Its cost hardly depends on how many of the 256 rows
+    // there are (8 requests of 16 K bf16 slots, 8 KV heads: 229 us from 1 to 12 rows per request, 236 at 36), the scalar
+    // kernel's grows with the query tokens (same calls: 153 us at 1 row of 1 token, 245 at 4 of 1, 347 at 3 of 3, 1633 at
+    // 36 of 9); up to four rows per request the scalar kernel was the faster one somewhere, from five on nowhere.
+    pl.kernel = K_PREFILL_SPLIT;
+    pl.row_tiles = (int)(n_rows / per_wg + p->B);
+    long wgs = (n_rows + per_wg - 1) / per_wg;
+    if (wgs < p->B) wgs = p->B;
+    wgs *= p->Hkv;
+    cut_kv(p, n_blocks, wgs > 0 ? (512 + wgs - 1) / wgs : 1, &pl);
+    if (partial_bytes(p, pl.n_splits) > pl.workspace_bytes) pl.workspace_bytes = partial_bytes(p, pl.n_splits);
+  }
   return pl;
+}
+
+// A workspace between the least and the reported size: as many splits as it holds partials for.
+void fit_workspace(const mepic_attn_params* p, Plan* pl) {
+  if (pl->kernel != K_PREFILL_SPLIT || p->workspace_bytes >= pl->workspace_bytes) return;
+  const long room = (long)(p->workspace_bytes / partial_bytes(p, 1));
+  const int n_blocks = pl->n_splits * pl->blocks_per_split;  // rounded up to whole splits: only the bound matters
+  if (room < pl->n_splits) cut_kv(p, n_blocks, room, pl);
 }
 
 void mark(void* ev, hipStream_t s) {
@@ -129,8 +163,9 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
   if (!(p->rope_theta > 0.f)) return MEPIC_ERR_INVALID;
   if ((p->timing_start == nullptr) != (p->timing_stop == nullptr)) return MEPIC_ERR_INVALID;
 
-  const Plan pl = make_plan(p, prefill);
-  if (pl.workspace_bytes && (!p->workspace || p->workspace_bytes < pl.workspace_bytes)) return MEPIC_ERR_CAPACITY;
+  Plan pl = make_plan(p, prefill);
+  if (pl.workspace_bytes && (!p->workspace || p->workspace_bytes < pl.min_workspace_bytes)) return MEPIC_ERR_CAPACITY;
+  fit_workspace(p, &pl);
   if (reinterpret_cast<uintptr_t>(p->workspace) & 255u) return MEPIC_ERR_INVALID;
 
   AttnArgs a{};
@@ -146,7 +181,7 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
   a.interleaved = (p->flags & MEPIC_FLAG_ROPE_INTERLEAVED) ? 1 : 0;
   a.kv_read_once = (p->flags & MEPIC_FLAG_KV_READ_ONCE) ? 1 : 0;
   a.causal = prefill ? 1 : 0;
-  a.n_splits = pl.n_splits; a.blocks_per_split = pl.blocks_per_split;
+  a.n_splits = pl.n_splits; a.blocks_per_split = pl.blocks_per_split; a.row_tiles = pl.row_tiles;
   const double sm = p->sm_scale > 0.f ? (double)p->sm_scale : 1.0 / std::sqrt((double)p->D);
   a.qk_scale_log2 = (float)(sm * 1.4426950408889634);
   // frequencies in turns per position, f_i / (2 pi), as a two-float sum
@@ -176,9 +211,10 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
     default:
       g_last_kernel = "general";
       mark(a.timing_start, s);
-      e = launch_general(a, s);
+      e = pl.kernel == K_PREFILL_SPLIT ? launch_prefill_split(a, s) : launch_general(a, s);
       mark(a.timing_stop, s);
-      if (e == hipSuccess) e = launch_combine(a, s);
+      // (the matrix-core kernel writes its rows itself where there is nothing to merge)
+      if (e == hipSuccess && !(pl.kernel == K_PREFILL_SPLIT && a.n_splits == 1)) e = launch_combine(a, s);
       break;
   }
   return e == hipSuccess ? MEPIC_OK : MEPIC_ERR_LAUNCH;

@@ -1,0 +1,96 @@
+// Shared device helpers of the general path's matrix-core kernels (attn_prefill_split.hip, attn_decode_split.hip).
+//
+// "Split" precision: an fp32 value x enters a bf16 matrix product as two operands, hi = bf16(x) and lo = bf16(x - hi),
+// which together carry 16 significant bits (relative error 2^-18). A product of two such values is three matrix
+// products (hi hi + hi lo + lo hi; the dropped lo lo is of the size of the error), a product with an operand that bf16
+// holds exactly (stored bf16 values, e4m3 codes) two. Everything else - phases, rotation, softmax, sums - is fp32, as in
+// attn_general.hip, so results keep that kernel's accuracy (the output's own bf16 rounding, 2^-9, is what is left)
+// at matrix-core speed.
+#pragma once
+#include "attn_common.h"
+
+namespace mepic {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+union SplitFrag {  // one 16-byte operand fragment
+  uint4 u;
+  bf16x8 v;
+  uint32_t w[4];
+};
+
+__device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {  // round to nearest even (v_cvt_pk_bf16_f32)
+  const f32x2 v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// Two fp32 values -> their packed bf16 heads and packed bf16 remainders.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+  hi = pack2_bf16(x0, x1);
+  lo = pack2_bf16(x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xffff0000u));
+}
+
+__device__ __forceinline__ int uni_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uni_f(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
+
+// Eight stored elements (one granule of bf16, or half a granule of e4m3 codes) as loaded.
+template <bool kFp8> struct Raw8;
+template <> struct Raw8<false> { uint4 r; };
+template <> struct Raw8<true> { uint2 r; };
+
+template <bool kFp8>
+__device__ __forceinline__ void widen8(const Raw8<kFp8>& in, float (&x)[8]) {
+  if constexpr (kFp8) {
+    const uint32_t w[2] = {in.r.x, in.r.y};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8(w[i], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w[i], true);
+      x[4 * i] = a[0]; x[4 * i + 1] = a[1]; x[4 * i + 2] = b[0]; x[4 * i + 3] = b[1];
+    }
+  } else {
+    const uint32_t w[4] = {in.r.x, in.r.y, in.r.z, in.r.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[2 * i] = __uint_as_float(w[i] << 16);
+      x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+  }
+}
+
+// Eight stored elements as packed bf16 (exact for e4m3 codes, whose page scale is applied elsewhere).
+template <bool kFp8>
+__device__ __forceinline__ SplitFrag bf16_of8(const Raw8<kFp8>& in) {
+  SplitFrag f;
+  if constexpr (kFp8) {
+    const uint32_t w[2] = {in.r.x, in.r.y};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8(w[i], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w[i], true);
+      f.w[2 * i] = __builtin_amdgcn_perm(__float_as_uint(a[1]), __float_as_uint(a[0]), 0x07060302u);
+      f.w[2 * i + 1] = __builtin_amdgcn_perm(__float_as_uint(b[1]), __float_as_uint(b[0]), 0x07060302u);
+    }
+  } else {
+    f.u = in.r;
+  }
+  return f;
+}
+
+// Keep the elements of `f` whose bit of `keep` (8 bits) is set, zero the others.
+__device__ __forceinline__ void mask8(SplitFrag& f, uint32_t keep) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    f.w[i] &= ((keep >> (2 * i)) & 1u ? 0x0000ffffu : 0u) | ((keep >> (2 * i + 1)) & 1u ? 0xffff0000u : 0u);
+}
+
+// Does any of the eight bf16 elements have all exponent bits set (Inf or NaN)?
+__device__ __forceinline__ bool any_nonfinite8(const SplitFrag& f) {
+  u16x2 m = __builtin_bit_cast(u16x2, f.w[0] & 0x7fff7fffu);
+#pragma unroll
+  for (int i = 1; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, f.w[i] & 0x7fff7fffu));
+  return m[0] >= 0x7f80u || m[1] >= 0x7f80u;
+}
+
+}  // namespace mepic

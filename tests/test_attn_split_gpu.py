@@ -1,0 +1,100 @@
+"""The general path's matrix-core kernels (split precision) against the fp64 oracle: every form they take over from the
+scalar kernel, at the edges of their tiles. Their error is the output's own rounding to bf16 (half an ulp of an 8-bit significand,
+2^-8 of the value) plus a remainder of the operands' 2^-18 terms, bounded here by 2^-13 of the largest output."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from harness import DeviceCase, align_with_oracle, oracle_out
+
+pytestmark = pytest.mark.gpu
+
+
+def within_output_rounding(got, want):
+    assert np.isfinite(got).all()
+    excess = np.abs(got - want) - np.abs(want) * 2.0 ** -8
+    assert excess.max() <= np.abs(want).max() * 2.0 ** -13, f"{excess.max():.3e}"
+
+
+def question_prefill(seed, n_q, kv_dtype="bf16", D=128, P=16, Hq=28, Hkv=4, chunk=150, **kw):
+    st = W.prefill_structure("split_prefill", seed, B=len(n_q), Hq=Hq, Hkv=Hkv, D=D, P=P, theta=5e5, n_chunks=3,
+                             chunk_tokens=chunk, pool=3, q_tokens=1, max_gap_pages=2, kv_dtype=kv_dtype, **kw)
+    st.n_q = list(n_q)
+    for b, n in enumerate(n_q):
+        st.requests[b][-1] = (0, n + 5 * b, 0)
+    return st
+
+
+def check(M, oracle_attn, st, pads_are_positions=True, interleaved=False, change=None):
+    case = W.assemble(st, align_with_oracle(st)[0], pads_are_positions=pads_are_positions)
+    if change:
+        change(case)
+    dc = DeviceCase(M, case, flags=M.FLAG_FORCE_GENERAL | (M.FLAG_ROPE_INTERLEAVED if interleaved else 0))
+    got = dc.run()
+    within_output_rounding(got, oracle_out(oracle_attn, case, interleaved=interleaved))
+    return case, dc
+
+
+@pytest.mark.parametrize("pads_are_positions", [True, False])
+@pytest.mark.parametrize("interleaved", [False, True])
+@pytest.mark.parametrize("P", [16, 32])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
+def test_prefill_forms(mepic, oracle_attn, kv_dtype, D, P, interleaved, pads_are_positions):
+    """Rows cross token boundaries (G = 7), one request fills more than a row tile, one only part of a wave."""
+    check(mepic, oracle_attn, question_prefill(5, [37, 90, 3], kv_dtype, D, P), pads_are_positions, interleaved)
+
+
+@pytest.mark.parametrize("Hq,Hkv,n_q", [(1, 1, [257]), (16, 1, [16, 17, 1]), (12, 12, [1, 300]), (10, 2, [51, 52])])
+@pytest.mark.parametrize("chunk", [5, 64, 700])
+def test_prefill_row_tiles_and_contexts(mepic, oracle_attn, Hq, Hkv, n_q, chunk):
+    """One row past a tile, exactly a tile, contexts of one tile and of several splits."""
+    check(mepic, oracle_attn, question_prefill(9, n_q, "bf16", Hq=Hq, Hkv=Hkv, chunk=chunk), chunk != 64)
+
+
+@pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("bf16", 32), ("f8e4m3", 32)])
+def test_prefill_non_finite_values_reach_only_the_rows_that_see_them(mepic, oracle_attn, kv_dtype, P):
+    """V of a question token that holds Inf / NaN: rows before it stay what they were, rows that see it are not finite."""
+    st = question_prefill(13, [40, 9], kv_dtype, P=P)
+    where = {}
+
+    def poison(case):
+        slot = int(case.q_positions[25])
+        page = int(case.block_tables[0, slot // P])
+        if kv_dtype == "bf16":
+            case.pages.v[page, 1, 3, slot % P] = float("inf")
+        else:
+            case.pages.v.view(torch.uint8)[page, 1, 3, slot % P] = 0x7F
+        where["tok"] = 25
+
+    case = W.assemble(st, align_with_oracle(st)[0])
+    poison(case)
+    got = DeviceCase(mepic, case, flags=mepic.FLAG_FORCE_GENERAL).run()
+    want = oracle_out(oracle_attn, case)
+    hit = np.zeros(got.shape, dtype=bool)
+    hit[25:40, 7:14, 3] = True                       # the rows from that token on, the KV head's group, the dim
+    assert not np.isfinite(got[hit]).any() and not np.isfinite(want[hit]).any()
+    if kv_dtype == "bf16":
+        assert (got[hit] == np.inf).all()
+    within_output_rounding(got[~hit], want[~hit])
+
+
+def test_prefill_smaller_workspace_and_refusal(mepic, oracle_attn):
+    """The size query reports what the preferred split of the KV needs; less, down to one partial per row as the scalar
+    kernel needed, still runs, and less than that is refused."""
+    st = question_prefill(17, [60, 33], "f8e4m3", P=32, chunk=900)
+    case, dc = check(mepic, oracle_attn, st)
+    want = oracle_out(oracle_attn, case)
+    least = case.n_q * st.Hq * (st.D + 2) * 4
+    full = dc.params.workspace_bytes
+    assert full >= 4 * least
+    rows = case.n_q * st.Hkv
+    scalar_splits = min(-(-2048 // rows), -(-int(case.kv_lens.max()) // 256))
+    for room in (full - 1, scalar_splits * least):
+        dc.params.workspace_bytes = room
+        within_output_rounding(dc.run(), want)
+    dc.params.workspace_bytes = least - 1
+    assert mepic.load().mepic_attn_prefill(ctypes.byref(dc.params), None) == mepic.ERR_CAPACITY
