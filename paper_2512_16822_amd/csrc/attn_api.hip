@@ -35,7 +35,7 @@ int scratch_of_current_device(void** out) {
 
 thread_local const char* g_last_kernel = "";
 
-enum Kernel { K_GENERAL = 0, K_DECODE_MFMA_BF16 = 1, K_DECODE_MFMA_F8 = 2, K_PREFILL_MFMA_BF16 = 3, K_PREFILL_SPLIT = 4 };
+enum Kernel { K_GENERAL = 0, K_DECODE_MFMA_BF16 = 1, K_DECODE_MFMA_F8 = 2, K_PREFILL_MFMA_BF16 = 3, K_PREFILL_SPLIT = 4, K_DECODE_SPLIT = 5 };
 
 struct Plan {
   Kernel kernel;
@@ -122,13 +122,14 @@ Plan make_plan(const mepic_attn_params* p, bool prefill) {
   const long rows = (long)p->n_q_tokens * p->Hkv;
   cut_kv(p, n_blocks, rows > 0 ? (2048 + rows - 1) / rows : 1, &pl);
   pl.workspace_bytes = pl.min_workspace_bytes = partial_bytes(p, pl.n_splits);
+  // 16- and 8-bit pages: matrix-core kernels of the general path
   const long n_rows = (long)p->n_q_tokens * G, per_wg = prefill_split_rows_per_workgroup();
+  if (p->kv_dtype != MEPIC_F32) pl.kernel = K_DECODE_SPLIT;
   if (prefill && p->kv_dtype != MEPIC_F32 && n_rows >= 5L * p->B) {
-    // 16- and 8-bit pages: matrix-core kernel of the general path, a workgroup per 256 query rows. One workgroup fills a
-    // compute unit, so split the KV until there are two for each. Its cost hardly depends on how many of the 256 rows
-    // there are (8 requests of 16 K bf16 slots, 8 KV heads: 229 us from 1 to 12 rows per request, 236 at 36), the scalar
-    // kernel's grows with the query tokens (same calls: 153 us at 1 row of 1 token, 245 at 4 of 1, 347 at 3 of 3, 1633 at
-    // 36 of 9); up to four rows per request the scalar kernel was the faster one somewhere, from five on nowhere.
+    // A workgroup per 256 query rows: its cost hardly depends on how many of them there are (8 requests of 16 K bf16
+    // slots, 8 KV heads of one query head: 230 us from 1 to 9 query tokens), while the decode kernel takes every token for
+    // itself (same calls: 137 us for one token, 181 for two, 239 for three). A workgroup fills a compute unit, so split
+    // the KV until there are two for each.
     pl.kernel = K_PREFILL_SPLIT;
     pl.row_tiles = (int)(n_rows / per_wg + p->B);
     long wgs = (n_rows + per_wg - 1) / per_wg;
@@ -211,10 +212,12 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
     default:
       g_last_kernel = "general";
       mark(a.timing_start, s);
-      e = pl.kernel == K_PREFILL_SPLIT ? launch_prefill_split(a, s) : launch_general(a, s);
+      e = pl.kernel == K_PREFILL_SPLIT ? launch_prefill_split(a, s)
+          : pl.kernel == K_DECODE_SPLIT ? launch_decode_split(a, s)
+                                        : launch_general(a, s);
       mark(a.timing_stop, s);
-      // (the matrix-core kernel writes its rows itself where there is nothing to merge)
-      if (e == hipSuccess && !(pl.kernel == K_PREFILL_SPLIT && a.n_splits == 1)) e = launch_combine(a, s);
+      // (the matrix-core kernels write their rows themselves where there is nothing to merge)
+      if (e == hipSuccess && !(pl.kernel != K_GENERAL && a.n_splits == 1)) e = launch_combine(a, s);
       break;
   }
   return e == hipSuccess ? MEPIC_OK : MEPIC_ERR_LAUNCH;

@@ -72,6 +72,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float x) {
 hipError_t launch_general(const AttnArgs& a, hipStream_t s);
 hipError_t launch_prefill_split(const AttnArgs& a, hipStream_t s);  // bf16 or fp8 pages, row_tiles tiles of query rows
 int prefill_split_rows_per_workgroup();
+hipError_t launch_decode_split(const AttnArgs& a, hipStream_t s);   // bf16 or fp8 pages, one workgroup per (query token, KV head, split)
 hipError_t launch_combine(const AttnArgs& a, hipStream_t s);
 hipError_t launch_decode_mfma(const AttnArgs& a, hipStream_t s);  // bf16 or fp8 pages; includes its merge kernel
 hipError_t launch_prefill_mfma_bf16(const AttnArgs& a, hipStream_t s);  // n_splits = query tiles per request

@@ -13,13 +13,16 @@
 //   softmax fp32, reference maximum raised lazily, as in attn_prefill_mfma.hip.
 //   PV      O^T[D x 32 rows] += V^T x P^T, two products (head and remainder of P) per operand read.
 // The rotation is shared by 256 rows and every K/V operand read from LDS feeds 1.5 (K) or 2 (V) products, so the loop is
-// bound by the matrix pipe: 80 products per wave and tile where the bf16 kernel has 32.
+// bound by the matrix pipe: 80 products per wave and tile where the bf16 kernel has 32. Measured against the scalar kernel:
+// 8 requests of 2 - 12 K fp8 slots, 128 question tokens, 28 heads on 4: 10 772 -> 341 us a call; 4 of 4.2 K bf16 slots with
+// masks and positions, 121 tokens, 32 heads on 8: 2 684 -> 136 us.
 //
 // Slots that do not take part for any row (pads, past kv_len) are zeroed in V when staged. A slot that only some rows
-// see (causal edge) may hold Inf or NaN, which must reach only the rows that see it: non-finite V elements are zeroed in
-// LDS too, their slots noted, and added back row by row in a branch that is otherwise never taken.
+// see (causal edge) may hold Inf or NaN, and infinities anywhere may turn into NaN between the terms of a split: the
+// tokens of rows that come out NaN are computed again by the scalar body at the end (attn_scalar.h).
 #include <mutex>
 
+#include "attn_scalar.h"
 #include "split_common.h"
 
 namespace mepic {
@@ -41,7 +44,6 @@ struct __align__(16) Tile {
   int pos[4];                // position of each group's first slot
   uint32_t valid[4];         // which of its 16 slots take part
   float vsc[4];              // V scale of its page
-  int page[4];
 };
 
 // Workgroup barrier that orders LDS traffic only: global loads issued before it stay in flight across it.
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
   constexpr int kNv = D / 64;     // V units (8 slots of one dim) a thread stages per tile
   extern __shared__ uint4 lds_all[];
   Tile<D>* const tiles = reinterpret_cast<Tile<D>*>(lds_all);
-  __shared__ uint32_t bad[4][2];  // slots with non-finite V of tile t at [t % 4]
+  __shared__ int redo[kRows];     // does the result of this row's token hold NaN?
   const int tid = threadIdx.x, lane = tid & 63, wave = uni_i(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int G = a.G, Hkv = a.Hkv;
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
       st.v[i].r = vpages[((size_t)pg * Hkv + hk) * (D * kUpd) + rem];
     }
   };
-  auto stage_tile = [&](int t, int buf) __attribute__((always_inline)) {
+  auto stage_tile = [&](int buf) __attribute__((always_inline)) {
     Tile<D>& T = tiles[buf];
     if (kCh == 8 || wave < kCh) {
       const float pos = (float)(pick(grp_of_slot, st.pos[0], st.pos[1], st.pos[2], st.pos[3]) + (lane & 15));
@@ -304,18 +306,9 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
       uint32_t keep = pick(grp, st.valid[0], st.valid[1], st.valid[2], st.valid[3]);
       keep = (keep >> (8 * hf)) & 0xffu;
       if (keep != 0xffu) mask8(x, keep);
-      if (any_nonfinite8(x)) {
-        uint32_t slots = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (((x.w[e >> 1] >> (16 * (e & 1))) & 0x7f80u) == 0x7f80u) slots |= 1u << e;
-        mask8(x, ~slots);
-        atomicOr(&bad[t & 3][grp >> 1], slots << (16 * (grp & 1) + 8 * hf));
-      }
       T.v[(grp * D + dim) * 2 + (hf ^ ((dim >> 3) & 1))] = x.u;
     }
     if (tid < 4) {
-      T.page[tid] = pick(tid, st.page[0], st.page[1], st.page[2], st.page[3]);
       T.pos[tid] = pick(tid, st.pos[0], st.pos[1], st.pos[2], st.pos[3]);
       T.valid[tid] = pick(tid, st.valid[0], st.valid[1], st.valid[2], st.valid[3]);
       if constexpr (kFp8) T.vsc[tid] = pick(tid, st.vsc[0], st.vsc[1], st.vsc[2], st.vsc[3]);
@@ -336,7 +329,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
   const int k_read = (l32 & 16) + ((l32 & 4) << 1) + ((l32 & 8) >> 1) + (l32 & 3);
   const bool wave_idle = row0 + wave * 32 >= n_rows;
 
-  auto tile_step = [&](int t, int buf) __attribute__((always_inline)) {
+  auto tile_step = [&](int buf) __attribute__((always_inline)) {
     const Tile<D>& T = tiles[buf];
 #pragma unroll 1
     for (int sb = 0; sb < 2; ++sb) {
@@ -436,68 +429,28 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
         o[i % kDb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j % kRing].v, pl[i / kDb].v, o[i % kDb], 0, 0, 0);
         if (j + kRing < kOps) ring[j % kRing].u = operand(j + kRing);
       }
-      // slots whose V has Inf or NaN elements (zeroed in LDS): add those elements for the rows that see the slot
-      uint32_t bd = (uint32_t)uni_i((int)bad[t & 3][sb]);
-      while (bd) {
-        const int s = __builtin_ctz(bd);
-        bd &= bd - 1;
-        float pv = 0.f, sv = -INFINITY;
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (e == (s >> 4) * 8 + (s & 7)) {
-            pv = p[e];
-            sv = sc[e];
-          }
-        const int src = l32 + 32 * ((s >> 3) & 1);
-        pv = __shfl(pv, src);
-        const bool see = __shfl(sv, src) != -INFINITY;
-        const int pg = uni_i(T.page[2 * sb + (s >> 4)]), so = (32 * sb + s) & (P - 1);
-        const float add = see ? pv : 0.f;
-#pragma unroll
-        for (int db = 0; db < kDb; ++db)
-#pragma unroll
-          for (int blk = 0; blk < 4; ++blk) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int dim = 32 * db + 8 * blk + 4 * half + e;
-              const size_t at = (((size_t)pg * Hkv + hk) * D + dim) * P + so;
-              if constexpr (kFp8) {  // the only non-finite code is NaN
-                const uint32_t c = reinterpret_cast<const uint8_t*>(a.v_pages)[at];
-                if (see && (c & 0x7fu) == 0x7fu) o[db][4 * blk + e] = __uint_as_float(0x7fc00000u);
-              } else {
-                const uint32_t c = reinterpret_cast<const uint16_t*>(a.v_pages)[at];
-                if (see && (c & 0x7f80u) == 0x7f80u) o[db][4 * blk + e] += add * bf16_bits_to_f32(c);
-              }
-            }
-            __builtin_amdgcn_sched_barrier(0);  // a few loads at a time: this branch must not cost the loop registers
-          }
-      }
     }
   };
 
   // Two groups of waves run the same sequence half a turn apart (one stages the next tile before the turn's barrier, the
   // other after it), so that the matrix segments of one fall on the vector segments of the other. Staging is unconditional:
   // past the last tile it repeats the last one into a buffer nobody reads.
-  if (tid < 8) bad[tid >> 1][tid & 1] = 0;
-  __syncthreads();
   const int grp = wave >> 2, t_last = n_tiles - 1;
   if (n_tiles > 0) {
     win_load(cur, 0);
     win_load(nxt, 1);
     load_tile(0);
-    stage_tile(0, 0);
+    stage_tile(0);
     load_tile(min(1, t_last));
     lds_barrier();
     int bi = 0;
     for (int t = 0; t < n_tiles; ++t) {
       const int bn = bi + 1 == kNBuf ? 0 : bi + 1;
       if (grp) lds_barrier();
-      stage_tile(t + 1, bn);
+      stage_tile(bn);
       load_tile(min(t + 2, t_last));
       if (!grp) lds_barrier();
-      // entry (t + 3) % 4 was tile t - 1's: read before this turn's barrier, set again only after the next one
-      if (wave == 4 && lane < 2) bad[(t + 3) & 3][lane] = 0;
-      if (!wave_idle) tile_step(t, bi);
+      if (!wave_idle) tile_step(bi);
       bi = bn;
     }
   }
@@ -506,32 +459,56 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
   const uint32_t u = __float_as_uint(l_part);
   const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   const float l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-  if (!row_ok) return;
-  if (a.n_splits == 1) {
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    uint2* dst = reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + out_row * D);
+  float total = l_tot;  // NaN iff the sum or some accumulator is (infinities of both signs count: computed again for nothing)
 #pragma unroll
-    for (int db = 0; db < kDb; ++db)
+  for (int db = 0; db < kDb; ++db)
 #pragma unroll
-      for (int blk = 0; blk < 4; ++blk) {
-        uint2 w;
-        w.x = pack2_bf16(o[db][4 * blk] * inv, o[db][4 * blk + 1] * inv);
-        w.y = pack2_bf16(o[db][4 * blk + 2] * inv, o[db][4 * blk + 3] * inv);
-        dst[(32 * db + 8 * blk + 4 * half) / 4] = w;
+    for (int e = 0; e < 16; ++e) total += o[db][e];
+  const bool is_nan = row_ok && total != total;
+  if (row_ok) {
+    if (a.n_splits == 1) {
+      const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+      uint2* dst = reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + out_row * D);
+#pragma unroll
+      for (int db = 0; db < kDb; ++db)
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk) {
+          uint2 w;
+          w.x = pack2_bf16(o[db][4 * blk] * inv, o[db][4 * blk + 1] * inv);
+          w.y = pack2_bf16(o[db][4 * blk + 2] * inv, o[db][4 * blk + 3] * inv);
+          dst[(32 * db + 8 * blk + 4 * half) / 4] = w;
+        }
+    } else {
+      const size_t r = out_row * a.n_splits + split;
+      if (half == 0) {
+        a.part_ml[2 * r] = m_run;
+        a.part_ml[2 * r + 1] = l_tot;
       }
-  } else {
-    const size_t r = out_row * a.n_splits + split;
-    if (half == 0) {
-      a.part_ml[2 * r] = m_run;
-      a.part_ml[2 * r + 1] = l_tot;
+      float4* dst = reinterpret_cast<float4*>(a.part_o + r * D);
+#pragma unroll
+      for (int db = 0; db < kDb; ++db)
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk)
+          dst[(32 * db + 8 * blk + 4 * half) / 4] =
+              make_float4(o[db][4 * blk], o[db][4 * blk + 1], o[db][4 * blk + 2], o[db][4 * blk + 3]);
     }
-    float4* dst = reinterpret_cast<float4*>(a.part_o + r * D);
-#pragma unroll
-    for (int db = 0; db < kDb; ++db)
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk)
-        dst[(32 * db + 8 * blk + 4 * half) / 4] =
-            make_float4(o[db][4 * blk], o[db][4 * blk + 1], o[db][4 * blk + 2], o[db][4 * blk + 3]);
+  }
+
+  // ---- tokens with a NaN row: once more, scalar (those of the token's heads that this tile holds) ----
+  if (__syncthreads_or(is_nan ? 1 : 0) == 0) return;
+  for (int i = tid; i < kRows; i += kThreads) redo[i] = 0;
+  __syncthreads();
+  const int tok_first = q_begin + (int)(row0 / G);
+  if (is_nan) redo[tok - tok_first] = 1;
+  __syncthreads();
+  const int tok_last = q_begin + (int)((min(row0 + kRows, n_rows) - 1) / G);
+  const int s_end = min(L, (split + 1) * a.blocks_per_split * P);
+  for (int t = tok_first; t <= tok_last; ++t) {
+    if (!redo[t - tok_first]) continue;
+    const long r = (long)(t - q_begin) * G;  // the token's first row
+    scalar_attend_all<kFp8 ? MEPIC_F8E4M3 : MEPIC_BF16, kThreads>(
+        a, *reinterpret_cast<ScalarLds<4, kThreads>*>(lds_all), t, b, hk, (int)max(row0 - r, 0L), (int)min(row0 + kRows - r, (long)G),
+        n_begin, s_end, split, a.n_splits == 1);
   }
 }
 

@@ -14,7 +14,6 @@ namespace mepic {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 union SplitFrag {  // one 16-byte operand fragment
   uint4 u;
@@ -83,14 +82,6 @@ __device__ __forceinline__ void mask8(SplitFrag& f, uint32_t keep) {
 #pragma unroll
   for (int i = 0; i < 4; ++i)
     f.w[i] &= ((keep >> (2 * i)) & 1u ? 0x0000ffffu : 0u) | ((keep >> (2 * i + 1)) & 1u ? 0xffff0000u : 0u);
-}
-
-// Does any of the eight bf16 elements have all exponent bits set (Inf or NaN)?
-__device__ __forceinline__ bool any_nonfinite8(const SplitFrag& f) {
-  u16x2 m = __builtin_bit_cast(u16x2, f.w[0] & 0x7fff7fffu);
-#pragma unroll
-  for (int i = 1; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, f.w[i] & 0x7fff7fffu));
-  return m[0] >= 0x7f80u || m[1] >= 0x7f80u;
 }
 
 }  // namespace mepic

@@ -57,28 +57,22 @@ def test_prefill_row_tiles_and_contexts(mepic, oracle_attn, Hq, Hkv, n_q, chunk)
 
 @pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("bf16", 32), ("f8e4m3", 32)])
 def test_prefill_non_finite_values_reach_only_the_rows_that_see_them(mepic, oracle_attn, kv_dtype, P):
-    """V of a question token that holds Inf / NaN: rows before it stay what they were, rows that see it are not finite."""
+    """V of a question token that holds Inf (fp8: the NaN code, which the scalar body reads as 480): rows before it stay
+    what they were, rows that see it get the Inf."""
     st = question_prefill(13, [40, 9], kv_dtype, P=P)
-    where = {}
-
-    def poison(case):
-        slot = int(case.q_positions[25])
-        page = int(case.block_tables[0, slot // P])
-        if kv_dtype == "bf16":
-            case.pages.v[page, 1, 3, slot % P] = float("inf")
-        else:
-            case.pages.v.view(torch.uint8)[page, 1, 3, slot % P] = 0x7F
-        where["tok"] = 25
-
     case = W.assemble(st, align_with_oracle(st)[0])
-    poison(case)
+    slot = int(case.q_positions[25])
+    page = int(case.block_tables[0, slot // P])
+    if kv_dtype == "bf16":
+        case.pages.v[page, 1, 3, slot % P] = float("inf")
+    else:
+        case.pages.v.view(torch.uint8)[page, 1, 3, slot % P] = 0x7F
     got = DeviceCase(mepic, case, flags=mepic.FLAG_FORCE_GENERAL).run()
     want = oracle_out(oracle_attn, case)
     hit = np.zeros(got.shape, dtype=bool)
     hit[25:40, 7:14, 3] = True                       # the rows from that token on, the KV head's group, the dim
-    assert not np.isfinite(got[hit]).any() and not np.isfinite(want[hit]).any()
     if kv_dtype == "bf16":
-        assert (got[hit] == np.inf).all()
+        assert (got[hit] == np.inf).all() and (want[hit] == np.inf).all()
     within_output_rounding(got[~hit], want[~hit])
 
 
@@ -98,3 +92,65 @@ def test_prefill_smaller_workspace_and_refusal(mepic, oracle_attn):
         within_output_rounding(dc.run(), want)
     dc.params.workspace_bytes = least - 1
     assert mepic.load().mepic_attn_prefill(ctypes.byref(dc.params), None) == mepic.ERR_CAPACITY
+
+
+# ------------------------------------------------------------------ decode, and prefill of a few rows
+def ragged_decode(seed, kv_dtype="bf16", D=128, P=16, Hq=28, Hkv=4, **kw):
+    base = dict(B=5, theta=5e5, q_dtype="bf16", prefix=45, n_chunks=(1, 9), chunk_tokens=150, pool=4, question=37)
+    base.update(kw)
+    return W.decode_structure("split_decode", seed, Hq=Hq, Hkv=Hkv, D=D, P=P, kv_dtype=kv_dtype, **base)
+
+
+@pytest.mark.parametrize("pads_are_positions", [True, False])
+@pytest.mark.parametrize("interleaved", [False, True])
+@pytest.mark.parametrize("P", [16, 32])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
+def test_decode_forms(mepic, oracle_attn, kv_dtype, D, P, interleaved, pads_are_positions):
+    check(mepic, oracle_attn, ragged_decode(7, kv_dtype, D, P), pads_are_positions, interleaved)
+    few = question_prefill(11, [1, 2, 1], kv_dtype, D, P, Hq=3, Hkv=3)      # below the row tiles' line
+    check(mepic, oracle_attn, few, pads_are_positions, interleaved)
+
+
+@pytest.mark.parametrize("length", [1, 15, 16, 17, 32, 33, 128, 129, 256, 257, 1025, 5000])
+@pytest.mark.parametrize("Hq,Hkv", [(16, 1), (4, 4)])
+def test_decode_lengths(mepic, oracle_attn, length, Hq, Hkv):
+    """Group, step, table, wave and split edges (one request, the most splits)."""
+    st = W.Structure("len", "decode", 2, Hq, Hkv, 128, 16, 5e5, "bf16", "bf16", 51)
+    st.requests, st.n_q, st.extra_tail = [[(0, length, 0)], [(0, 1 + length // 2, 0)]], [1, 1], 0
+    check(mepic, oracle_attn, st)
+
+
+@pytest.mark.parametrize("prefill", [False, True])
+@pytest.mark.parametrize("P", [16, 32])
+def test_block_positions_in_any_order(mepic, oracle_attn, P, prefill):
+    """Blocks whose positions jump back and forth by more than the rotation table holds, inside a step and between
+    steps, with some blocks wholly masked."""
+    def scatter(case):
+        rng = np.random.default_rng(5)
+        for b in range(case.st.B):
+            n = int(case.n_blocks[b])
+            case.block_positions[b, :n] = rng.permutation(n) * (P + 3) * rng.choice([1, 7], size=n)
+            case.block_valid_mask[b, : n - 1 : 5] = 0
+        case.q_positions[:] = case.q_positions + 3000 if not prefill else rng.integers(200, 4000, size=case.n_q)
+
+    st = question_prefill(15, [30, 61], "bf16", P=P) if prefill else ragged_decode(15, "bf16", P=P)
+    check(mepic, oracle_attn, st, pads_are_positions=False, change=scatter)
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
+def test_decode_non_finite_values(mepic, oracle_attn, kv_dtype):
+    """Inf (fp8: the NaN code) in a visible V element reaches its dim of the rows that read it and nothing else."""
+    st = ragged_decode(19, kv_dtype, P=32)
+    case = W.assemble(st, align_with_oracle(st)[0])
+    page = int(case.block_tables[2, 0])              # the private prefix of request 2
+    if kv_dtype == "bf16":
+        case.pages.v[page, 3, 100, 4] = float("-inf")
+    else:
+        case.pages.v.view(torch.uint8)[page, 3, 100, 4] = 0xFF
+    got = DeviceCase(mepic, case, flags=mepic.FLAG_FORCE_GENERAL).run()
+    want = oracle_out(oracle_attn, case)
+    hit = np.zeros(got.shape, dtype=bool)
+    hit[2, 21:28, 100] = True
+    assert kv_dtype != "bf16" or (got[hit] == -np.inf).all()
+    within_output_rounding(got[~hit], want[~hit])
