@@ -54,6 +54,7 @@
 
 #include "attn_common.h"
 #include "decode_plan.h"
+#include "merge_partials.h"
 
 namespace mepic {
 namespace {
@@ -227,7 +228,9 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
   typedef typename std::conditional<kFp8, float2, float4>::type RotK;
   __shared__ RotK rotK[kNV * 16][64];  // slot rotation: index v*16 + (u*2 + h)*4 + w
   __shared__ float4 rotS[8][64];       // step rotation R(-32 kNV): index h*4 + w
-  __shared__ float2 freq_lds[kBatched ? 64 : 1];  // batched: {hi, lo} of the frequencies, index kg*16 + pair
+  // {hi, lo} of the frequencies, index kg*16 + pair: read per lane, for which the kernel arguments themselves are slow
+  // (vector loads of the argument buffer; the tables and every Q' set-up waited microseconds for them)
+  __shared__ float2 freq_lds[64];
   __shared__ uint4 q_lds[kBatched ? kWaves * 4 : 1][64];  // batched: q of the current piece, [wave*4 + fragment][lane]
   extern __shared__ int cum[];     // cum[b] = steps of the requests before b; B + 1 entries
 
@@ -260,20 +263,18 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
   // bf16 (dims i and i + 64 sit in k-steps h and h + 2), i(p) = 16kg + p for fp8. ----
   auto freq_of = [&](int pidx) { return kFp8 ? 16 * kg + pidx : 32 * (pidx >> 3) + 8 * kg + (pidx & 7); };
   const int slot_u0 = 8 * (n16 >> 2) + (n16 & 3);
-  if constexpr (kBatched) {
-    // a piece of a run starts every few steps: its Q' set-up reads the frequencies from LDS, not from memory
-    if (wave == 0) {
-      const int i = freq_of(n16);  // lane (kg, n16) fills entry kg*16 + n16
-      freq_lds[lane] = make_float2(a.freq_hi[i], a.freq_lo[i]);
-    }
+  if (wave == kWaves - 1) {
+    const int i = freq_of(n16);  // lane (kg, n16) fills entry kg*16 + n16
+    freq_lds[lane] = make_float2(a.freq_hi[i], a.freq_lo[i]);
   }
+  __syncthreads();
   for (int idx = wave; idx < kNV * 16 + 8; idx += kWaves) {
     const bool is_k = idx < kNV * 16;
     const int h = (idx >> 2) & 1, w = idx & 3;  // idx = v*16 + (u*2 + h)*4 + w for rotK, kNV*16 + h*4 + w for rotS
     const float pos = is_k ? (float)(slot_u0 + 4 * ((idx >> 3) & 1) + 32 * (idx >> 4)) : -32.0f * kNV;
-    const int i = freq_of(8 * h + 2 * w);     // pairs 8h + 2w and 8h + 2w + 1 have consecutive frequencies
-    const float t0 = turns_frac(pos, a.freq_hi[i], a.freq_lo[i]);
-    const float t1 = turns_frac(pos, a.freq_hi[i + 1], a.freq_lo[i + 1]);
+    const float2 f0 = freq_lds[kg * 16 + 8 * h + 2 * w], f1 = freq_lds[kg * 16 + 8 * h + 2 * w + 1];
+    const float t0 = turns_frac(pos, f0.x, f0.y);
+    const float t1 = turns_frac(pos, f1.x, f1.y);
     const float4 r = make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1),
                                  __builtin_amdgcn_sinf(t1));
     if (!is_k) {
@@ -833,11 +834,11 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const int i = freq_of(8 * h + e);
+          const float2 f = freq_lds[kg * 16 + 8 * h + e];
           const uint32_t wl = qf[h].w[e >> 1], wh = qf[h + 2].w[e >> 1];
           const float x0 = qs * ((e & 1) ? __uint_as_float(wl & 0xffff0000u) : bf16_bits_to_f32(wl & 0xffffu));
           const float x1 = qs * ((e & 1) ? __uint_as_float(wh & 0xffff0000u) : bf16_bits_to_f32(wh & 0xffffu));
-          const float t = turns_frac(delta, a.freq_hi[i], a.freq_lo[i]);
+          const float t = turns_frac(delta, f.x, f.y);
           const float c = __builtin_amdgcn_cosf(t), sn = __builtin_amdgcn_sinf(t);
           qlo[h][e] = x0 * c - x1 * sn;
           qhi[h][e] = x1 * c + x0 * sn;
@@ -880,70 +881,25 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
   }
 }
 
-// Merge ns partials (reference max in log2 units, sum, un-normalised row of 128) into one bf16 output row.
-// 128 threads: four groups of 32 take every fourth partial, a thread four dims of it, so that enough loads are in
-// flight for the merge to run at memory speed when a request has tens of partials; LDS adds the groups up.
-__device__ __forceinline__ void merge_row(const float* ml, const float* po, int ns, uint16_t* out_row) {
-  __shared__ float4 num_s[4][32];
-  __shared__ float den_s[4];
-  const int part = threadIdx.x >> 5, dq = threadIdx.x & 31;
-  float m = -INFINITY;
-  for (int s = 0; s < ns; ++s) m = fmaxf(m, ml[2 * s]);
-  float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-  float den = 0.f;
-  if (m != -INFINITY) {
-    const float4* po4 = reinterpret_cast<const float4*>(po);
-    int s = part;
-    for (; s + 4 < ns; s += 8) {  // two partials per turn
-      const float w0 = __builtin_amdgcn_exp2f(ml[2 * s] - m), w1 = __builtin_amdgcn_exp2f(ml[2 * s + 8] - m);
-      const float4 x0 = po4[(size_t)s * (kD / 4) + dq], x1 = po4[(size_t)(s + 4) * (kD / 4) + dq];
-      num.x += w0 * x0.x + w1 * x1.x; num.y += w0 * x0.y + w1 * x1.y;
-      num.z += w0 * x0.z + w1 * x1.z; num.w += w0 * x0.w + w1 * x1.w;
-      den += w0 * ml[2 * s + 1] + w1 * ml[2 * s + 9];
-    }
-    if (s < ns) {
-      const float w0 = __builtin_amdgcn_exp2f(ml[2 * s] - m);
-      const float4 x0 = po4[(size_t)s * (kD / 4) + dq];
-      num.x += w0 * x0.x; num.y += w0 * x0.y; num.z += w0 * x0.z; num.w += w0 * x0.w;
-      den += w0 * ml[2 * s + 1];
-    }
-  }
-  num_s[part][dq] = num;
-  if (dq == 0) den_s[part] = den;
-  __syncthreads();
-  if (part == 0) {
-    const float4 a1 = num_s[1][dq], a2 = num_s[2][dq], a3 = num_s[3][dq];
-    // the same order of additions in every thread
-    const float d = (den_s[0] + den_s[1]) + (den_s[2] + den_s[3]);
-    const float inv = d > 0.f ? 1.f / d : 0.f;
-    const float o0 = ((num.x + a1.x) + (a2.x + a3.x)) * inv, o1 = ((num.y + a1.y) + (a2.y + a3.y)) * inv;
-    const float o2 = ((num.z + a1.z) + (a2.z + a3.z)) * inv, o3 = ((num.w + a1.w) + (a2.w + a3.w)) * inv;
-    uint2 packed;
-    packed.x = f32_to_bf16_bits(o0) | (f32_to_bf16_bits(o1) << 16);
-    packed.y = f32_to_bf16_bits(o2) | (f32_to_bf16_bits(o3) << 16);
-    reinterpret_cast<uint2*>(out_row)[dq] = packed;
-  }
-}
-
 // Merge the partials of one (request, query head). Request b owns steps [cum[b], cum[b+1]) of its KV
 // head's sequence; the waves that cut that range wrote partials 0 .. (cum[b+1]-1)/chunk - cum[b]/chunk.
-__global__ __launch_bounds__(128) void combine_streamk_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(kMergeThreads) void combine_streamk_kernel(const AttnArgs a) {
   const int row = blockIdx.x;
   const int b = row / a.Hq;
   const int c0 = a.part_meta[b], c1 = a.part_meta[b + 1], chunk = a.part_meta[a.B + 1];
   const int ns = c1 > c0 ? (c1 - 1) / chunk - c0 / chunk + 1 : 0;
-  merge_row(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, ns,
-            reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
+  merge_row<kD>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, a.n_splits, ns,
+                reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
 }
 
 // Merge for the batched variant: request b has n_part[b] partials per head, in slots 0 .. n_part[b]-1.
-__global__ __launch_bounds__(128) void combine_batched_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(kMergeThreads) void combine_batched_kernel(const AttnArgs a) {
   const int row = blockIdx.x;
   const int b = row / a.Hq;
   const int n_runs = a.plan[1];
   const int ns = a.plan[plan_off_npart(n_runs) + b];
-  merge_row(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, ns,
-            reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
+  merge_row<kD>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, a.n_splits, ns,
+                reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
 }
 
 // Self-test of dot_rotate_block: words[i] = {e0..e3, ca0, cb0, ca1, cb1, ca2, cb2, ca3, cb3}; out[i] = {l0..l3, h0..h3}.
@@ -988,7 +944,7 @@ hipError_t launch_decode_mfma(const AttnArgs& a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (a.timing_stop) (void)hipEventRecord(reinterpret_cast<hipEvent_t>(a.timing_stop), s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(combine_streamk_kernel, dim3(a.n_q * a.Hq), dim3(kD), 0, s, a);
+  hipLaunchKernelGGL(combine_streamk_kernel, dim3(a.n_q * a.Hq), dim3(kMergeThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1014,7 +970,7 @@ hipError_t launch_decode_mfma_batched(const AttnArgs& a, int n_runs, hipStream_t
   hipError_t e = hipGetLastError();
   if (a.timing_stop) (void)hipEventRecord(reinterpret_cast<hipEvent_t>(a.timing_stop), s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(combine_batched_kernel, dim3(a.n_q * a.Hq), dim3(kD), 0, s, a);
+  hipLaunchKernelGGL(combine_batched_kernel, dim3(a.n_q * a.Hq), dim3(kMergeThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -65,8 +65,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   extern __shared__ uint4 smem[];
   float4(*const tab)[kTab] = reinterpret_cast<float4(*)[kTab]>(smem);  // [frequencies 2 c, 2 c + 1][slot] {c0, s0, c1, s1}
   __shared__ uint4 q_lds[kKs][64];  // un-rotated q, granule j of every lane's head
+  __shared__ __align__(16) float2 freq[D / 2];  // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
 
   const int tid = threadIdx.x, lane = tid & 63, wave = uni_i(tid >> 6), n16 = lane & 15, kg = lane >> 4;
+  if (tid < D / 2) freq[tid] = make_float2(a.freq_hi[tid], a.freq_lo[tid]);
   const int G = a.G, Hkv = a.Hkv;
   const int hk = (int)(blockIdx.x % (unsigned)Hkv), split = (int)blockIdx.z;
   const int t = (int)(blockIdx.y * (gridDim.x / (unsigned)Hkv) + blockIdx.x / (unsigned)Hkv);
@@ -162,10 +164,11 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   const float qs = row_ok ? a.qk_scale_log2 : 0.f;
 
   // ---- rotation table ----
+  __syncthreads();
   for (int i = tid; i < D / 4 * kTab; i += kThreads) {
     const int c = i / kTab, s = i % kTab;
-    const float t0 = turns_frac((float)s, a.freq_hi[2 * c], a.freq_lo[2 * c]);
-    const float t1 = turns_frac((float)s, a.freq_hi[2 * c + 1], a.freq_lo[2 * c + 1]);
+    const float t0 = turns_frac((float)s, freq[2 * c].x, freq[2 * c].y);
+    const float t1 = turns_frac((float)s, freq[2 * c + 1].x, freq[2 * c + 1].y);
     tab[c][s] = make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1),
                             __builtin_amdgcn_sinf(t1));
   }
@@ -179,7 +182,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     int again = 0;
     asm volatile("" : "+v"(again));  // q and the frequencies are fetched anew each time: they must not stay in registers
     auto rot = [&](float x0, float x1, int i, float& y0, float& y1) __attribute__((always_inline)) {
-      const float tr = turns_frac(delta, a.freq_hi[i + again], a.freq_lo[i + again]);
+      const float2 f = freq[i + again];
+      const float tr = turns_frac(delta, f.x, f.y);
       const float c = __builtin_amdgcn_cosf(tr), s = __builtin_amdgcn_sinf(tr);
       y0 = (x0 * c - x1 * s) * qs;
       y1 = (x1 * c + x0 * s) * qs;

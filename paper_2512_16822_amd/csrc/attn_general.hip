@@ -5,6 +5,7 @@
 // heads that share the KV head reuse every rotated key. Partial (max, sum, un-normalised output) per split go to the
 // workspace; combine_kernel merges them.
 #include "attn_scalar.h"
+#include "merge_partials.h"
 
 namespace mepic {
 namespace {
@@ -39,29 +40,12 @@ __global__ __launch_bounds__(kThreads) void attn_general_kernel(const AttnArgs a
   scalar_attend<MEPIC_F32, GM, kThreads>(a, lds, t, b, hk, 0, a.G, n_begin, n_end, split, false);
 }
 
-// Merge the per-split partials of one (query token, query head): with m* the largest split maximum,
-// out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s (all zeros when no slot took part).
-__global__ __launch_bounds__(128) void combine_kernel(const AttnArgs a) {
-  const int row = blockIdx.x, d = threadIdx.x;
-  if (d >= a.D) return;
-  const float* ml = a.part_ml + (size_t)row * a.n_splits * 2;
-  const float* po = a.part_o + (size_t)row * a.n_splits * a.D;
-  float m = -INFINITY;
-  for (int s = 0; s < a.n_splits; ++s) m = fmaxf(m, ml[2 * s]);
-  float num = 0.f, den = 0.f;
-  if (m != -INFINITY) {
-    for (int s = 0; s < a.n_splits; ++s) {
-      const float ms = ml[2 * s];
-      if (ms == -INFINITY) continue;
-      const float w = exp2f(ms - m);
-      num += w * po[(size_t)s * a.D + d];
-      den += w * ml[2 * s + 1];
-    }
-  }
-  const float o = den > 0.f ? num / den : 0.f;
-  const size_t idx = (size_t)row * a.D + d;
-  if (a.q_dtype == MEPIC_F32) reinterpret_cast<float*>(a.out)[idx] = o;
-  else reinterpret_cast<uint16_t*>(a.out)[idx] = (uint16_t)f32_to_bf16_bits(o);
+// Merge the per-split partials of one (query token, query head).
+template <int D, typename Out>
+__global__ __launch_bounds__(kMergeThreads) void combine_kernel(const AttnArgs a) {
+  const int row = blockIdx.x;
+  merge_row<D>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * D, a.n_splits, a.n_splits,
+               reinterpret_cast<Out*>(a.out) + (size_t)row * D);
 }
 
 }  // namespace
@@ -77,7 +61,12 @@ hipError_t launch_general(const AttnArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(combine_kernel, dim3(a.n_q * a.Hq), dim3(128), 0, s, a);
+  const dim3 grid(a.n_q * a.Hq), block(kMergeThreads);
+  const bool f32 = a.q_dtype == MEPIC_F32;
+  if (a.D == 128 && f32) hipLaunchKernelGGL((combine_kernel<128, float>), grid, block, 0, s, a);
+  else if (a.D == 128) hipLaunchKernelGGL((combine_kernel<128, uint16_t>), grid, block, 0, s, a);
+  else if (f32) hipLaunchKernelGGL((combine_kernel<64, float>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((combine_kernel<64, uint16_t>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -78,6 +78,9 @@ __device__ __forceinline__ size_t rope_entry(int p, int pc, int e) {
 }
 
 __global__ __launch_bounds__(256) void rope_table_kernel(const AttnArgs a, int n_pos) {
+  __shared__ float2 freq[kD / 2];  // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
+  if (threadIdx.x < kD / 2) freq[threadIdx.x] = make_float2(a.freq_hi[threadIdx.x], a.freq_lo[threadIdx.x]);
+  __syncthreads();
   const int idx = blockIdx.x * 256 + threadIdx.x;   // (p / 64, pc, e, p % 64), the entry index itself
   if (idx >= n_pos * 16) return;
   const int p = ((idx >> 10) << 6) + (idx & 63), pc = (idx >> 7) & 7, e = (idx >> 6) & 1;
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(256) void rope_table_kernel(const AttnArgs a, int n
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int i = 8 * pc + 4 * e + j;
-    const float t = turns_frac((float)p, a.freq_hi[i], a.freq_lo[i]);
+    const float t = turns_frac((float)p, freq[i].x, freq[i].y);
     r.h[2 * j] = (_Float16)__builtin_amdgcn_cosf(t);
     r.h[2 * j + 1] = (_Float16)__builtin_amdgcn_sinf(t);
   }
@@ -111,6 +114,9 @@ struct __align__(16) Tile {
 __global__ __launch_bounds__(kThreads, 1) void prefill_mfma_bf16_kernel(const AttnArgs a) {
   extern __shared__ uint4 lds_all[];
   Tile* const tiles = reinterpret_cast<Tile*>(lds_all);   // kNBuf tiles
+  __shared__ float2 freq[kD / 2];   // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
+  if (threadIdx.x < kD / 2) freq[threadIdx.x] = make_float2(a.freq_hi[threadIdx.x], a.freq_lo[threadIdx.x]);
+  __syncthreads();
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int G = a.G, Hkv = a.Hkv;
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_mfma_bf16_kernel(const At
           const uint32_t wl = raw[ks].w[w], wh = raw[ks + 4].w[w];
           const float x0 = qs * (e ? __uint_as_float(wl & 0xffff0000u) : bf16_bits_to_f32(wl & 0xffffu));
           const float x1 = qs * (e ? __uint_as_float(wh & 0xffff0000u) : bf16_bits_to_f32(wh & 0xffffu));
-          const float t = turns_frac((float)pos_q, a.freq_hi[i], a.freq_lo[i]);
+          const float t = turns_frac((float)pos_q, freq[i].x, freq[i].y);
           const float c = __builtin_amdgcn_cosf(t), s = __builtin_amdgcn_sinf(t);
           lo[e] = x0 * c - x1 * s;
           hi[e] = x1 * c + x0 * s;

@@ -70,6 +70,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
   Tile<D>* const tiles = reinterpret_cast<Tile<D>*>(lds_all);
   __shared__ int redo[kRows];     // does the result of this row's token hold NaN?
   const int tid = threadIdx.x, lane = tid & 63, wave = uni_i(tid >> 6);
+  __shared__ float2 freq[D / 2];  // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
+  if (tid < D / 2) freq[tid] = make_float2(a.freq_hi[tid], a.freq_lo[tid]);
   const int l32 = lane & 31, half = lane >> 5;
   const int G = a.G, Hkv = a.Hkv;
   const int hk = (int)(blockIdx.x % (unsigned)Hkv);
@@ -101,11 +103,12 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
   const int pos_q = a.q_positions[tok];
   const size_t out_row = (size_t)tok * a.Hq + (size_t)hk * G + g;
   SplitFrag qh[kKs], ql[kKs];
+  __syncthreads();
   {
     const uint4* q4 = reinterpret_cast<const uint4*>(a.q) + out_row * (D / 8);
     const float qs = row_ok ? a.qk_scale_log2 : 0.f;
     auto rotate = [&](float x0, float x1, int i, float& y0, float& y1) __attribute__((always_inline)) {
-      const float t = turns_frac((float)pos_q, a.freq_hi[i], a.freq_lo[i]);
+      const float t = turns_frac((float)pos_q, freq[i].x, freq[i].y);
       const float c = __builtin_amdgcn_cosf(t), s = __builtin_amdgcn_sinf(t);
       y0 = (x0 * c - x1 * s) * qs;
       y1 = (x1 * c + x0 * s) * qs;

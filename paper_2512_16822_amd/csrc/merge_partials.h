@@ -1,0 +1,106 @@
+// Merge of split-K partials: one workgroup of 128 threads per (query token, query head). Partial s holds a reference maximum
+// (log2 units), a sum and an un-normalised row of D fp32 values; with m* the largest maximum,
+//   out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s          (all zeros when no slot took part).
+//
+// What a merge of tens of partials costs is memory latency, not bytes, so there is as little as possible in its chain of
+// dependent loads: lane i of every wave takes the maximum and the sum of partial i (64 at a time, one coalesced load; the
+// serial scan over the maxima that this replaces cost a load latency per few partials), and each thread's first
+// row is requested before the number of partials is known, the next ones before the weights are. Groups of D / 4 threads take every kGroups-th partial, a thread four
+// dims of it; LDS adds the groups up. Measured (kernel time) on 128 rows of 54 partials:
+// 7.4 -> 4.6 us, 2048 rows of the batched decode plan: 6.1 -> 5.0 us, 256 rows of up to 256: 7.0 -> 6.0 us.
+#pragma once
+#include "attn_common.h"
+
+namespace mepic {
+
+template <typename Out> __device__ __forceinline__ void store4(Out* dst, const float4& v);
+template <> __device__ __forceinline__ void store4<float>(float* dst, const float4& v) { *reinterpret_cast<float4*>(dst) = v; }
+template <> __device__ __forceinline__ void store4<uint16_t>(uint16_t* dst, const float4& v) {
+  uint2 p;
+  p.x = f32_to_bf16_bits(v.x) | (f32_to_bf16_bits(v.y) << 16);
+  p.y = f32_to_bf16_bits(v.z) | (f32_to_bf16_bits(v.w) << 16);
+  *reinterpret_cast<uint2*>(dst) = p;
+}
+
+// Reductions over the wave without LDS: rotations inside rows of 16 lanes, then the two lane-swap instructions.
+template <int kRor>
+__device__ __forceinline__ float row_ror(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + kRor, 0xf, 0xf, true));
+}
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float x, Op op) {
+  x = op(x, row_ror<1>(x));
+  x = op(x, row_ror<2>(x));
+  x = op(x, row_ror<4>(x));
+  x = op(x, row_ror<8>(x));
+  uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  u = __float_as_uint(x);
+  const auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+constexpr int kMergeThreads = 128;
+
+// ml: [room][2], po: [room][D], out: the row; ns <= room partials exist (room is known before ns has been loaded, so the
+// first loads go by room).
+template <int D, typename Out>
+__device__ __forceinline__ void merge_row(const float* ml, const float* po, int room, int ns, Out* out) {
+  constexpr int kCols = D / 4, kGroups = kMergeThreads / kCols;
+  __shared__ float4 num_s[kGroups][kCols];
+  const int lane = threadIdx.x & 63, part = threadIdx.x / kCols, dq = threadIdx.x % kCols;
+  const float2* ml2 = reinterpret_cast<const float2*>(ml);
+  const float4* po4 = reinterpret_cast<const float4*>(po) + dq;
+  float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+  float den = 0.f, m = -INFINITY;
+  auto row = [&](int s) { return s < ns ? po4[(size_t)s * kCols] : make_float4(0.f, 0.f, 0.f, 0.f); };
+  auto add = [&](const float4& x, float w) {
+    if (w != 0.f) {  // a partial nothing took part in, or that does not exist, may hold anything
+      num.x += w * x.x; num.y += w * x.y; num.z += w * x.z; num.w += w * x.w;
+    }
+  };
+  float2 e = lane < room ? ml2[lane] : make_float2(-INFINITY, 0.f);
+  float4 a = part < room ? po4[(size_t)part * kCols] : make_float4(0.f, 0.f, 0.f, 0.f), b;
+  for (int s0 = 0; s0 < ns; s0 += 64) {  // (one turn but for the longest contexts)
+    int s = s0 + part;
+    if (s0 > 0) {
+      e = ml2[min(s0 + lane, ns - 1)];
+      a = row(s);
+    }
+    b = row(s + kGroups);
+    if (s0 + lane >= ns) e = make_float2(-INFINITY, 0.f);
+    const int s_end = min(ns, s0 + 64);
+    const float m_new = fmaxf(m, wave_reduce(e.x, [](float x, float y) { return fmaxf(x, y); }));
+    if (m_new != m && m != -INFINITY) {
+      const float f = __builtin_amdgcn_exp2f(m - m_new);
+      num.x *= f; num.y *= f; num.z *= f; num.w *= f;
+      den *= f;
+    }
+    m = m_new;
+    const float w = e.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(e.x - m);
+    den += wave_reduce(w == 0.f ? 0.f : w * e.y, [](float x, float y) { return x + y; });
+    // (every lane runs as many turns as the first group: the shuffles need all of them)
+    for (int i = s0; i < s_end; i += 2 * kGroups, s += 2 * kGroups) {
+      const float4 x = a, y = b;
+      a = row(s + 2 * kGroups);
+      b = row(s + 3 * kGroups);
+      add(x, __shfl(w, (s - s0) & 63));
+      add(y, __shfl(w, (s + kGroups - s0) & 63));
+    }
+  }
+  num_s[part][dq] = num;
+  __syncthreads();
+  if (part == 0) {
+#pragma unroll
+    for (int p = 1; p < kGroups; ++p) {
+      const float4 x = num_s[p][dq];
+      num.x += x.x; num.y += x.y; num.z += x.z; num.w += x.w;
+    }
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    store4<Out>(out + 4 * dq, den > 0.f ? make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv)
+                                        : make_float4(0.f, 0.f, 0.f, 0.f));
+  }
+}
+
+}  // namespace mepic
