@@ -14,7 +14,9 @@
 // whose groups lie too far apart is taken in two turns). What bounds it is the vector work on K (widen, rotate, split:
 // six instructions per element), not the products.
 //
-// 64 requests of 4.3 K bf16 slots with valid masks and block positions, 32 heads on 8: 382 us (scalar) -> 146 us a call.
+// 64 requests of 4.3 K bf16 slots with valid masks and block positions, 32 heads on 8: 382 us (scalar) -> 107 us a call
+// (146 before the loads got scalar bases and a fixed order, so that a step's waits leave the next step's loads in flight, and
+// one round of workgroups); where no page is shared, 64 requests of 4 - 6 K slots, 249 us = 5.4 TB/s: HBM.
 //
 // A NaN in the merged result (operand splits make NaN of some infinities) sends the workgroup through the scalar body.
 #include <mutex>
@@ -47,6 +49,16 @@ __device__ __forceinline__ float sum_over_kgroups(float x) {
   const uint32_t v = __float_as_uint(y);
   const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Keep the elements whose bit of `keep` (4 bits) is set, zero the others.
+__device__ __forceinline__ void mask4(uint2& x, uint32_t keep) {
+  x.x &= (keep & 1u ? 0x0000ffffu : 0u) | (keep & 2u ? 0xffff0000u : 0u);
+  x.y &= (keep & 4u ? 0x0000ffffu : 0u) | (keep & 8u ? 0xffff0000u : 0u);
+}
+__device__ __forceinline__ void mask4(uint32_t& x, uint32_t keep) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x &= (keep >> e) & 1u ? ~0u : ~(0xffu << (8 * e));
 }
 
 template <int D>
@@ -131,28 +143,44 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   }
 
   // ---- K and V of a step. K row n16 of product u is slot n16 of group u. ----
+  // (addresses: a page's base is uniform and a lane's place in it never changes, so that the loads take a scalar base, a
+  // 32-bit lane offset and an immediate - as 64-bit sums per load the addresses alone were 130 vector instructions a step)
   using RawT = decltype(Raw8<kFp8>::r);
-  const RawT* kpages = reinterpret_cast<const RawT*>(a.k_pages);
-  const Raw4* vpages = reinterpret_cast<const Raw4*>(a.v_pages);
+  constexpr int kElem = kFp8 ? 1 : 2;
+  constexpr size_t kHeadBytes = (size_t)D * P * kElem;       // one KV head of a page, K or V alike
   Raw8<kFp8> kf[2][kKs];
   Raw4 vf[2][kNt];
-  auto issue = [&](int pg0, int pg1) __attribute__((always_inline)) {
+  const uint32_t k_off = kFp8 ? (uint32_t)(((kg >> 1) * P + n16) * 16 + (kg & 1) * 8) : (uint32_t)((kg * P + n16) * 16);
+  const uint32_t v_off = (uint32_t)((n16 * P + 4 * kg) * kElem);
+  constexpr uint32_t kStepK = (kFp8 ? 2 : 4) * P * 16;        // bytes between a lane's granules of successive k-steps
+  auto issue_k = [&](int pg0, int pg1) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const size_t head = (size_t)(u ? pg1 : pg0) * Hkv + hk;
-      const int s0 = P == 16 ? 0 : 16 * u;  // steps start at multiples of 32: a page of 32 is a whole step
+      // steps start at multiples of 32: a page of 32 is a whole step
+      const char* base = reinterpret_cast<const char*>(a.k_pages) + ((size_t)(u ? pg1 : pg0) * Hkv + hk) * kHeadBytes +
+                         (P == 16 ? 0 : 16 * 16 * u);
 #pragma unroll
-      for (int j = 0; j < kKs; ++j) {
-        const int c = 4 * j + kg;  // chunk of 8 dims
-        if constexpr (kFp8) kf[u][j].r = kpages[(head * (D / 16 * P) + (size_t)(c >> 1) * P + s0 + n16) * 2 + (c & 1)];
-        else kf[u][j].r = kpages[head * (D / 8 * P) + (size_t)c * P + s0 + n16];
-      }
-#pragma unroll
-      for (int nt = 0; nt < kNt; ++nt) vf[u][nt] = vpages[((head * D + 16 * nt + n16) * P + s0 + 4 * kg) / 4];
+      for (int j = 0; j < kKs; ++j) kf[u][j].r = *reinterpret_cast<const RawT*>(base + j * kStepK + k_off);
     }
   };
-  auto page_of = [&](int st, int u) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(cur.page, (2 * st + u) & 63); };
-  if (n_st > 0) issue(page_of(0, 0), page_of(0, 1));
+  auto issue_v = [&](int pg0, int pg1) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const char* base = reinterpret_cast<const char*>(a.v_pages) + ((size_t)(u ? pg1 : pg0) * Hkv + hk) * kHeadBytes +
+                         (P == 16 ? 0 : 16 * kElem * u);
+#pragma unroll
+      for (int nt = 0; nt < kNt; ++nt) vf[u][nt] = *reinterpret_cast<const Raw4*>(base + nt * (16 * P * kElem) + v_off);
+    }
+  };
+  int np0 = 0, np1 = 0;  // pages of the next step
+  if (n_st > 0) {
+    np0 = __builtin_amdgcn_readlane(cur.page, 0);
+    np1 = __builtin_amdgcn_readlane(cur.page, 1);
+    issue_k(np0, np1);
+    __builtin_amdgcn_sched_barrier(0);  // K before V on every path: the loop's waits count on it
+    issue_v(np0, np1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   // ---- q of this lane's head, un-rotated: granule j as stored ----
   const bool row_ok = n16 < G;
@@ -257,7 +285,88 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   float m_run = -INFINITY, l_part = 0.f;
   int base = 0;
   bool have_base = false;
+  auto inside = [&](int ps) __attribute__((always_inline)) {
+    const long d = (long)ps - base;
+    return d >= 0 && d <= kTab - 16;
+  };
 
+  // Softmax and output products of one turn; slots of the step outside vis0 / vis1 get no weight.
+  auto attend = [&](floatx4 (&sc)[2], uint32_t vis0, uint32_t vis1, int l0) __attribute__((always_inline)) {
+    float vs0 = 1.f, vs1 = 1.f;
+    if constexpr (kFp8) {
+      sc[0] *= __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0));
+      sc[1] *= __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0 + 1));
+      vs0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.vsc), l0));
+      vs1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.vsc), l0 + 1));
+    }
+    const bool partial = (vis0 & vis1) != 0xffffu;
+    if (partial) {
+      asm volatile("");  // a branch, not selects in every step
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!(((u ? vis1 : vis0) >> (4 * kg + e)) & 1u)) sc[u][e] = -INFINITY;
+    }
+    const float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
+                           fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
+    if (__any(mx > m_run + kRescaleSlack)) {
+      const float m_new = fmaxf(m_run, max_over_kgroups(mx));
+      const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_part *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {  // accumulator rows of this lane are heads 4 kg + e; their factors live in lanes 4 kg + e
+        const float ar = __shfl(alpha, 4 * kg + e);
+#pragma unroll
+        for (int nt = 0; nt < kNt; ++nt) o[nt][e] *= ar;
+      }
+    }
+    const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
+    float pf[8];
+    float psum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      pf[e] = __builtin_amdgcn_exp2f(sc[e >> 2][e & 3] - m_use);
+      psum += pf[e];
+    }
+    l_part += psum;
+    if constexpr (kFp8) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pf[e] *= e < 4 ? vs0 : vs1;
+    }
+    if (partial) {  // slots that take no part may hold anything, NaN included, and so may the scale of a page of such
+      asm volatile("");
+      // (V in place: a group whose turn is yet to come keeps its slots, under probabilities of zero)
+      const uint32_t all0 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0), all1 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0 + 1);
+      const uint32_t keep0 = (all0 >> (4 * kg)) & 0xfu, keep1 = (all1 >> (4 * kg)) & 0xfu;
+#pragma unroll
+      for (int nt = 0; nt < kNt; ++nt) {
+        mask4(vf[0][nt], keep0);
+        mask4(vf[1][nt], keep1);
+      }
+      if constexpr (kFp8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (!(((e < 4 ? vis0 : vis1) >> (4 * kg + (e & 3))) & 1u)) pf[e] = 0.f;
+      }
+    }
+    SplitFrag ph, pl;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) split2(pf[2 * w], pf[2 * w + 1], ph.w[w], pl.w[w]);
+#pragma unroll
+    for (int nt = 0; nt < kNt; ++nt) {
+      Raw8<kFp8> both;
+      if constexpr (kFp8) both.r = make_uint2(vf[0][nt], vf[1][nt]);
+      else both.r = make_uint4(vf[0][nt].x, vf[0][nt].y, vf[1][nt].x, vf[1][nt].y);
+      const SplitFrag vb = bf16_of8<kFp8>(both);
+      o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph.v, vb.v, o[nt], 0, 0, 0);
+      o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl.v, vb.v, o[nt], 0, 0, 0);
+    }
+  };
+
+  // K of the next step is requested as soon as the scores are done with the registers, V after its products; always, so
+  // that the waits can count the loads in flight (past the last step the last pages come once more).
   for (int st = 0; st < n_st; ++st) {
     const int l0 = (2 * st) & 63;
     if (st > 0 && l0 == 0) {
@@ -265,91 +374,39 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       ++win;
       if (n_st > 32 * (win + 1)) win_load(nxt, win + 1);
     }
-    if (st > 0) issue(page_of(st, 0), page_of(st, 1));
-    const int ps0 = __builtin_amdgcn_readlane(cur.pos, l0), ps1 = __builtin_amdgcn_readlane(cur.pos, l0 + 1);
-    uint32_t todo0 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0), todo1 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0 + 1);
-    while (todo0 | todo1) {  // one turn unless the groups' positions are too far apart for one table
-      auto inside = [&](int ps) __attribute__((always_inline)) {
-        const long d = (long)ps - base;
-        return d >= 0 && d <= kTab - 16;
-      };
-      if (!have_base || (todo0 && !inside(ps0)) || (!todo0 && !inside(ps1))) {
-        base = todo0 ? ps0 : ps1;
-        have_base = true;
-        rotate_q(base);
-      }
-      const bool in1 = inside(ps1);
-      const uint32_t vis0 = todo0, vis1 = in1 ? todo1 : 0u;
-      todo0 = 0;
-      if (in1) todo1 = 0;
-
-      floatx4 sc[2];
-      sc[0] = score(0, ps0 - base);
-      sc[1] = score(1, ps1 - base);
-      float ks0 = 1.f, ks1 = 1.f, vs0 = 1.f, vs1 = 1.f;
-      if constexpr (kFp8) {
-        ks0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0));
-        ks1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0 + 1));
-        vs0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.vsc), l0));
-        vs1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.vsc), l0 + 1));
-        sc[0] *= ks0;
-        sc[1] *= ks1;
-      }
-      const bool partial = (vis0 & vis1) != 0xffffu;
-      if (partial) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (!(((u ? vis1 : vis0) >> (4 * kg + e)) & 1u)) sc[u][e] = -INFINITY;
-      }
-      const float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
-                             fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-      if (__any(mx > m_run + kRescaleSlack)) {
-        const float m_new = fmaxf(m_run, max_over_kgroups(mx));
-        const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        l_part *= alpha;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {  // accumulator rows of this lane are heads 4 kg + e; their factors live in lanes 4 kg + e
-          const float ar = __shfl(alpha, 4 * kg + e);
-#pragma unroll
-          for (int nt = 0; nt < kNt; ++nt) o[nt][e] *= ar;
-        }
-      }
-      const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
-      float pf[8];
-      float psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        pf[e] = __builtin_amdgcn_exp2f(sc[e >> 2][e & 3] - m_use);
-        psum += pf[e];
-      }
-      l_part += psum;
-      if constexpr (kFp8) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pf[e] *= e < 4 ? vs0 : vs1;
-      }
-      if (partial) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)  // (the V scale of a page that nothing of takes part may be anything)
-          if (kFp8 && !(((e < 4 ? vis0 : vis1) >> (4 * kg + (e & 3))) & 1u)) pf[e] = 0.f;
-      }
-      SplitFrag ph, pl;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) split2(pf[2 * w], pf[2 * w + 1], ph.w[w], pl.w[w]);
-      const uint32_t keep = ((vis0 >> (4 * kg)) & 0xfu) | (((vis1 >> (4 * kg)) & 0xfu) << 4);
-#pragma unroll
-      for (int nt = 0; nt < kNt; ++nt) {
-        Raw8<kFp8> both;
-        if constexpr (kFp8) both.r = make_uint2(vf[0][nt], vf[1][nt]);
-        else both.r = make_uint4(vf[0][nt].x, vf[0][nt].y, vf[1][nt].x, vf[1][nt].y);
-        SplitFrag vb = bf16_of8<kFp8>(both);
-        if (partial) mask8(vb, keep);  // slots that take no part may hold anything, NaN included
-        o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph.v, vb.v, o[nt], 0, 0, 0);
-        o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl.v, vb.v, o[nt], 0, 0, 0);
-      }
+    const int cp0 = np0, cp1 = np1;
+    if (st + 1 < n_st) {
+      const int pages = l0 == 62 ? nxt.page : cur.page, l1 = (l0 + 2) & 63;
+      np0 = __builtin_amdgcn_readlane(pages, l1);
+      np1 = __builtin_amdgcn_readlane(pages, l1 + 1);
     }
+    const int ps0 = __builtin_amdgcn_readlane(cur.pos, l0), ps1 = __builtin_amdgcn_readlane(cur.pos, l0 + 1);
+    const uint32_t vis0 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0), vis1 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0 + 1);
+    if (!have_base || (vis0 && !inside(ps0)) || (!vis0 && vis1 && !inside(ps1))) {
+      base = vis0 ? ps0 : ps1;
+      have_base = true;
+      rotate_q(base);
+    }
+    const bool both = inside(ps1);  // (a group without visible slots may be rotated by anything)
+    floatx4 sc[2];
+    sc[0] = score(0, ps0 - base);
+    sc[1] = score(1, ps1 - base);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_k(np0, np1);
+    __builtin_amdgcn_sched_barrier(0);
+    attend(sc, vis0, both ? vis1 : 0u, l0);
+    if (!both && vis1) {  // the step's groups lie too far apart for one table: the second one takes a turn of its own
+      issue_k(cp0, cp1);
+      base = ps1;
+      rotate_q(base);
+      sc[0] = floatx4{0.f, 0.f, 0.f, 0.f};
+      sc[1] = score(1, 0);
+      attend(sc, 0u, vis1, l0);
+      issue_k(np0, np1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    issue_v(np0, np1);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   // ---- merge the waves (the table's LDS is free now), write the split's partial or, if it is the only one, the rows ----

@@ -26,7 +26,8 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {  // round t
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// Two fp32 values -> their packed bf16 heads and packed bf16 remainders.
+// Two fp32 values -> their packed bf16 heads and packed bf16 remainders. (x - head as a two-term dot product of the packed
+// word with (-1, 0) saves two of the six instructions and measured no faster here and 5 % slower in the prefill kernel.)
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
   hi = pack2_bf16(x0, x1);
   lo = pack2_bf16(x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xffff0000u));
