@@ -39,9 +39,9 @@ enum Kernel { K_GENERAL = 0, K_DECODE_MFMA_BF16 = 1, K_DECODE_MFMA_F8 = 2, K_PRE
 
 struct Plan {
   Kernel kernel;
-  int n_splits, blocks_per_split, row_tiles;
+  int n_splits, blocks_per_split, kv_tiles;
   size_t workspace_bytes;      // what the size query reports
-  size_t min_workspace_bytes;  // what a call must bring; with less than workspace_bytes it cuts the KV into fewer splits
+  size_t min_workspace_bytes;  // what a call must bring; with less than workspace_bytes another kernel serves it
 };
 
 size_t partial_bytes(const mepic_attn_params* p, long n_splits) {
@@ -79,7 +79,8 @@ int check_shapes(const mepic_attn_params* p, bool prefill) {
   return MEPIC_OK;
 }
 
-Plan make_plan(const mepic_attn_params* p, bool prefill) {
+// no_pieces: do without the prefill kernel that needs more workspace than the scalar one did.
+Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false) {
   Plan pl{};
   const int G = p->Hq / p->Hkv;
   int max_kv = p->max_kv_len > 0 ? p->max_kv_len : p->max_blocks * p->P;
@@ -122,38 +123,32 @@ Plan make_plan(const mepic_attn_params* p, bool prefill) {
   const long rows = (long)p->n_q_tokens * p->Hkv;
   cut_kv(p, n_blocks, rows > 0 ? (2048 + rows - 1) / rows : 1, &pl);
   pl.workspace_bytes = pl.min_workspace_bytes = partial_bytes(p, pl.n_splits);
-  // 16- and 8-bit pages: matrix-core kernels of the general path
-  const long n_rows = (long)p->n_q_tokens * G, per_wg = prefill_split_rows_per_workgroup();
+  // 16- and 8-bit pages: matrix-core kernels of the general path. The workspace is at least what the scalar kernel's
+  // plan asks for; more of it lets a prefill cut its work evenly.
   if (p->kv_dtype != MEPIC_F32) {
     // Its workgroups (two fill a compute unit) build a rotation table first and its partials cost a merge: one round of
     // workgroups, not the scalar kernel's four. 64 requests of 4 K bf16 slots, D 128, 8 KV heads: 202 us at 2048
-    // workgroups, 194 at 1024, 187 at 512; lengths mixed 1:32 255 / 278 / 270, 8 mixed requests 51 / 44 / 39. The
-    // workspace stays what the scalar kernel's plan asked for.
+    // workgroups, 194 at 1024, 187 at 512; lengths mixed 1:32 255 / 278 / 270, 8 mixed requests 51 / 44 / 39.
     pl.kernel = K_DECODE_SPLIT;
     cut_kv(p, n_blocks, rows > 0 ? (512 + rows - 1) / rows : 1, &pl);
   }
-  if (prefill && p->kv_dtype != MEPIC_F32 && n_rows >= 5L * p->B) {
+  const long n_rows = (long)p->n_q_tokens * G;
+  if (prefill && p->kv_dtype != MEPIC_F32 && n_rows >= 5L * p->B && !no_pieces) {
     // A workgroup per 256 query rows: its cost hardly depends on how many of them there are (8 requests of 16 K bf16
-    // slots, 8 KV heads of one query head: 230 us from 1 to 9 query tokens), while the decode kernel takes every token for
-    // itself (same calls: 137 us for one token, 181 for two, 239 for three). A workgroup fills a compute unit, so split
-    // the KV until there are two for each.
-    pl.kernel = K_PREFILL_SPLIT;
-    pl.row_tiles = (int)(n_rows / per_wg + p->B);
-    long wgs = (n_rows + per_wg - 1) / per_wg;
-    if (wgs < p->B) wgs = p->B;
-    wgs *= p->Hkv;
-    cut_kv(p, n_blocks, wgs > 0 ? (512 + wgs - 1) / wgs : 1, &pl);
-    if (partial_bytes(p, pl.n_splits) > pl.workspace_bytes) pl.workspace_bytes = partial_bytes(p, pl.n_splits);
+    // slots, 8 KV heads: 230 us from 1 to 9 query tokens), while the decode kernel takes every token for itself (same
+    // calls: 137 us for one token, 181 for two, 239 for three).
+    int kv_tiles, min_run, max_pieces;
+    prefill_split_plan(p->B, p->Hkv, n_rows, max_kv, &kv_tiles, &min_run, &max_pieces);
+    if (max_pieces > 0) {
+      pl.kernel = K_PREFILL_SPLIT;
+      pl.kv_tiles = kv_tiles;
+      pl.blocks_per_split = min_run;
+      pl.n_splits = max_pieces;
+      const size_t bytes = partial_bytes(p, max_pieces) + (size_t)p->n_q_tokens * p->Hq * sizeof(int32_t);
+      if (bytes > pl.workspace_bytes) pl.workspace_bytes = bytes;
+    }
   }
   return pl;
-}
-
-// A workspace between the least and the reported size: as many splits as it holds partials for.
-void fit_workspace(const mepic_attn_params* p, Plan* pl) {
-  if (pl->kernel != K_PREFILL_SPLIT || p->workspace_bytes >= pl->workspace_bytes) return;
-  const long room = (long)(p->workspace_bytes / partial_bytes(p, 1));
-  const int n_blocks = pl->n_splits * pl->blocks_per_split;  // rounded up to whole splits: only the bound matters
-  if (room < pl->n_splits) cut_kv(p, n_blocks, room, pl);
 }
 
 void mark(void* ev, hipStream_t s) {
@@ -173,7 +168,7 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
 
   Plan pl = make_plan(p, prefill);
   if (pl.workspace_bytes && (!p->workspace || p->workspace_bytes < pl.min_workspace_bytes)) return MEPIC_ERR_CAPACITY;
-  fit_workspace(p, &pl);
+  if (p->workspace_bytes < pl.workspace_bytes) pl = make_plan(p, prefill, true);
   if (reinterpret_cast<uintptr_t>(p->workspace) & 255u) return MEPIC_ERR_INVALID;
 
   AttnArgs a{};
@@ -189,7 +184,7 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
   a.interleaved = (p->flags & MEPIC_FLAG_ROPE_INTERLEAVED) ? 1 : 0;
   a.kv_read_once = (p->flags & MEPIC_FLAG_KV_READ_ONCE) ? 1 : 0;
   a.causal = prefill ? 1 : 0;
-  a.n_splits = pl.n_splits; a.blocks_per_split = pl.blocks_per_split; a.row_tiles = pl.row_tiles;
+  a.n_splits = pl.n_splits; a.blocks_per_split = pl.blocks_per_split; a.kv_tiles = pl.kv_tiles;
   const double sm = p->sm_scale > 0.f ? (double)p->sm_scale : 1.0 / std::sqrt((double)p->D);
   a.qk_scale_log2 = (float)(sm * 1.4426950408889634);
   // frequencies in turns per position, f_i / (2 pi), as a two-float sum
@@ -219,12 +214,14 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
     default:
       g_last_kernel = "general";
       mark(a.timing_start, s);
-      e = pl.kernel == K_PREFILL_SPLIT ? launch_prefill_split(a, s)
-          : pl.kernel == K_DECODE_SPLIT ? launch_decode_split(a, s)
-                                        : launch_general(a, s);
+      if (pl.kernel == K_PREFILL_SPLIT) {
+        e = launch_prefill_split(a, s);
+        break;
+      }
+      e = pl.kernel == K_DECODE_SPLIT ? launch_decode_split(a, s) : launch_general(a, s);
       mark(a.timing_stop, s);
-      // (the matrix-core kernels write their rows themselves where there is nothing to merge)
-      if (e == hipSuccess && !(pl.kernel != K_GENERAL && a.n_splits == 1)) e = launch_combine(a, s);
+      // (the matrix-core kernel writes its rows itself where there is nothing to merge)
+      if (e == hipSuccess && !(pl.kernel == K_DECODE_SPLIT && a.n_splits == 1)) e = launch_combine(a, s);
       break;
   }
   return e == hipSuccess ? MEPIC_OK : MEPIC_ERR_LAUNCH;

@@ -37,7 +37,7 @@ struct AttnArgs {
   int32_t interleaved, causal;
   int32_t kv_read_once;  // hint: pages are not shared between requests (matrix-core decode: non-temporal loads)
   int32_t n_splits, blocks_per_split;
-  int32_t row_tiles;                 // split-precision kernels: tiles of query rows over all requests
+  int32_t kv_tiles;                  // split-precision prefill: most KV tiles of a request
   float qk_scale_log2;               // sm_scale * log2(e): scores are kept in log2 units
   // Rotary frequencies in turns per position, f_i / (2 pi), split into two floats whose sum carries
   // ~48 bits, so that position * frequency can be reduced modulo one turn without fp64.
@@ -70,8 +70,8 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float x) {
 
 // Launchers (host). Each returns a hipError_t from the launch.
 hipError_t launch_general(const AttnArgs& a, hipStream_t s);
-hipError_t launch_prefill_split(const AttnArgs& a, hipStream_t s);  // bf16 or fp8 pages, row_tiles tiles of query rows
-int prefill_split_rows_per_workgroup();
+hipError_t launch_prefill_split(const AttnArgs& a, hipStream_t s);  // bf16 or fp8 pages; includes its merge kernel and timing_stop
+void prefill_split_plan(int B, int Hkv, long n_rows, int max_kv_len, int* kv_tiles, int* min_run, int* max_pieces);
 hipError_t launch_decode_split(const AttnArgs& a, hipStream_t s);   // bf16 or fp8 pages, one workgroup per (query token, KV head, split)
 hipError_t launch_combine(const AttnArgs& a, hipStream_t s);
 hipError_t launch_decode_mfma(const AttnArgs& a, hipStream_t s);  // bf16 or fp8 pages; includes its merge kernel

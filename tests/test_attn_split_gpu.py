@@ -55,6 +55,21 @@ def test_prefill_row_tiles_and_contexts(mepic, oracle_attn, Hq, Hkv, n_q, chunk)
     check(mepic, oracle_attn, question_prefill(9, n_q, "bf16", Hq=Hq, Hkv=Hkv, chunk=chunk), chunk != 64)
 
 
+@pytest.mark.parametrize("Hkv", [1, 3])
+def test_prefill_work_cut_across_requests(mepic, oracle_attn, Hkv):
+    """More requests than a wave scans at once, of very different lengths, some without queries or without slots: runs of
+    the work sequence begin and end anywhere, row tiles come whole and in pieces."""
+    rng = np.random.default_rng(23)
+    n_q = [int(x) for x in rng.integers(0, 40, size=70)]
+    n_q[3], n_q[50] = 0, 300
+    st = question_prefill(23, n_q, "bf16", P=32, Hq=4 * Hkv, Hkv=Hkv, chunk=90)
+    st.requests[50].insert(0, (0, 3000, 0))
+
+    def change(case):
+        case.kv_lens[[5, 60]] = 0
+    check(mepic, oracle_attn, st, change=change)
+
+
 @pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("bf16", 32), ("f8e4m3", 32)])
 def test_prefill_non_finite_values_reach_only_the_rows_that_see_them(mepic, oracle_attn, kv_dtype, P):
     """V of a question token that holds Inf (fp8: the NaN code, which the scalar body reads as 480): rows before it stay
@@ -77,8 +92,8 @@ def test_prefill_non_finite_values_reach_only_the_rows_that_see_them(mepic, orac
 
 
 def test_prefill_smaller_workspace_and_refusal(mepic, oracle_attn):
-    """The size query reports what the preferred split of the KV needs; less, down to one partial per row as the scalar
-    kernel needed, still runs, and less than that is refused."""
+    """The size query reports what the even cut of the work needs; less, down to what the scalar kernel's plan needed, still
+    runs, and less than that is refused."""
     st = question_prefill(17, [60, 33], "f8e4m3", P=32, chunk=900)
     case, dc = check(mepic, oracle_attn, st)
     want = oracle_out(oracle_attn, case)
