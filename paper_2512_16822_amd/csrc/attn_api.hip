@@ -35,7 +35,7 @@ int scratch_of_current_device(void** out) {
 
 thread_local const char* g_last_kernel = "";
 
-enum Kernel { K_GENERAL = 0, K_DECODE_MFMA_BF16 = 1, K_DECODE_MFMA_F8 = 2, K_PREFILL_MFMA_BF16 = 3, K_PREFILL_SPLIT = 4, K_DECODE_SPLIT = 5 };
+enum Kernel { K_DECODE_MFMA_BF16, K_DECODE_MFMA_F8, K_PREFILL_MFMA_BF16, K_PREFILL_SPLIT, K_DECODE_SPLIT, K_DECODE_F32 };
 
 struct Plan {
   Kernel kernel;
@@ -48,18 +48,36 @@ size_t partial_bytes(const mepic_attn_params* p, long n_splits) {
   return (size_t)p->n_q_tokens * p->Hq * n_splits * (p->D + 2) * sizeof(float);
 }
 
-// Cut n_blocks into at most `want` splits of whole 256-slot tiles.
-void cut_kv(const mepic_attn_params* p, int n_blocks, long want, Plan* pl) {
-  const int tile_blocks = 256 / p->P;
-  const int max_splits = (n_blocks + tile_blocks - 1) / tile_blocks;
+// Splits of the KV the general path's workspace is sized for: a split is a whole number of 256-slot tiles, enough of
+// them for 2048 workgroups of one (query token, KV head, split).
+int general_splits(const mepic_attn_params* p, int n_blocks) {
+  const long rows = (long)p->n_q_tokens * p->Hkv;
+  const int tile_blocks = 256 / p->P, max_splits = (n_blocks + tile_blocks - 1) / tile_blocks;
+  long want = rows > 0 ? (2048 + rows - 1) / rows : 1;
   if (want > max_splits) want = max_splits;
   if (want > 1024) want = 1024;
   if (want < 1) want = 1;
   int bps = (int)((n_blocks + want - 1) / want);
   bps = (bps + tile_blocks - 1) / tile_blocks * tile_blocks;
   if (bps < tile_blocks) bps = tile_blocks;
-  pl->blocks_per_split = bps;
-  pl->n_splits = n_blocks > 0 ? (n_blocks + bps - 1) / bps : 1;
+  return n_blocks > 0 ? (n_blocks + bps - 1) / bps : 1;
+}
+
+// The splits the general path's decode kernels use, at most that many: one round of the `resident` workgroups that run at a
+// time (each builds a rotation table first, and partials cost a merge), but none where the context is so short that
+// the merge's launch, about four turns of 128 slots, costs more than the turns it saves. Measured (us): 64 requests of 4 K bf16
+// slots, D 128, 8 KV heads: 187 with 512 workgroups, 194 with 1024, 202 with 2048; lengths mixed 1:32 270, 278, 255; 8 such
+// requests 39 with 512, 51 with 2048; 40 mixed requests, 12 heads: 202 with 960, 246 with 480; one fp32 request of 289
+// slots 9.0 without a second split, 11.1 with.
+void cut_kv(const mepic_attn_params* p, int n_blocks, int resident, Plan* pl) {
+  const long rows = (long)p->n_q_tokens * p->Hkv;
+  const int turn_blocks = 128 / p->P, turns = (n_blocks + turn_blocks - 1) / turn_blocks;
+  const int most = general_splits(p, n_blocks);
+  int n = rows > 0 ? (int)((resident + rows - 1) / rows < most ? (resident + rows - 1) / rows : most) : 1;
+  if (turns <= (turns + n - 1) / n + 4) n = 1;
+  const int per = turns > 0 ? (turns + n - 1) / n : 1;
+  pl->blocks_per_split = per * turn_blocks;
+  pl->n_splits = turns > 0 ? (turns + per - 1) / per : 1;
 }
 
 int check_shapes(const mepic_attn_params* p, bool prefill) {
@@ -88,7 +106,6 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
   const int n_blocks = (max_kv + p->P - 1) / p->P;
   const bool plain = !p->block_positions && !p->block_valid_mask &&
                      !(p->flags & (MEPIC_FLAG_ROPE_INTERLEAVED | MEPIC_FLAG_FORCE_GENERAL));
-  pl.kernel = K_GENERAL;
 
   const bool mfma_bf16 = p->q_dtype == MEPIC_BF16 && p->kv_dtype == MEPIC_BF16 && p->D == 128 && p->P == 16;
   const bool mfma_fp8 = p->q_dtype == MEPIC_BF16 && p->kv_dtype == MEPIC_F8E4M3 && p->D == 128 && p->P == 32;
@@ -118,20 +135,10 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
     return pl;
   }
 
-  // General path: one workgroup per (query token, KV head, split); a split is a whole number of
-  // 256-slot tiles. Enough splits to put ~8 workgroups on each of the 256 compute units.
-  const long rows = (long)p->n_q_tokens * p->Hkv;
-  cut_kv(p, n_blocks, rows > 0 ? (2048 + rows - 1) / rows : 1, &pl);
-  pl.workspace_bytes = pl.min_workspace_bytes = partial_bytes(p, pl.n_splits);
-  // 16- and 8-bit pages: matrix-core kernels of the general path. The workspace is at least what the scalar kernel's
-  // plan asks for; more of it lets a prefill cut its work evenly.
-  if (p->kv_dtype != MEPIC_F32) {
-    // Its workgroups (two fill a compute unit) build a rotation table first and its partials cost a merge: one round of
-    // workgroups, not the scalar kernel's four. 64 requests of 4 K bf16 slots, D 128, 8 KV heads: 202 us at 2048
-    // workgroups, 194 at 1024, 187 at 512; lengths mixed 1:32 255 / 278 / 270, 8 mixed requests 51 / 44 / 39.
-    pl.kernel = K_DECODE_SPLIT;
-    cut_kv(p, n_blocks, rows > 0 ? (512 + rows - 1) / rows : 1, &pl);
-  }
+  // General path: one workgroup per (query token, KV head, split).
+  pl.workspace_bytes = pl.min_workspace_bytes = partial_bytes(p, general_splits(p, n_blocks));
+  pl.kernel = p->kv_dtype == MEPIC_F32 ? K_DECODE_F32 : K_DECODE_SPLIT;
+  cut_kv(p, n_blocks, pl.kernel == K_DECODE_F32 && p->D == 128 ? 256 : 512, &pl);
   const long n_rows = (long)p->n_q_tokens * G;
   if (prefill && p->kv_dtype != MEPIC_F32 && n_rows >= 5L * p->B && !no_pieces) {
     // A workgroup per 256 query rows: its cost hardly depends on how many of them there are (8 requests of 16 K bf16
@@ -218,10 +225,9 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
         e = launch_prefill_split(a, s);
         break;
       }
-      e = pl.kernel == K_DECODE_SPLIT ? launch_decode_split(a, s) : launch_general(a, s);
+      e = pl.kernel == K_DECODE_SPLIT ? launch_decode_split(a, s) : launch_decode_f32(a, s);
       mark(a.timing_stop, s);
-      // (the matrix-core kernel writes its rows itself where there is nothing to merge)
-      if (e == hipSuccess && !(pl.kernel == K_DECODE_SPLIT && a.n_splits == 1)) e = launch_combine(a, s);
+      if (e == hipSuccess && a.n_splits > 1) e = launch_combine(a, s);  // (a single split writes its rows itself)
       break;
   }
   return e == hipSuccess ? MEPIC_OK : MEPIC_ERR_LAUNCH;

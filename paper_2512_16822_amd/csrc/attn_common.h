@@ -69,7 +69,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float x) {
 }
 
 // Launchers (host). Each returns a hipError_t from the launch.
-hipError_t launch_general(const AttnArgs& a, hipStream_t s);
+hipError_t launch_decode_f32(const AttnArgs& a, hipStream_t s);     // fp32 pages, one workgroup per (query token, KV head, split)
 hipError_t launch_prefill_split(const AttnArgs& a, hipStream_t s);  // bf16 or fp8 pages; includes its merge kernel and timing_stop
 void prefill_split_plan(int B, int Hkv, long n_rows, int max_kv_len, int* kv_tiles, int* min_run, int* max_pieces);
 hipError_t launch_decode_split(const AttnArgs& a, hipStream_t s);   // bf16 or fp8 pages, one workgroup per (query token, KV head, split)

@@ -34,23 +34,6 @@ constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr int kTab = 128;             // slots the rotation table covers
 constexpr float kRescaleSlack = 6.f;  // the reference maximum may lag the true one by this much (log2 units)
 
-__device__ __forceinline__ float max_over_kgroups(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float sum_over_kgroups(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
 // Keep the elements whose bit of `keep` (4 bits) is set, zero the others.
 __device__ __forceinline__ void mask4(uint2& x, uint32_t keep) {
   x.x &= (keep & 1u ? 0x0000ffffu : 0u) | (keep & 2u ? 0xffff0000u : 0u);

@@ -169,3 +169,4 @@ def test_decode_non_finite_values(mepic, oracle_attn, kv_dtype):
     hit[2, 21:28, 100] = True
     assert kv_dtype != "bf16" or (got[hit] == -np.inf).all()
     within_output_rounding(got[~hit], want[~hit])
+
