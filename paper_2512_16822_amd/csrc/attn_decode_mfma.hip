@@ -239,25 +239,39 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
 
   // ---- cum[]: steps before each item of the sequence (requests, or the plan's runs) ----
   const int n_items = kBatched ? sload(a.plan, 1) : a.B;
+  // Plain walker, up to 64 requests: every wave scans the lengths itself and keeps them in its lanes (lane b: request b's
+  // length and the steps up to its end), so that its first page ids are on their way before the tables are built.
+  const bool in_lanes = !kBatched && a.B <= 64;
+  int len_lane = 0, cum_lane = 0;
+  auto scan = [&](int x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    return x;
+  };
+  auto steps_of = [](int len) { return ((len + kP - 1) / kP + kBps - 1) / kBps; };
   if constexpr (kBatched) {
     for (int i = tid; i <= n_items; i += 64 * kWaves) cum[i] = a.plan[plan_off_cum(n_items) + i];
+  } else if (in_lanes) {
+    len_lane = lane < a.B ? a.kv_lens[lane] : 0;
+    cum_lane = scan(steps_of(len_lane));
   } else if (wave == 0) {
     // from kv_lens (a step = two blocks); one wave scans
     int carry = 0;
     for (int base = 0; base < a.B; base += 64) {
       const int b = base + lane;
-      int x = 0;
-      if (b < a.B) x = ((a.kv_lens[b] + kP - 1) / kP + kBps - 1) / kBps;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-      }
+      const int x = scan(b < a.B ? steps_of(a.kv_lens[b]) : 0);
       if (b < a.B) cum[b + 1] = carry + x;
       carry += __shfl(x, 63);
     }
     if (lane == 0) cum[0] = 0;
   }
+  auto cum_at = [&](int i) __attribute__((always_inline)) {  // i wave-uniform
+    if (in_lanes) return i == 0 ? 0 : __builtin_amdgcn_readlane(cum_lane, i - 1);
+    return uni(cum[i]);
+  };
   // ---- rotation constants. As holder of K rows, row n16 of product u is slot32 = 8*(n16/4) + 4u + n16%4 of
   // the step. A lane owns 16 rotary pairs p = 8h + e (h in {0,1}, e < 8): frequency i(p) = 32h + 8kg + e for
   // bf16 (dims i and i + 64 sit in k-steps h and h + 2), i(p) = 16kg + p for fp8. ----
@@ -267,7 +281,90 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
     const int i = freq_of(n16);  // lane (kg, n16) fills entry kg*16 + n16
     freq_lds[lane] = make_float2(a.freq_hi[i], a.freq_lo[i]);
   }
+  const int hk = (int)blockIdx.x % Hkv;
+  const int wk = ((int)blockIdx.x / Hkv) * kWaves + wave, n_k = ((int)gridDim.x / Hkv) * kWaves;
+  int chunk = 0, pos_begin = 0, pos_end = 0;
+  auto cut = [&]() __attribute__((always_inline)) {  // this wave's part of the sequence
+    if constexpr (kBatched) {  // the planner placed the cuts between the waves (the host checked n_k against the plan)
+      const int32_t* cuts = a.plan + plan_off_cuts(n_items, a.B, sload(a.plan, 7));
+      pos_begin = sload(cuts, wk);
+      pos_end = sload(cuts, wk + 1);
+    } else {
+      const int T = cum_at(n_items);
+      chunk = max((T + n_k - 1) / n_k, a.blocks_per_split);  // blocks_per_split carries the minimum chunk
+      pos_begin = wk * chunk;
+      pos_end = min(pos_begin + chunk, T);
+      if (blockIdx.x == 0 && wave == 0) {  // what the merge kernel needs to find each request's partials
+        for (int i = lane; i <= a.B; i += 64) {
+          if (in_lanes) {
+            if (i < a.B) a.part_meta[i + 1] = cum_lane;
+          } else {
+            a.part_meta[i] = cum[i];
+          }
+        }
+        if (lane == 0) {
+          a.part_meta[0] = 0;
+          a.part_meta[a.B + 1] = chunk;
+        }
+      }
+    }
+  };
+  // ---- plain walker: a run of steps of one request, and what its start waits for (page ids, q): requested for the first
+  // run before the tables are built, for every other one while the run before it is computed ----
+  const uint4* q4 = reinterpret_cast<const uint4*>(a.q);
+  struct Seg {
+    int b, c0, seg_end, n_st, step_first, L;
+    int bt0, bt1, posq;  // lane i: page of block i (64 + i) of the run; position of the query token
+    Frag qf[4];
+  };
+  auto seg_load = [&](Seg& sg, int pos, int b) __attribute__((always_inline)) {
+    int c0 = cum_at(b), c1 = cum_at(b + 1);
+    while (c1 <= pos) {  // skip requests without steps
+      ++b;
+      c0 = c1;
+      c1 = cum_at(b + 1);
+    }
+    sg.b = b; sg.c0 = c0; sg.seg_end = min(pos_end, c1); sg.n_st = sg.seg_end - pos; sg.step_first = pos - c0;
+    sg.L = in_lanes ? __builtin_amdgcn_readlane(len_lane, b) : sload(a.kv_lens, b);
+    const int j0 = kBps * sg.step_first, jl = (sg.L + kP - 1) / kP - 1;
+    const size_t row = (size_t)b * a.max_blocks;
+    sg.bt0 = safe_page(a.block_tables[row + min(j0 + lane, jl)], a.num_pages);
+    sg.bt1 = safe_page(a.block_tables[row + min(j0 + 64 + lane, jl)], a.num_pages);
+    sg.posq = a.q_positions[b];
+    // q of head n16: the lane's four 8-element chunks (rows >= G are zeroed through the scale):
+    // qf[h] = pairs 8h.. low dims, qf[h + 2] = the same pairs' high dims (+64)
+    const size_t qrow = ((size_t)b * a.Hq + (size_t)hk * G + (n16 < G ? n16 : 0)) * (kD / 8);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int glo = kFp8 ? 2 * kg + h : 4 * h + kg;
+      sg.qf[h].u = q4[qrow + glo];
+      sg.qf[h + 2].u = q4[qrow + 8 + glo];
+    }
+  };
+  Seg seg;
+  auto first_seg = [&]() __attribute__((always_inline)) {
+    if (pos_begin >= pos_end) return;
+    int lo = 0;  // request that owns the first step: largest b with cum[b] <= pos_begin
+    if (in_lanes) {
+      lo = min((int)__popcll(__ballot(lane < a.B && cum_lane <= pos_begin)), a.B - 1);
+    } else {
+      int hi = n_items - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (uni(cum[mid]) <= pos_begin) lo = mid; else hi = mid - 1;
+      }
+    }
+    seg_load(seg, pos_begin, uni(lo));
+  };
+  if (in_lanes) {
+    cut();
+    first_seg();
+  }
   __syncthreads();
+  if (!in_lanes) {
+    cut();
+    if constexpr (!kBatched) first_seg();
+  }
   for (int idx = wave; idx < kNV * 16 + 8; idx += kWaves) {
     const bool is_k = idx < kNV * 16;
     const int h = (idx >> 2) & 1, w = idx & 3;  // idx = v*16 + (u*2 + h)*4 + w for rotK, kNV*16 + h*4 + w for rotS
@@ -291,26 +388,10 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
   }
   __syncthreads();
 
-  const int T = uni(cum[n_items]);
-  const int hk = (int)blockIdx.x % Hkv;
-  const int wk = ((int)blockIdx.x / Hkv) * kWaves + wave, n_k = ((int)gridDim.x / Hkv) * kWaves;
-  // blocks_per_split carries the minimum chunk
-  const int chunk = kBatched ? 0 : max((T + n_k - 1) / n_k, a.blocks_per_split);
-  if (!kBatched && blockIdx.x == 0 && wave == 0) {  // what the merge kernel needs to find each request's partials
-    for (int i = lane; i <= a.B; i += 64) a.part_meta[i] = cum[i];
-    if (lane == 0) a.part_meta[a.B + 1] = chunk;
-  }
-  int pos_begin = wk * chunk, pos_end = min(pos_begin + chunk, T);
-  if constexpr (kBatched) {  // the planner placed the cuts between the waves (the host checked n_k against the plan)
-    const int32_t* cuts = a.plan + plan_off_cuts(n_items, a.B, sload(a.plan, 7));
-    pos_begin = sload(cuts, wk);
-    pos_end = sload(cuts, wk + 1);
-  }
   if (pos_begin >= pos_end) return;
 
   const uint4* kpages = reinterpret_cast<const uint4*>(a.k_pages);
   const VRaw* vpages = reinterpret_cast<const VRaw*>(a.v_pages);
-  const uint4* q4 = reinterpret_cast<const uint4*>(a.q);
 
   floatx4 o[8];
   float m_run, l_part;
@@ -749,27 +830,30 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
   }
 
   // ---- walk the wave's chunk request by request ----
-  int pos = pos_begin, b = 0;
-  {  // request that owns the first step: largest b with cum[b] <= pos_begin
-    int lo = 0, hi = n_items - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (uni(cum[mid]) <= pos_begin) lo = mid; else hi = mid - 1;
+  // Ring of kNBuf register buffers: while a step is computed the K and V of the next kNBuf - 1 steps are in flight.
+  constexpr int kNBuf = n_buf(kFp8);
+  Frag kbuf[kNBuf][2][kNK];
+  VRaw vbuf[kNBuf][8];
+  float ks_of[kNBuf], vs_of[kNBuf];  // page scales (fp8), loaded with the step's K and V
+  auto issue_pages = [&](int rb, int p0, int p1) __attribute__((always_inline)) {
+    if constexpr (kFp8) {
+      ks_of[rb] = a.k_scales[p0];
+      vs_of[rb] = a.v_scales[p0];
+    } else {
+      ks_of[rb] = vs_of[rb] = 1.f;
     }
-    b = lo;
-  }
-  while (pos < pos_end) {
-    int c0 = uni(cum[b]), c1 = uni(cum[b + 1]);
-    while (c1 <= pos) {  // skip requests without steps
-      ++b;
-      c0 = c1;
-      c1 = uni(cum[b + 1]);
-    }
-    const int seg_end = min(pos_end, c1), n_st = seg_end - pos;
-    const int step_first = pos - c0;
-    const bool row_ok = n16 < G;  // matrix row n16 is query head n16 of the KV head's group
-    const int L = sload(a.kv_lens, b), jend = (L + kP - 1) / kP;
+    issue_k(kbuf[rb], p0, p1);
+    issue_v(vbuf[rb], p0, p1);
+  };
+  auto issue_first = [&]() __attribute__((always_inline)) {  // the run's first step
+    const int p0 = __builtin_amdgcn_readlane(seg.bt0, 0), p1 = kBps > 1 ? __builtin_amdgcn_readlane(seg.bt0, kBps - 1) : p0;
+    issue_pages(0, p0, p1);
+  };
+  issue_first();
+  for (;;) {
+    const int b = seg.b, c0 = seg.c0, n_st = seg.n_st, step_first = seg.step_first, L = seg.L, jend = (L + kP - 1) / kP;
     const int j0 = kBps * step_first;
+    const bool row_ok = n16 < G;  // matrix row n16 is query head n16 of the KV head's group
     const bool ragged_end = (step_first + n_st) * 32 > L;
     const size_t bt_row = (size_t)b * a.max_blocks;
     // Page ids of the run: lane i of bt_cur holds the page of block j0 + 64*bt_win + i (clamped to the
@@ -777,7 +861,7 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
     // purpose: scalar loads share a counter with the LDS reads, so every wait for a rotation constant would
     // also wait for them. The next window is fetched a whole window ahead.
     auto bt_load = [&](int win) { return safe_page(a.block_tables[bt_row + min(j0 + 64 * win + lane, jend - 1)], a.num_pages); };
-    int bt_win = 0, bt_cur = bt_load(0), bt_nxt = bt_load(1);
+    int bt_win = 0, bt_cur = seg.bt0, bt_nxt = seg.bt1;
     auto page = [&](int st, int k) {  // page k of step st; called with non-decreasing st
       const int rel = kBps * st + k;
       if ((rel >> 6) != bt_win) {
@@ -787,39 +871,10 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
       }
       return __builtin_amdgcn_readlane(bt_cur, rel & 63);
     };
-
-    // q of head n16: the lane's four 8-element chunks (rows >= G are zeroed through the scale):
-    // qf[h] = pairs 8h.. low dims, qf[h + 2] = the same pairs' high dims (+64)
-    Frag qf[4];
-    {
-      const size_t qrow = ((size_t)b * a.Hq + (size_t)hk * G + (row_ok ? n16 : 0)) * (kD / 8);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int glo = kFp8 ? 2 * kg + h : 4 * h + kg;
-        qf[h].u = q4[qrow + glo];
-        qf[h + 2].u = q4[qrow + 8 + glo];
-      }
-    }
-    // Ring of kNBuf register buffers: while a step is computed the K and V of the next kNBuf-1 steps are in
-    // flight.
-    constexpr int kNBuf = n_buf(kFp8);
-    Frag kbuf[kNBuf][2][kNK];
-    VRaw vbuf[kNBuf][8];
-    float ks_of[kNBuf], vs_of[kNBuf];  // page scales (fp8), loaded with the step's K and V
     auto issue_step = [&](int rb, int st) {
       const int p0 = page(st, 0), p1 = kBps > 1 ? page(st, kBps - 1) : p0;
-      if constexpr (kFp8) {
-        ks_of[rb] = a.k_scales[p0];
-        vs_of[rb] = a.v_scales[p0];
-      } else {
-        ks_of[rb] = vs_of[rb] = 1.f;
-      }
-      issue_k(kbuf[rb], p0, p1);
-      issue_v(vbuf[rb], p0, p1);
+      issue_pages(rb, p0, p1);
     };
-#pragma unroll
-    for (int r = 0; r < kNBuf - 1; ++r)
-      if (r < n_st) issue_step(r, r);
 
     // Q' = R(pos_q - n0) q, scaled into log2 units; reset the accumulators
 #pragma unroll
@@ -828,14 +883,14 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
     l_part = 0.f;
     v_ref = 0.f;
     {
-      const float delta = (float)(sload(a.q_positions, b) - step_first * 32);
+      const float delta = (float)(uni(seg.posq) - step_first * 32);
       const float qs = row_ok ? a.qk_scale_log2 : 0.f;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float2 f = freq_lds[kg * 16 + 8 * h + e];
-          const uint32_t wl = qf[h].w[e >> 1], wh = qf[h + 2].w[e >> 1];
+          const uint32_t wl = seg.qf[h].w[e >> 1], wh = seg.qf[h + 2].w[e >> 1];
           const float x0 = qs * ((e & 1) ? __uint_as_float(wl & 0xffff0000u) : bf16_bits_to_f32(wl & 0xffffu));
           const float x1 = qs * ((e & 1) ? __uint_as_float(wh & 0xffff0000u) : bf16_bits_to_f32(wh & 0xffffu));
           const float t = turns_frac(delta, f.x, f.y);
@@ -845,6 +900,9 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
         }
     }
 
+    const bool more = seg.seg_end < pos_end;
+    if (more) seg_load(seg, seg.seg_end, b);  // the next run: in flight while this one is computed
+
     for (int s0 = 0; s0 < n_st; s0 += kNBuf) {
 #pragma unroll
       for (int r = 0; r < kNBuf; ++r) {
@@ -852,11 +910,13 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
         if (st < n_st) {
           constexpr int kLead = kNBuf - 1;
           const int rn = (r + kLead) % kNBuf;  // buffer of step st + kLead (free: step st - 1 used it)
-          if (st + kLead < n_st) issue_step(rn, st + kLead);
+          if (kLead > 0 ? st + kLead < n_st : st > 0) issue_step(rn, st + kLead);  // (a run's first step is on its way already)
           compute(kbuf[r], vbuf[r], (j0 + kBps * st) * kP, st, L, ragged_end && st == n_st - 1, ks_of[r], vs_of[r]);
         }
       }
     }
+
+    if (more) issue_first();
 
     // the partial of this (request, wave): un-normalised rows, reference max (log2 units), sum
     {
@@ -877,7 +937,7 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
         }
       }
     }
-    pos = seg_end;
+    if (!more) break;
   }
 }
 
