@@ -21,6 +21,7 @@ namespace {
 // Source tokens per workgroup: 64 for the same-format copy, 32 for the quantising one (measured on 64 x 1024 tokens:
 // 98.5 -> 95.0 us and 82.3 <- 86.0 us respectively).
 constexpr int kThreads = 256;
+constexpr int kStagedRuns = 1024;  // runs whose prefix sums a workgroup keeps in LDS
 
 struct CommitArgs {
   const void* k_new;
@@ -130,6 +131,7 @@ __global__ __launch_bounds__(kThreads) void kv_commit_kernel(const CommitArgs a)
   __shared__ int s_slot[kTile];
   __shared__ float s_ksc[kTile], s_vsc[kTile];
   __shared__ int s_fast[kGroups];
+  __shared__ int s_cu[kStagedRuns];
   __shared__ __attribute__((aligned(16))) unsigned char s_v[kTile * kPitch];
 
   const int tid = threadIdx.x;
@@ -156,18 +158,27 @@ __global__ __launch_bounds__(kThreads) void kv_commit_kernel(const CommitArgs a)
     }
   }
 
+  // The prefix sums of up to kStagedRuns runs go to LDS in one load: a binary search over them in memory is a chain of
+  // 4 (16 runs) to 9 (272 runs) dependent loads in front of the four that resolve a destination. (44 K tokens in 272 runs,
+  // bf16 to e4m3: 31.8 -> 29.2 us.)
+  const bool staged = a.n_runs < kStagedRuns;
+  if (staged) {
+    for (int i = tid; i <= a.n_runs; i += kThreads) s_cu[i] = a.cu_run_tokens[i];
+    __syncthreads();
+  }
+  auto cu_at = [&](int i) { return staged ? s_cu[i] : a.cu_run_tokens[i]; };
   if (tid < kTile) {
     const int t = t0 + tid;
     int page = -1, slot = 0;
     float ks = 1.f, vs = 1.f;
-    if (t < a.n_tokens && t < a.cu_run_tokens[a.n_runs]) {
+    if (t < a.n_tokens && t < cu_at(a.n_runs)) {
       int lo = 0, hi = a.n_runs;                  // last run r with cu[r] <= t (it is not empty: cu[r+1] > t)
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (a.cu_run_tokens[mid] <= t) lo = mid; else hi = mid;
+        if (cu_at(mid) <= t) lo = mid; else hi = mid;
       }
       const int req = a.run_request[lo];
-      const long n = (long)a.run_first_slot[lo] + (t - a.cu_run_tokens[lo]);
+      const long n = (long)a.run_first_slot[lo] + (t - cu_at(lo));
       const long blk = n / P;
       if (req >= 0 && req < a.B && n >= 0 && blk < a.max_blocks) {
         const int p = a.block_tables[(long)req * a.max_blocks + blk];
