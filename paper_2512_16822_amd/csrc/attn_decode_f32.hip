@@ -16,8 +16,6 @@
 // against 64 bits is a tenth of the scalar kernel's (2.4e-7 and 2.4e-6 on the first): shorter chains of sums, phases.
 //
 // A NaN in the merged result sends the workgroup through the scalar body.
-#include <mutex>
-
 #include "attn_scalar.h"
 #include "split_common.h"
 
@@ -339,13 +337,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
 
 template <int D, int P, bool kIL>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
-  // the table may take all of the LDS a kernel gets by default: ask once per process (the attribute sticks)
-  static std::once_flag once;
-  static hipError_t status = hipSuccess;
-  std::call_once(once, [] {
-    status = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_f32_kernel<D, P, kIL>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes<D>());
-  });
+  static std::atomic<uint64_t> asked{0};
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_f32_kernel<D, P, kIL>), lds_bytes<D>(), asked);
   if (status != hipSuccess) return status;
   // KV heads fastest (neighbours go to different dies, which then each keep their own heads' pages); tokens over x and y
   const unsigned per_row = (unsigned)min(a.n_q, max(65536 / a.Hkv, 1));

@@ -19,7 +19,6 @@
 // one round of workgroups); where no page is shared, 64 requests of 4 - 6 K slots, 249 us = 5.4 TB/s: HBM.
 //
 // A NaN in the merged result (operand splits make NaN of some infinities) sends the workgroup through the scalar body.
-#include <mutex>
 #include <type_traits>
 
 #include "attn_scalar.h"
@@ -448,13 +447,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
 
 template <bool kFp8, int D, int P, bool kIL>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
-  // the table may take all of the LDS a kernel gets by default: ask once per process (the attribute sticks)
-  static std::once_flag once;
-  static hipError_t status = hipSuccess;
-  std::call_once(once, [] {
-    status = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)table_bytes(D));
-  });
+  static std::atomic<uint64_t> asked{0};
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL>), table_bytes(D), asked);
   if (status != hipSuccess) return status;
   // KV heads fastest (neighbours go to different dies, which then each keep their own heads' pages); tokens over x and y
   const unsigned per_row = (unsigned)min(a.n_q, max(65536 / a.Hkv, 1));

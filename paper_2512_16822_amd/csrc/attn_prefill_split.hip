@@ -24,8 +24,6 @@
 // Slots that do not take part for any row (pads, past kv_len) are zeroed in V when staged. A slot that only some rows
 // see (causal edge) may hold Inf or NaN, and infinities anywhere may turn into NaN between the terms of a split: the
 // tokens of rows that come out NaN are computed again by the scalar body at the end (attn_scalar.h).
-#include <mutex>
-
 #include "attn_scalar.h"
 #include "merge_partials.h"
 #include "split_common.h"
@@ -580,13 +578,8 @@ int prefill_split_workgroups_per_head(int Hkv) { return max(device_compute_units
 
 template <bool kFp8, int D, int P, bool kIL>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
-  // three tile buffers are more LDS than a kernel gets by default: ask once per process (the attribute sticks)
-  static std::once_flag once;
-  static hipError_t status = hipSuccess;
-  std::call_once(once, [] {
-    status = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_split_kernel<kFp8, D, P, kIL>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kNBuf * sizeof(Tile<D>)));
-  });
+  static std::atomic<uint64_t> asked{0};
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&prefill_split_kernel<kFp8, D, P, kIL>), kNBuf * sizeof(Tile<D>), asked);
   if (status != hipSuccess) return status;
   const unsigned grid = (unsigned)a.Hkv * (unsigned)prefill_split_workgroups_per_head(a.Hkv);
   hipLaunchKernelGGL((prefill_split_kernel<kFp8, D, P, kIL>), dim3(grid), dim3(kThreads), kNBuf * sizeof(Tile<D>), s, a);

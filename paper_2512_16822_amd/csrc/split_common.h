@@ -4,12 +4,27 @@
 // which together carry 16 significant bits (relative error 2^-18). A product of two such values is three matrix
 // products (hi hi + hi lo + lo hi; the dropped lo lo is of the size of the error), a product with an operand that bf16
 // holds exactly (stored bf16 values, e4m3 codes) two. Everything else - phases, rotation, softmax, sums - is fp32, as in
-// attn_general.hip, so results keep that kernel's accuracy (the output's own bf16 rounding, 2^-9, is what is left)
-// at matrix-core speed.
+// attn_scalar.h, so results keep that accuracy (the output's own bf16 rounding, 2^-8, is what is left) at matrix-core
+// speed.
 #pragma once
+#include <atomic>
+
 #include "attn_common.h"
 
 namespace mepic {
+
+// Ask for more dynamic LDS than a kernel gets by default: once per kernel and device (the attribute sticks to a device's
+// copy of the kernel). `asked` is the kernel's own, one bit for each device.
+inline hipError_t allow_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& asked) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+  if (asked.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) asked.fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
