@@ -1,5 +1,5 @@
-// Merge of split-K partials: one workgroup of 128 threads per (query token, query head). Partial s holds a reference maximum
-// (log2 units), a sum and an un-normalised row of D fp32 values; with m* the largest maximum,
+// Merge of split-K partials: one workgroup of kThreads (64 or 128) threads per (query token, query head). Partial s holds a
+// reference maximum (log2 units), a sum and an un-normalised row of D fp32 values; with m* the largest maximum,
 //   out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s          (all zeros when no slot took part).
 //
 // What a merge of tens of partials costs is memory latency, not bytes, so there is as little as possible in its chain of
@@ -45,9 +45,9 @@ constexpr int kMergeThreads = 128;
 
 // ml: [room][2], po: [room][D], out: the row; ns <= room partials exist (room is known before ns has been loaded, so the
 // first loads go by room).
-template <int D, typename Out>
+template <int D, int kThreads = kMergeThreads, typename Out>
 __device__ __forceinline__ void merge_row(const float* ml, const float* po, int room, int ns, Out* out) {
-  constexpr int kCols = D / 4, kGroups = kMergeThreads / kCols;
+  constexpr int kCols = D / 4, kGroups = kThreads / kCols;
   __shared__ float4 num_s[kGroups][kCols];
   const int lane = threadIdx.x & 63, part = threadIdx.x / kCols, dq = threadIdx.x % kCols;
   const float2* ml2 = reinterpret_cast<const float2*>(ml);

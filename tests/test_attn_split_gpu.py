@@ -91,6 +91,18 @@ def test_prefill_non_finite_values_reach_only_the_rows_that_see_them(mepic, orac
     within_output_rounding(got[~hit], want[~hit])
 
 
+def test_prefill_non_finite_in_more_places_than_are_listed(mepic, oracle_attn):
+    """Every request has an Inf, and a workgroup gets more row tiles than it can list for the scalar body: all are done again."""
+    st = question_prefill(29, [5] * 150, "bf16", D=64, Hq=64, Hkv=64, chunk=20)
+    case = W.assemble(st, align_with_oracle(st)[0])
+    case.pages.v[:, :, 3, 0] = float("inf")                   # slot 0 of every block, dim 3: visible to every row
+    case.pages.v[:, :, 3, 1:] = 0.0
+    got, want = DeviceCase(mepic, case, flags=mepic.FLAG_FORCE_GENERAL).run(), oracle_out(oracle_attn, case)
+    assert (got[:, :, 3] == np.inf).all() and (want[:, :, 3] == np.inf).all()
+    rest = np.arange(64) != 3
+    within_output_rounding(got[:, :, rest], want[:, :, rest])
+
+
 def test_prefill_smaller_workspace_and_refusal(mepic, oracle_attn):
     """The size query reports what the even cut of the work needs; less, down to what the scalar kernel's plan needed, still
     runs, and less than that is refused."""
