@@ -288,6 +288,24 @@ def test_decode_many_requests_skewed_lengths(mepic, oracle_attn, kv_dtype, P):
     assert torch.isfinite(out).all() and (out[[3, 40, 149]] == 0).all()
 
 
+@pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("f8e4m3", 32)])
+@pytest.mark.parametrize("B", [1, 63, 64, 65])
+def test_decode_request_counts_around_one_wave(mepic, oracle_attn, B, kv_dtype, P):
+    """Up to 64 requests their lengths and prefix sums stay in a wave's lanes, more go through LDS. Uneven lengths, the first and
+    the last request and some in between empty (of several requests), so that runs begin and end at any of them."""
+    st = W.Structure("lanes", "decode", B, 8, 2, 128, P, 5e5, "bf16", kv_dtype, B)
+    rng = np.random.default_rng(B)
+    for b in range(B):
+        st.requests.append([(0, int(rng.integers(1, 90)) + (2500 if b == B // 2 else 0), 0)])
+        st.n_q.append(1)
+    case = build_case(mepic, st)
+    empty = [0, 5, 6, B - 1] if B > 1 else []
+    case.kv_lens[empty] = 0
+    _, dc = check(mepic, oracle_attn, case)
+    assert mepic.last_kernel().startswith("decode_mfma")
+    assert (dc.out.float()[empty] == 0).all()
+
+
 def test_dispatch_names(mepic, oracle_attn):
     """Which kernel serves which case (the general kernel must stay reachable for everything else)."""
     for st, want in ((small_decode("bf16"), "decode_mfma_bf16"), (small_decode("f8e4m3", P=32), "decode_mfma_fp8"),

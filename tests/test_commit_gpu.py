@@ -127,6 +127,24 @@ def test_full_size_prompt_commit(mepic, kv_dtype, P):
     assert_same(*run_both(mepic, pages, bt, runs, k_new, v_new))
 
 
+@pytest.mark.parametrize("n_runs", [1, 255, 256, 1023, 1024, 1500])
+def test_run_counts_around_what_is_searched_in_lds(mepic, n_runs):
+    """Prefix sums of fewer than 1024 runs are staged (256 per pass of the workgroup), those of more are searched in memory; a
+    third of the runs are empty, tokens of a tile belong to many of them."""
+    Hkv, D, P, B, MB = 1, 128, 16, 3, 160
+    rng = np.random.default_rng(n_runs)
+    pages = W.gen_pages(27, B * MB, Hkv, P, D, "f8e4m3")
+    bt = rng.permutation(B * MB).reshape(B, MB).astype(np.int32)
+    free, runs = [0] * B, []
+    for i in range(n_runs):
+        r, c = int(rng.integers(B)), i % 3 if n_runs > 1 else 40
+        runs.append((r, free[r], c))
+        free[r] += c
+    assert max(free) <= MB * P
+    n = sum(c for _, _, c in runs)
+    assert_same(*run_both(mepic, pages, bt, runs, _src(rng, n, Hkv, D, "f8e4m3"), _src(rng, n, Hkv, D, "f8e4m3")))
+
+
 def test_commit_then_attend_equals_the_oracle_on_the_original_pages(mepic, oracle_attn):
     """Wipe the private tail of every request, put it back through mepic_kv_commit, run decode attention."""
     from harness import DeviceCase, align_with_oracle, oracle_out
