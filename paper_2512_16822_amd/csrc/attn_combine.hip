@@ -6,22 +6,30 @@ namespace mepic {
 namespace {
 
 // Merge the per-split partials of one (query token, query head).
-template <int D, typename Out>
-__global__ __launch_bounds__(kMergeThreads) void combine_kernel(const AttnArgs a) {
+template <int D, typename Out, int kThreads>
+__global__ __launch_bounds__(kThreads) void combine_kernel(const AttnArgs a) {
   const int row = blockIdx.x;
-  merge_row<D>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * D, a.n_splits, a.n_splits,
-               reinterpret_cast<Out*>(a.out) + (size_t)row * D);
+  merge_row<D, kThreads>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * D, a.n_splits,
+                         a.n_splits, reinterpret_cast<Out*>(a.out) + (size_t)row * D);
+}
+
+template <int D, typename Out>
+void launch_one(const AttnArgs& a, hipStream_t s) {
+  const int rows = a.n_q * a.Hq;
+  if (rows <= kMergeFewRows)
+    hipLaunchKernelGGL((combine_kernel<D, Out, kMergeThreadsFew>), dim3(rows), dim3(kMergeThreadsFew), 0, s, a);
+  else
+    hipLaunchKernelGGL((combine_kernel<D, Out, kMergeThreads>), dim3(rows), dim3(kMergeThreads), 0, s, a);
 }
 
 }  // namespace
 
 hipError_t launch_combine(const AttnArgs& a, hipStream_t s) {
-  const dim3 grid(a.n_q * a.Hq), block(kMergeThreads);
   const bool f32 = a.q_dtype == MEPIC_F32;
-  if (a.D == 128 && f32) hipLaunchKernelGGL((combine_kernel<128, float>), grid, block, 0, s, a);
-  else if (a.D == 128) hipLaunchKernelGGL((combine_kernel<128, uint16_t>), grid, block, 0, s, a);
-  else if (f32) hipLaunchKernelGGL((combine_kernel<64, float>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((combine_kernel<64, uint16_t>), grid, block, 0, s, a);
+  if (a.D == 128 && f32) launch_one<128, float>(a, s);
+  else if (a.D == 128) launch_one<128, uint16_t>(a, s);
+  else if (f32) launch_one<64, float>(a, s);
+  else launch_one<64, uint16_t>(a, s);
   return hipGetLastError();
 }
 

@@ -943,23 +943,25 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
 
 // Merge the partials of one (request, query head). Request b owns steps [cum[b], cum[b+1]) of its KV
 // head's sequence; the waves that cut that range wrote partials 0 .. (cum[b+1]-1)/chunk - cum[b]/chunk.
-__global__ __launch_bounds__(kMergeThreads) void combine_streamk_kernel(const AttnArgs a) {
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void combine_streamk_kernel(const AttnArgs a) {
   const int row = blockIdx.x;
   const int b = row / a.Hq;
   const int c0 = a.part_meta[b], c1 = a.part_meta[b + 1], chunk = a.part_meta[a.B + 1];
   const int ns = c1 > c0 ? (c1 - 1) / chunk - c0 / chunk + 1 : 0;
-  merge_row<kD>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, a.n_splits, ns,
-                reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
+  merge_row<kD, kThreads>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, a.n_splits, ns,
+                          reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
 }
 
 // Merge for the batched variant: request b has n_part[b] partials per head, in slots 0 .. n_part[b]-1.
-__global__ __launch_bounds__(kMergeThreads) void combine_batched_kernel(const AttnArgs a) {
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void combine_batched_kernel(const AttnArgs a) {
   const int row = blockIdx.x;
   const int b = row / a.Hq;
   const int n_runs = a.plan[1];
   const int ns = a.plan[plan_off_npart(n_runs) + b];
-  merge_row<kD>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, a.n_splits, ns,
-                reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
+  merge_row<kD, kThreads>(a.part_ml + (size_t)row * a.n_splits * 2, a.part_o + (size_t)row * a.n_splits * kD, a.n_splits, ns,
+                          reinterpret_cast<uint16_t*>(a.out) + (size_t)row * kD);
 }
 
 // Self-test of dot_rotate_block: words[i] = {e0..e3, ca0, cb0, ca1, cb1, ca2, cb2, ca3, cb3}; out[i] = {l0..l3, h0..h3}.
@@ -1004,7 +1006,11 @@ hipError_t launch_decode_mfma(const AttnArgs& a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (a.timing_stop) (void)hipEventRecord(reinterpret_cast<hipEvent_t>(a.timing_stop), s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(combine_streamk_kernel, dim3(a.n_q * a.Hq), dim3(kMergeThreads), 0, s, a);
+  const int rows = a.n_q * a.Hq;
+  if (rows <= kMergeFewRows)
+    hipLaunchKernelGGL((combine_streamk_kernel<kMergeThreadsFew>), dim3(rows), dim3(kMergeThreadsFew), 0, s, a);
+  else
+    hipLaunchKernelGGL((combine_streamk_kernel<kMergeThreads>), dim3(rows), dim3(kMergeThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1030,7 +1036,11 @@ hipError_t launch_decode_mfma_batched(const AttnArgs& a, int n_runs, hipStream_t
   hipError_t e = hipGetLastError();
   if (a.timing_stop) (void)hipEventRecord(reinterpret_cast<hipEvent_t>(a.timing_stop), s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(combine_batched_kernel, dim3(a.n_q * a.Hq), dim3(kMergeThreads), 0, s, a);
+  const int rows = a.n_q * a.Hq;
+  if (rows <= kMergeFewRows)
+    hipLaunchKernelGGL((combine_batched_kernel<kMergeThreadsFew>), dim3(rows), dim3(kMergeThreadsFew), 0, s, a);
+  else
+    hipLaunchKernelGGL((combine_batched_kernel<kMergeThreads>), dim3(rows), dim3(kMergeThreads), 0, s, a);
   return hipGetLastError();
 }
 

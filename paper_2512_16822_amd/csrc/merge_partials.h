@@ -1,4 +1,4 @@
-// Merge of split-K partials: one workgroup of kThreads (64 or 128) threads per (query token, query head). Partial s holds a
+// Merge of split-K partials: one workgroup of kThreads (64 to 256) threads per (query token, query head). Partial s holds a
 // reference maximum (log2 units), a sum and an un-normalised row of D fp32 values; with m* the largest maximum,
 //   out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s          (all zeros when no slot took part).
 //
@@ -41,11 +41,14 @@ __device__ __forceinline__ float wave_reduce(float x, Op op) {
   return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-constexpr int kMergeThreads = 128;
+// Threads per row. Up to two rows per compute unit leave it nearly idle: 256 threads, so that a thread has half as many loads in
+// its chain (128 rows of 54 partials 4.9 -> 4.0 us, 256 rows of up to 256 5.8 -> 5.0, 512 rows even; 512 threads: no better). With
+// more rows there are enough loads in flight, and the extra waves cost: 2048 batched rows 5.0 -> 5.6 us, 3584 rows 5.0 -> 6.8.
+constexpr int kMergeThreads = 128, kMergeThreadsFew = 256, kMergeFewRows = 512;
 
 // ml: [room][2], po: [room][D], out: the row; ns <= room partials exist (room is known before ns has been loaded, so the
 // first loads go by room).
-template <int D, int kThreads = kMergeThreads, typename Out>
+template <int D, int kThreads, typename Out>
 __device__ __forceinline__ void merge_row(const float* ml, const float* po, int room, int ns, Out* out) {
   constexpr int kCols = D / 4, kGroups = kThreads / kCols;
   __shared__ float4 num_s[kGroups][kCols];
