@@ -1,6 +1,8 @@
 // Merge of split-K partials: one workgroup of kThreads (64 to 256) threads per (query token, query head). Partial s holds a
 // reference maximum (log2 units), a sum and an un-normalised row of D fp32 values; with m* the largest maximum,
 //   out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s          (all zeros when no slot took part).
+// A partial no slot took part in has maximum -inf; its row may hold anything and is left out. Every other one counts, however
+// small its weight, so that a NaN or Inf of its row is in the result wherever the context was cut.
 //
 // What a merge of tens of partials costs is memory latency, not bytes, so there is as little as possible in its chain of
 // dependent loads: lane i of every wave takes the maximum and the sum of partial i (64 at a time, one coalesced load; the
@@ -59,7 +61,7 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
   float den = 0.f, m = -INFINITY;
   auto row = [&](int s) { return s < ns ? po4[(size_t)s * kCols] : make_float4(0.f, 0.f, 0.f, 0.f); };
   auto add = [&](const float4& x, float w) {
-    if (w != 0.f) {  // a partial nothing took part in, or that does not exist, may hold anything
+    if (!(w < 0.f)) {  // (a weight may be NaN)
       num.x += w * x.x; num.y += w * x.y; num.z += w * x.z; num.w += w * x.w;
     }
   };
@@ -81,8 +83,9 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
       den *= f;
     }
     m = m_new;
-    const float w = e.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(e.x - m);
-    den += wave_reduce(w == 0.f ? 0.f : w * e.y, [](float x, float y) { return x + y; });
+    const bool took = e.x != -INFINITY;
+    const float w = took ? __builtin_amdgcn_exp2f(e.x - m) : -1.f;
+    den += wave_reduce(took ? w * e.y : 0.f, [](float x, float y) { return x + y; });
     // (every lane runs as many turns as the first group: the shuffles need all of them)
     for (int i = s0; i < s_end; i += 2 * kGroups, s += 2 * kGroups) {
       const float4 x = a, y = b;

@@ -1,0 +1,58 @@
+"""NaN and Inf on every attention path: what a row reads is in the row, wherever the context is cut, and what it does not read
+is not."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from harness import DeviceCase, align_with_oracle
+
+pytestmark = pytest.mark.gpu
+TOL = {"f32": 1e-4, "bf16": 2e-2, "f8e4m3": 2e-2}
+
+# kv_dtype, P, general path, prefill, planned
+PATHS = [("bf16", 16, False, False, False), ("f8e4m3", 32, False, False, False), ("bf16", 16, False, False, True),
+         ("f8e4m3", 32, False, False, True), ("bf16", 16, True, False, False), ("f32", 16, True, False, False),
+         ("bf16", 16, True, True, False), ("f32", 16, True, True, False)]
+
+
+def structure(kv_dtype, P, prefill, lengths):
+    st = W.Structure("nonfinite", "prefill" if prefill else "decode", len(lengths), 8, 2, 128, P, 5e5,
+                     "f32" if kv_dtype == "f32" else "bf16", kv_dtype, 81)
+    st.requests, st.extra_tail = [[(0, n, 0)] for n in lengths], 0
+    st.n_q = [min(n, 40) if prefill else 1 for n in lengths]
+    return st
+
+
+def run(M, case, general, planned):
+    dc = DeviceCase(M, case, flags=M.FLAG_FORCE_GENERAL if general else 0)
+    return dc.run_batched() if planned else dc.run()
+
+
+@pytest.mark.parametrize("value", ["nan", "inf"])
+@pytest.mark.parametrize("kv_dtype,P,general,prefill,planned", PATHS)
+def test_a_non_finite_value_under_a_vanishing_weight(mepic, oracle_attn, kv_dtype, P, general, prefill, planned, value):
+    """Scores some 400 log2 units higher at the end of the context than before: V at its beginning has no weight in fp32, but
+    0 x Inf is not 0, whether the two meet inside one partial or when partials are merged."""
+    case = W.assemble(s := structure(kv_dtype, P, prefill, [6000, 100]), align_with_oracle(s)[0])
+    k, n = W.unpack_k(case.pages.k.float()), 5900          # a key along the pair of dims that hardly turns, and q with it
+    high = 40.0 if kv_dtype == "f8e4m3" else 60.0
+    if kv_dtype == "f8e4m3":
+        k = k * case.pages.k_scales[:, None, None, None]
+    k[int(case.block_tables[0, n // P]), :, n % P, 63] = high
+    stored, scales = W.store_round(k.nan_to_num(0.0), kv_dtype)
+    case.pages.k, case.pages.k_scales = W.pack_k(stored, kv_dtype), scales
+    case.q[:, :, 63] = 60.0 if kv_dtype != "f8e4m3" else 120.0
+    clean = run(mepic, case, general, planned)
+    assert np.isfinite(clean).all()
+    hit = np.zeros(clean.shape, dtype=bool)
+    for n, dim in ((3, 100), (4803, 101)):                 # before the high score's run of partials, and near it
+        page = int(case.block_tables[0, n // P])
+        if kv_dtype == "f8e4m3":
+            case.pages.v.view(torch.uint8)[page, 1, dim, n % P] = 0x7F
+        else:
+            case.pages.v[page, 1, dim, n % P] = float(value)
+        hit[:int(case.cu_q_lens[1]) if prefill else 1, 4:8, dim] = True
+    got = run(mepic, case, general, planned)
+    assert not np.isfinite(got[hit]).any()
+    assert np.array_equal(got[~hit], clean[~hit]) or np.abs(got[~hit] - clean[~hit]).max() <= TOL[kv_dtype]
