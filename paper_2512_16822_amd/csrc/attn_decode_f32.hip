@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
     is_nan |= all != all;
     const size_t row = (size_t)t * a.Hq + (size_t)hk * G + g;
     if (direct) {
-      const bool some = l > 0.f;
+      const bool some = l != 0.f;
       reinterpret_cast<float4*>(a.out)[row * (D / 4) + dq] =
           make_float4(some ? x.x / l : 0.f, some ? x.y / l : 0.f, some ? x.z / l : 0.f, some ? x.w / l : 0.f);
     } else {

@@ -60,8 +60,6 @@ namespace mepic {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kD = 128;
@@ -109,12 +107,6 @@ union Frag {  // one 16-byte operand fragment
 __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
   const f32x2 v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
-}
-
-// Two fp32 -> packed bf16 pair, round to nearest even (one v_cvt_pk_bf16_f32 on gfx950).
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  const f32x2 v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -380,8 +372,8 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
       rotK[idx][lane] = make_float2(__uint_as_float(pack_f16x2(r.x, r.z)), __uint_as_float(pack_f16x2(r.y, r.w)));
     } else if constexpr (kDotRot) {
       // per pair the two constant words (cos, -sin) and (sin, cos) as packed bf16
-      rotK[idx][lane] = make_float4(__uint_as_float(pack_bf16x2(r.x, -r.y)), __uint_as_float(pack_bf16x2(r.y, r.x)),
-                                    __uint_as_float(pack_bf16x2(r.z, -r.w)), __uint_as_float(pack_bf16x2(r.w, r.z)));
+      rotK[idx][lane] = make_float4(__uint_as_float(pack2_bf16(r.x, -r.y)), __uint_as_float(pack2_bf16(r.y, r.x)),
+                                    __uint_as_float(pack2_bf16(r.z, -r.w)), __uint_as_float(pack2_bf16(r.w, r.z)));
     } else {
       rotK[idx][lane] = r;
     }
@@ -442,8 +434,8 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
-        bq[h].w[e / 2] = kFp8 ? pack_f16x2(qlo[h][e], qlo[h][e + 1]) : pack_bf16x2(qlo[h][e], qlo[h][e + 1]);
-        bq[h + 2].w[e / 2] = kFp8 ? pack_f16x2(qhi[h][e], qhi[h][e + 1]) : pack_bf16x2(qhi[h][e], qhi[h][e + 1]);
+        bq[h].w[e / 2] = kFp8 ? pack_f16x2(qlo[h][e], qlo[h][e + 1]) : pack2_bf16(qlo[h][e], qlo[h][e + 1]);
+        bq[h + 2].w[e / 2] = kFp8 ? pack_f16x2(qhi[h][e], qhi[h][e + 1]) : pack2_bf16(qhi[h][e], qhi[h][e + 1]);
       }
     // Rotate the K rows by their constant slot rotation and run the two QK products, then advance Q' by
     // R(-32). Six groups of four constants each; the constants of the next group are fetched from LDS while a
@@ -493,10 +485,10 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
             dot_rotate_block(e0, e1, e2, e3, __float_as_uint(r[w].x), __float_as_uint(r[w].y), __float_as_uint(r[w].z),
                              __float_as_uint(r[w].w), __float_as_uint(r[w + 1].x), __float_as_uint(r[w + 1].y),
                              __float_as_uint(r[w + 1].z), __float_as_uint(r[w + 1].w), l0, l1, l2, l3, h0, h1, h2, h3);
-            klo.w[w] = pack_bf16x2(l0, l1);
-            klo.w[w + 1] = pack_bf16x2(l2, l3);
-            khi.w[w] = pack_bf16x2(h0, h1);
-            khi.w[w + 1] = pack_bf16x2(h2, h3);
+            klo.w[w] = pack2_bf16(l0, l1);
+            klo.w[w + 1] = pack2_bf16(l2, l3);
+            khi.w[w] = pack2_bf16(h0, h1);
+            khi.w[w + 1] = pack2_bf16(h2, h3);
           }
           sc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(klo.v, bq[h].v, sc[u], 0, 0, 0);
           sc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(khi.v, bq[h + 2].v, sc[u], 0, 0, 0);
@@ -506,8 +498,8 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
             const uint32_t lo2 = kf[u][h].w[w], hi2 = kf[u][h + 2].w[w];
             const float l0 = bf16_bits_to_f32(lo2 & 0xffffu), l1 = __uint_as_float(lo2 & 0xffff0000u);
             const float h0 = bf16_bits_to_f32(hi2 & 0xffffu), h1 = __uint_as_float(hi2 & 0xffff0000u);
-            klo.w[w] = pack_bf16x2(l0 * r[w].x - h0 * r[w].y, l1 * r[w].z - h1 * r[w].w);  // r = {c0, s0, c1, s1}
-            khi.w[w] = pack_bf16x2(h0 * r[w].x + l0 * r[w].y, h1 * r[w].z + l1 * r[w].w);
+            klo.w[w] = pack2_bf16(l0 * r[w].x - h0 * r[w].y, l1 * r[w].z - h1 * r[w].w);  // r = {c0, s0, c1, s1}
+            khi.w[w] = pack2_bf16(h0 * r[w].x + l0 * r[w].y, h1 * r[w].z + l1 * r[w].w);
           }
           sc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(klo.v, bq[h].v, sc[u], 0, 0, 0);
           sc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(khi.v, bq[h + 2].v, sc[u], 0, 0, 0);
@@ -635,7 +627,7 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
     } else {
       Frag pa;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) pa.w[w] = pack_bf16x2(pf[2 * w], pf[2 * w + 1]);
+      for (int w = 0; w < 4; ++w) pa.w[w] = pack2_bf16(pf[2 * w], pf[2 * w + 1]);
 #pragma unroll
       for (int nt = 0; nt < 8; ++nt) {
         Frag vb;

@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     is_nan |= all != all;
     const size_t row = (size_t)t * a.Hq + (size_t)hk * G + g;
     if (direct) {
-      const float inv = l > 0.f ? 1.f / l : 0.f;
+      const float inv = l != 0.f ? 1.f / l : 0.f;
       uint2 w;
       w.x = pack2_bf16(x.x * inv, x.y * inv);
       w.y = pack2_bf16(x.z * inv, x.w * inv);

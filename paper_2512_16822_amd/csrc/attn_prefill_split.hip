@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
     if (row_ok) {
       if (half == 0 && split == 0) a.part_meta[out_row] = n_parts;  // for the merge
       if (n_parts == 1) {
-        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        const float inv = l_tot != 0.f ? 1.f / l_tot : 0.f;
         uint2* dst = reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + out_row * D);
 #pragma unroll
         for (int db = 0; db < kDb; ++db)

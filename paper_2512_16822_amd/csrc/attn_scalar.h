@@ -172,7 +172,7 @@ __device__ __forceinline__ void scalar_attend(const AttnArgs& a, ScalarLds<GM, k
       const float m_new = fmaxf(m_run[g], tm);
       alpha[g] = m_new == -INFINITY ? 1.f : exp2f(m_run[g] - m_new);
       m_run[g] = m_new;
-      const float p = take ? exp2f(s[g] - m_new) : 0.f;
+      const float p = take ? exp2f(s[g] - (m_new == -INFINITY ? 0.f : m_new)) : 0.f;
       lds.sc[g * kThreads + tid] = p;
       s[g] = p;
     }
@@ -228,9 +228,9 @@ __device__ __forceinline__ void scalar_attend(const AttnArgs& a, ScalarLds<GM, k
       for (int pp = 0; pp < parts; ++pp) o += lds.sc[g * kThreads + pp * D + d_own];
       const size_t row = (size_t)t * a.Hq + (size_t)hk * a.G + g0 + g;
       if (direct) {
-        const float r = l_run[g] > 0.f ? o / l_run[g] : 0.f;  // as combine_kernel
+        const float r = l_run[g] != 0.f ? o / l_run[g] : 0.f;  // as merge_row
         if (a.q_dtype == MEPIC_F32) reinterpret_cast<float*>(a.out)[row * D + d_own] = r;
-        else reinterpret_cast<uint16_t*>(a.out)[row * D + d_own] = (uint16_t)f32_to_bf16_bits(r);
+        else reinterpret_cast<uint16_t*>(a.out)[row * D + d_own] = (uint16_t)pack2_bf16(r, r);
       } else {
         const size_t pr = row * a.n_splits + split;
         a.part_o[pr * D + d_own] = o;

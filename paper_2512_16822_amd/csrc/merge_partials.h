@@ -1,8 +1,8 @@
 // Merge of split-K partials: one workgroup of kThreads (64 to 256) threads per (query token, query head). Partial s holds a
 // reference maximum (log2 units), a sum and an un-normalised row of D fp32 values; with m* the largest maximum,
 //   out = sum_s 2^(m_s - m*) o_s / sum_s 2^(m_s - m*) l_s          (all zeros when no slot took part).
-// A partial no slot took part in has maximum -inf; its row may hold anything and is left out. Every other one counts, however
-// small its weight, so that a NaN or Inf of its row is in the result wherever the context was cut.
+// A partial no slot took part in has maximum -inf and sum 0; its row may hold anything and is left out. Every other one counts,
+// however small its weight, so that a NaN or Inf of its row or its sum is in the result wherever the context was cut.
 //
 // What a merge of tens of partials costs is memory latency, not bytes, so there is as little as possible in its chain of
 // dependent loads: lane i of every wave takes the maximum and the sum of partial i (64 at a time, one coalesced load; the
@@ -19,8 +19,8 @@ template <typename Out> __device__ __forceinline__ void store4(Out* dst, const f
 template <> __device__ __forceinline__ void store4<float>(float* dst, const float4& v) { *reinterpret_cast<float4*>(dst) = v; }
 template <> __device__ __forceinline__ void store4<uint16_t>(uint16_t* dst, const float4& v) {
   uint2 p;
-  p.x = f32_to_bf16_bits(v.x) | (f32_to_bf16_bits(v.y) << 16);
-  p.y = f32_to_bf16_bits(v.z) | (f32_to_bf16_bits(v.w) << 16);
+  p.x = pack2_bf16(v.x, v.y);
+  p.y = pack2_bf16(v.z, v.w);
   *reinterpret_cast<uint2*>(dst) = p;
 }
 
@@ -75,6 +75,7 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
     }
     b = row(s + kGroups);
     if (s0 + lane >= ns) e = make_float2(-INFINITY, 0.f);
+    const bool took = e.x != -INFINITY || e.y != 0.f;
     const int s_end = min(ns, s0 + 64);
     const float m_new = fmaxf(m, wave_reduce(e.x, [](float x, float y) { return fmaxf(x, y); }));
     if (m_new != m && m != -INFINITY) {
@@ -83,8 +84,7 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
       den *= f;
     }
     m = m_new;
-    const bool took = e.x != -INFINITY;
-    const float w = took ? __builtin_amdgcn_exp2f(e.x - m) : -1.f;
+    const float w = took ? __builtin_amdgcn_exp2f(e.x - m) : -1.f;  // (NaN where all scores of the row are)
     den += wave_reduce(took ? w * e.y : 0.f, [](float x, float y) { return x + y; });
     // (every lane runs as many turns as the first group: the shuffles need all of them)
     for (int i = s0; i < s_end; i += 2 * kGroups, s += 2 * kGroups) {
@@ -103,9 +103,9 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
       const float4 x = num_s[p][dq];
       num.x += x.x; num.y += x.y; num.z += x.z; num.w += x.w;
     }
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    store4<Out>(out + 4 * dq, den > 0.f ? make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv)
-                                        : make_float4(0.f, 0.f, 0.f, 0.f));
+    const float inv = 1.f / den;
+    store4<Out>(out + 4 * dq, den != 0.f ? make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv)
+                                         : make_float4(0.f, 0.f, 0.f, 0.f));
   }
 }
 

@@ -27,19 +27,12 @@ inline hipError_t allow_lds(const void* kernel, size_t bytes, std::atomic<uint64
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 union SplitFrag {  // one 16-byte operand fragment
   uint4 u;
   bf16x8 v;
   uint32_t w[4];
 };
-
-__device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {  // round to nearest even (v_cvt_pk_bf16_f32)
-  const f32x2 v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
 
 // Two fp32 values -> their packed bf16 heads and packed bf16 remainders. (x - head as a two-term dot product of the packed
 // word with (-1, 0) saves two of the six instructions and measured no faster here and 5 % slower in the prefill kernel.)

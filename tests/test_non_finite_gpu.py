@@ -1,11 +1,11 @@
-"""NaN and Inf on every attention path: what a row reads is in the row, wherever the context is cut, and what it does not read
-is not."""
+"""NaN, Inf and very large values on every attention path: a row is zeros only where no slot takes part; a NaN or Inf that a row
+reads is in the row, wherever the context is cut; and what a row does not read is not."""
 import numpy as np
 import pytest
 import torch
 
 import workloads as W
-from harness import DeviceCase, align_with_oracle
+from harness import DeviceCase, align_with_oracle, oracle_out
 
 pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-4, "bf16": 2e-2, "f8e4m3": 2e-2}
@@ -27,6 +27,27 @@ def structure(kv_dtype, P, prefill, lengths):
 def run(M, case, general, planned):
     dc = DeviceCase(M, case, flags=M.FLAG_FORCE_GENERAL if general else 0)
     return dc.run_batched() if planned else dc.run()
+
+
+def set_k(pages, page, slot, dim, value):
+    X = pages.k.shape[-1]
+    if pages.kv_dtype == "f8e4m3":
+        assert value != value
+        pages.k.view(torch.uint8)[page, :, dim // X, slot, dim % X] = 0x7F
+    else:
+        pages.k[page, :, dim // X, slot, dim % X] = value
+
+
+@pytest.mark.parametrize("kv_dtype,P,general,prefill,planned", PATHS)
+def test_a_nan_key_reaches_the_rows_that_see_it(mepic, oracle_attn, kv_dtype, P, general, prefill, planned):
+    """One element of one key in a long context (many partials), in a short one (written directly), and the only key there is."""
+    case = W.assemble(s := structure(kv_dtype, P, prefill, [6000, 200, 1, 700]), align_with_oracle(s)[0])
+    for b, n in ((0, 5995), (1, 170), (2, 0)):  # (in prefill some of the query tokens come before it)
+        set_k(case.pages, int(case.block_tables[b, n // P]), n % P, 17, float("nan"))
+    got, want = run(mepic, case, general, planned), oracle_out(oracle_attn, case)
+    hit = np.isnan(want)
+    assert hit[-1].any() == False and hit.any() and (np.isnan(got) == hit).all()
+    assert np.abs(got[~hit] - want[~hit]).max() <= TOL[kv_dtype]
 
 
 @pytest.mark.parametrize("value", ["nan", "inf"])
