@@ -15,7 +15,8 @@
 // 1 K slots, 32 heads on 8, 128 dims: 57 -> 15 us; 16 of 2.5 - 10 K private slots 405 -> 153 us (5.9 TB/s). The error
 // against 64 bits is a tenth of the scalar kernel's (2.4e-7 and 2.4e-6 on the first): shorter chains of sums, phases.
 //
-// A NaN in the merged result sends the workgroup through the scalar body.
+// A NaN or Inf in the merged result sends the workgroup through the scalar body (values near the largest float, times
+// probabilities of up to 2^kRescaleSlack, make Inf of what plain arithmetic keeps finite).
 #include "attn_scalar.h"
 #include "split_common.h"
 
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
   }
   __syncthreads();
   const bool direct = a.n_splits == 1;
-  bool is_nan = false;
+  bool odd = false;
   for (int i = tid; i < G * (D / 4); i += kThreads) {
     const int g = i / (D / 4), dq = i % (D / 4);
     float m = mg.m[0][g];
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
       l += f * mg.l[w][g];
     }
     const float all = (x.x + x.y) + (x.z + x.w) + l;
-    is_nan |= all != all;
+    odd |= !(fabsf(all) < INFINITY);
     const size_t row = (size_t)t * a.Hq + (size_t)hk * G + g;
     if (direct) {
       const bool some = l != 0.f;
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
       }
     }
   }
-  if (__syncthreads_or(is_nan ? 1 : 0))
+  if (__syncthreads_or(odd ? 1 : 0))
     scalar_attend_all<MEPIC_F32, kThreads>(a, *reinterpret_cast<ScalarLds<4, kThreads>*>(smem), t, b, hk, 0, G, n_begin, s_end,
                                            split, direct);
 }

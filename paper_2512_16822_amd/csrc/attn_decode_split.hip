@@ -18,7 +18,8 @@
 // (146 before the loads got scalar bases and a fixed order, so that a step's waits leave the next step's loads in flight, and
 // one round of workgroups); where no page is shared, 64 requests of 4 - 6 K slots, 249 us = 5.4 TB/s: HBM.
 //
-// A NaN in the merged result (operand splits make NaN of some infinities) sends the workgroup through the scalar body.
+// A NaN or Inf in the merged result sends the workgroup through the scalar body: operand splits make NaN of some infinities, and
+// probabilities of up to 2^kRescaleSlack times values near the largest float make Inf of finite ones.
 #include <type_traits>
 
 #include "attn_scalar.h"
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   }
   __syncthreads();
   const bool direct = a.n_splits == 1;
-  bool is_nan = false;
+  bool odd = false;
   for (int i = tid; i < G * (D / 4); i += kThreads) {
     const int g = i / (D / 4), dq = i % (D / 4);
     float m = mg.m[0][g];
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       l += f * mg.l[w][g];
     }
     const float all = (x.x + x.y) + (x.z + x.w) + l;
-    is_nan |= all != all;
+    odd |= !(fabsf(all) < INFINITY);
     const size_t row = (size_t)t * a.Hq + (size_t)hk * G + g;
     if (direct) {
       const float inv = l != 0.f ? 1.f / l : 0.f;
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       }
     }
   }
-  if (__syncthreads_or(is_nan ? 1 : 0))
+  if (__syncthreads_or(odd ? 1 : 0))
     scalar_attend_all<kFp8 ? MEPIC_F8E4M3 : MEPIC_BF16, kThreads>(a, *reinterpret_cast<ScalarLds<4, kThreads>*>(smem), t, b, hk, 0, G,
                                                                   n_begin, s_end, split, direct);
 }

@@ -22,8 +22,9 @@
 // 17 K bf16 slots in pages of 32, 256 tokens: 480 TFLOP/s of attention, 1.2 PFLOP/s of products.
 //
 // Slots that do not take part for any row (pads, past kv_len) are zeroed in V when staged. A slot that only some rows
-// see (causal edge) may hold Inf or NaN, and infinities anywhere may turn into NaN between the terms of a split: the
-// tokens of rows that come out NaN are computed again by the scalar body at the end (attn_scalar.h).
+// see (causal edge) may hold Inf or NaN, infinities anywhere may turn into NaN between the terms of a split, and probabilities of up
+// to kBig times values of 2^88 and more make Inf of finite ones: the tokens of rows that come out NaN or Inf are computed again
+// by the scalar body at the end (attn_scalar.h).
 #include "attn_scalar.h"
 #include "merge_partials.h"
 #include "split_common.h"
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
   constexpr int kNv = D / 64;     // V units (8 slots of one dim) a thread stages per tile
   extern __shared__ uint4 lds_all[];
   Tile<D>* const tiles = reinterpret_cast<Tile<D>*>(lds_all);
-  // Runs of rows whose result holds NaN, for the scalar body at the end: where in the sequence, and which rows. (With more
+  // Runs of rows whose result holds NaN or Inf, for the scalar body at the end: where in the sequence, and which rows. (With more
   // of them than there is room for, everything the workgroup did is done again.)
   __shared__ int n_redo, redo_at[kMaxRedo];
   __shared__ uint32_t redo_rows[kMaxRedo][kRows / 32];
@@ -500,12 +501,12 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
     const uint32_t u = __float_as_uint(l_part);
     const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     const float l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    float total = l_tot;  // NaN iff the sum or some accumulator is (infinities of both signs count: computed again for nothing)
+    float total = l_tot;  // NaN or Inf if the sum or some accumulator is (or if their sum overflows: computed again for nothing)
 #pragma unroll
     for (int db = 0; db < kDb; ++db)
 #pragma unroll
       for (int e = 0; e < 16; ++e) total += o[db][e];
-    const bool is_nan = row_ok && total != total;
+    const bool odd = row_ok && !(fabsf(total) < INFINITY);
     if (row_ok) {
       if (half == 0 && split == 0) a.part_meta[out_row] = n_parts;  // for the merge
       if (n_parts == 1) {
@@ -536,8 +537,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
       }
     }
 
-    if (__syncthreads_or(is_nan ? 1 : 0)) {
-      const unsigned long long rows = __ballot(is_nan);  // both halves of the wave report their share of a row
+    if (__syncthreads_or(odd ? 1 : 0)) {
+      const unsigned long long rows = __ballot(odd);  // both halves of the wave report their share of a row
       if (n_redo < kMaxRedo && lane == 0) redo_rows[n_redo][wave] = (uint32_t)(rows | (rows >> 32));
       __syncthreads();
       if (tid == 0) {
@@ -548,7 +549,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
     }
   }
 
-  // ---- tokens with a NaN row once more, scalar (those of a token's heads that the row tile holds) ----
+  // ---- tokens with such a row once more, scalar (those of a token's heads that the row tile holds) ----
   __syncthreads();
   const int n_list = n_redo;
   if (n_list == 0) return;

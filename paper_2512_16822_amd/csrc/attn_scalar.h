@@ -1,7 +1,8 @@
 // The scalar body of the general path of fused-RoPE paged attention (§3.3.3): a workgroup serves up to GM query heads of one
 // (query token, KV head, range of slots) with plain fp32 arithmetic. The path's matrix-core kernels fall back to it for a
-// token whose result came out NaN: operands split into two bf16 terms turn some infinities (0 x Inf, Inf - Inf between the
-// terms) into NaN where plain arithmetic has none, and matrix products bring slots together that a row must not see.
+// token whose result came out NaN or Inf: operands split into two bf16 terms turn some infinities (0 x Inf, Inf - Inf between the
+// terms) into NaN where plain arithmetic has none, matrix products bring slots together that a row must not see, and
+// probabilities relative to a reference that lags the maximum overflow earlier than the body's, which are at most 1.
 //
 // Per tile of kThreads slots:
 //   phase A  thread = slot: gather the K row through the block table, rotate it at the slot's

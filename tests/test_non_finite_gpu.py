@@ -77,3 +77,21 @@ def test_a_non_finite_value_under_a_vanishing_weight(mepic, oracle_attn, kv_dtyp
     got = run(mepic, case, general, planned)
     assert not np.isfinite(got[hit]).any()
     assert np.array_equal(got[~hit], clean[~hit]) or np.abs(got[~hit] - clean[~hit]).max() <= TOL[kv_dtype]
+
+
+@pytest.mark.parametrize("kv_dtype,prefill,rise,power", [("bf16", True, 35.0, 100), ("bf16", False, 5.5, 117), ("f32", False, 5.5, 117)])
+def test_values_near_the_largest_float(mepic, oracle_attn, kv_dtype, prefill, rise, power):
+    """General path: V of 2^power in one dim, and scores that rise by less than moves the reference maximum, so that probabilities
+    are up to 2^rise. Sums of probability x value pass 2^128, the result does not, nor do the sums where the largest probability
+    is 1."""
+    case = W.assemble(s := structure(kv_dtype, 16, prefill, [700, 90]), align_with_oracle(s)[0])
+    case.q[:] = 0.0
+    case.q[:, :, 63] = 60.0                                  # one pair of dims, which hardly turns: score = k[63] x 7.65 log2 units
+    for n in range(700):                                     # (608: inside a tile and inside a wave's run, behind slots of score 0)
+        set_k(case.pages, int(case.block_tables[0, n // 16]), n % 16, 63, rise / 7.65 if n >= 608 else 0.0)
+        set_k(case.pages, int(case.block_tables[0, n // 16]), n % 16, 127, 0.0)
+    case.pages.v[:, :, 100, :] = torch.where(case.pages.v[:, :, 100, :].isnan(), float("nan"), 2.0 ** power)
+    got, want = run(mepic, case, True, False), oracle_out(oracle_attn, case)
+    big = np.arange(128) == 100
+    assert np.abs(got[:, :, big] / want[:, :, big] - 1.0).max() <= 2.0 ** -7
+    assert np.abs(got[:, :, ~big] - want[:, :, ~big]).max() <= TOL[kv_dtype]
