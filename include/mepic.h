@@ -195,7 +195,8 @@ typedef struct {
   const int32_t* kv_lens;           /* device [B] valid KV slots per request (<= max_blocks * P)      */
   const int32_t* q_positions;       /* device [n_q_tokens] absolute position of each query token      */
   const int32_t* cu_q_lens;         /* device [B+1] prefix sums of query tokens per request; prefill
-                                       only. Decode has one query token per request: n_q_tokens == B  */
+                                       only. Decode has one query token per request: n_q_tokens == B;
+                                       prefill tokens without a request (B == 0) are an error           */
   const int32_t* block_positions;   /* device [B][max_blocks] or NULL                                 */
   const uint32_t* block_valid_mask; /* device [B][max_blocks] or NULL                                 */
   int32_t B, n_q_tokens, Hq, Hkv, D, P, max_blocks, num_pages;

@@ -179,7 +179,7 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
   if (p->n_q_tokens == 0) return MEPIC_OK;
   if (!p->q || !p->out || !p->k_pages || !p->v_pages || !p->block_tables || !p->kv_lens || !p->q_positions)
     return MEPIC_ERR_INVALID;
-  if (prefill && !p->cu_q_lens) return MEPIC_ERR_INVALID;
+  if (prefill && (!p->cu_q_lens || p->B == 0)) return MEPIC_ERR_INVALID;  // (query tokens that no request owns)
   if (p->kv_dtype == MEPIC_F8E4M3 && (!p->k_scales || !p->v_scales)) return MEPIC_ERR_INVALID;
   if (!(p->rope_theta > 0.f)) return MEPIC_ERR_INVALID;
   if ((p->timing_start == nullptr) != (p->timing_stop == nullptr)) return MEPIC_ERR_INVALID;

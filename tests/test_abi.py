@@ -102,6 +102,17 @@ def test_null_pointers_are_rejected_before_any_launch(mepic):
     assert lib.mepic_pool_get_stats(None, None) == mepic.ERR_INVALID
 
 
+def test_prefill_tokens_without_a_request_are_rejected_before_any_launch(mepic):
+    """No request owns them, so no kernel would write their rows nor how many partials they have."""
+    here = ctypes.c_void_p(1 << 20)                                     # never dereferenced on the host
+    pointers = dict.fromkeys(("q", "out", "k_pages", "v_pages", "block_tables", "kv_lens", "q_positions", "cu_q_lens", "workspace"), here)
+    for D in (64, 128):
+        p = params(mepic, B=0, n_q_tokens=5, D=D, workspace_bytes=1 << 30, **pointers)
+        assert mepic.load().mepic_attn_prefill(ctypes.byref(p), None) == mepic.ERR_INVALID
+        p.n_q_tokens = 0
+        assert mepic.load().mepic_attn_prefill(ctypes.byref(p), None) == mepic.OK
+
+
 def test_commit_shape_errors_are_rejected_before_any_launch(mepic):
     lib = mepic.load()
 
