@@ -822,7 +822,8 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
   }
 
   // ---- walk the wave's chunk request by request ----
-  // Ring of kNBuf register buffers: while a step is computed the K and V of the next kNBuf - 1 steps are in flight.
+  // Ring of kNBuf register buffers: while a step is computed the K and V of the next kNBuf - 1 steps are in flight. (The first
+  // step of a run is requested during the run before it, steps 1 .. kNBuf - 2 at its start, the others by the loop.)
   constexpr int kNBuf = n_buf(kFp8);
   Frag kbuf[kNBuf][2][kNK];
   VRaw vbuf[kNBuf][8];
@@ -891,6 +892,10 @@ __global__ __launch_bounds__(64 * kWaves, wg_per_cu(kFp8, kBatched)) void decode
           qhi[h][e] = x1 * c + x0 * sn;
         }
     }
+
+#pragma unroll
+    for (int r = 1; r < kNBuf - 1; ++r)
+      if (r < n_st) issue_step(r, r);
 
     const bool more = seg.seg_end < pos_end;
     if (more) seg_load(seg, seg.seg_end, b);  // the next run: in flight while this one is computed
