@@ -140,10 +140,13 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
   pl.kernel = p->kv_dtype == MEPIC_F32 ? K_DECODE_F32 : K_DECODE_SPLIT;
   cut_kv(p, n_blocks, pl.kernel == K_DECODE_F32 && p->D == 128 ? 256 : 512, &pl);
   const long n_rows = (long)p->n_q_tokens * G;
-  if (prefill && p->kv_dtype != MEPIC_F32 && n_rows >= 5L * p->B && !no_pieces) {
-    // A workgroup per 256 query rows: its cost hardly depends on how many of them there are (8 requests of 16 K bf16
-    // slots, 8 KV heads: 230 us from 1 to 9 query tokens), while the decode kernel takes every token for itself (same
-    // calls: 137 us for one token, 181 for two, 239 for three).
+  if (prefill && p->kv_dtype != MEPIC_F32 && p->n_q_tokens >= 3L * p->B && n_rows >= 5L * p->B && !no_pieces) {
+    // A workgroup per 256 query rows: its cost hardly depends on how many of them there are, while the decode kernel takes
+    // every token (with all its heads) for itself. us with either for 1, 2, 3, 4, 5 tokens a request, whatever the group size:
+    // 8 requests of 16 K bf16 slots on 8 KV heads 191 against 101, 125, 207, 202, 284; 32 of 4 K on 4 heads, 7 query heads
+    // each: 110 against 46, 81, 90, 98, 140; 1 of 4 K on 8 heads: 20 against 13, 13, 16, 17, 20. One or two tokens are the
+    // decode kernel's in every call measured (1.2 to 2.7 times). Three and four are a matter of size (0.8 to 1.9 times); calls of
+    // one query head a KV head, where short questions are short calls, leave them to the decode kernel.
     int kv_tiles, min_run, max_pieces;
     prefill_split_plan(p->B, p->Hkv, n_rows, max_kv, &kv_tiles, &min_run, &max_pieces);
     if (max_pieces > 0) {

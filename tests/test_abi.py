@@ -92,6 +92,21 @@ def test_workspace_size_and_shape_errors(mepic):
     assert mepic.attn_workspace_size(params(mepic, n_q_tokens=40, flags=mepic.FLAG_FORCE_GENERAL), True) > 0
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (16, 8), (28, 4), (32, 2)])
+def test_general_prefill_goes_by_tokens_not_rows(mepic, Hq, Hkv):
+    """One or two tokens a request run on the decode kernel whatever the group size: then the size query reports its partials,
+    and more for the kernel of 256 rows a workgroup, which can cut this one long context finer."""
+    first = 5 if Hq == Hkv else 3
+
+    def size(n_q):
+        return mepic.attn_workspace_size(params(mepic, B=1, n_q_tokens=n_q, Hq=Hq, Hkv=Hkv, P=32, max_blocks=512), True)
+    for n_q in range(1, 7):
+        splits = min(-(-2048 // (n_q * Hkv)), 64)
+        splits = -(-64 // -(-64 // splits))                       # whole tiles of 256 slots, equally many in each
+        decode = n_q * Hq * splits * (128 + 2) * 4
+        assert size(n_q) == decode if n_q < first else size(n_q) > decode, n_q
+
+
 def test_null_pointers_are_rejected_before_any_launch(mepic):
     lib = mepic.load()
     p = params(mepic)

@@ -139,6 +139,13 @@ def test_decode_forms(mepic, oracle_attn, kv_dtype, D, P, interleaved, pads_are_
     check(mepic, oracle_attn, few, pads_are_positions, interleaved)
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (28, 4), (32, 2)])
+@pytest.mark.parametrize("n_q", [[1], [2, 2, 2], [2, 4, 3], [5, 5]])
+def test_prefill_of_few_tokens(mepic, oracle_attn, n_q, Hq, Hkv):
+    """Both sides of the line between the two prefill kernels, which goes by tokens, for several group sizes."""
+    check(mepic, oracle_attn, question_prefill(31, n_q, "bf16", P=32, Hq=Hq, Hkv=Hkv, chunk=700))
+
+
 @pytest.mark.parametrize("length", [1, 15, 16, 17, 32, 33, 128, 129, 256, 257, 1025, 5000])
 @pytest.mark.parametrize("Hq,Hkv", [(16, 1), (4, 4)])
 def test_decode_lengths(mepic, oracle_attn, length, Hq, Hkv):
