@@ -171,8 +171,12 @@ typedef enum { MEPIC_F32 = 0, MEPIC_BF16 = 1, MEPIC_F8E4M3 = 2 } mepic_dtype;
 
 enum {
   MEPIC_FLAG_ROPE_INTERLEAVED = 1u, /* pair (x[2i], x[2i+1]) instead of (x[i], x[i+D/2])              */
-  MEPIC_FLAG_FORCE_GENERAL = 2u,    /* run the general path (fp32 arithmetic) even where a faster
-                                       kernel exists (for tests: both must agree with the oracle)    */
+  MEPIC_FLAG_FORCE_GENERAL = 2u,    /* run the general path even where a faster kernel exists (for tests:
+                                       both must agree with the oracle). Its phases, softmax and sums are
+                                       fp32 and so is everything for fp32 pages; with bf16 and fp8 pages
+                                       rotated q and K and the probabilities enter matrix products as two
+                                       bf16 terms, 16 significant bits together: a score is off by at
+                                       most 2^-15 x scale x sum |q_i k_i|                              */
   MEPIC_FLAG_KV_READ_ONCE = 4u      /* a hint, never a change of the result: (almost) no page is read by
                                        more than one request of this call (the pool's unique and logical
                                        page counts nearly agree). The matrix-core decode kernels then load

@@ -1,6 +1,6 @@
 // General-path decode of fused-RoPE paged attention (§3.3.3) on matrix cores, for bf16 and e4m3 pages: both rotary
-// pairings, D 64 / 128, pages of 16 / 32 slots, block positions, valid masks; also prefill of so few rows per request that
-// attn_prefill_split.hip would idle. Split precision (split_common.h): the accuracy is that of the scalar body it replaces.
+// pairings, D 64 / 128, pages of 16 / 32 slots, block positions, valid masks; also prefill of so few tokens per request that
+// attn_prefill_split.hip would idle. Split precision (split_common.h).
 //
 // One workgroup of 4 waves serves one (query token, KV head, split of the KV); a wave takes a contiguous run of steps of 32
 // slots (two groups of 16, each inside one page) for all G <= 16 heads of the group and the waves' partials are merged

@@ -1,7 +1,6 @@
 // General-path prefill of fused-RoPE paged attention (§3.3.3) on matrix cores, for bf16 and e4m3 pages: both rotary
 // pairings, D 64 / 128, pages of 16 / 32 slots, any number of query heads per KV head, block positions, valid masks.
-// Split precision throughout (split_common.h): the accuracy is that of the scalar general kernel, which this replaces
-// for more than a few query rows per request.
+// Split precision throughout (split_common.h). For more than a few query tokens per request.
 //
 // One workgroup of 8 waves serves 256 query rows (row = query token x head of the KV head's group, counted through
 // token boundaries so that no group size leaves rows idle) of one (request, KV head) and walks the KV in tiles of 64 slots.

@@ -1,5 +1,5 @@
-"""The general path's matrix-core kernels (split precision) against the fp64 oracle: every form they take over from the
-scalar kernel, at the edges of their tiles. Their error is the output's own rounding to bf16 (half an ulp of an 8-bit significand,
+"""The general path's matrix-core kernels (split precision) against the fp64 oracle: every form they take, at the edges of their
+tiles, on values of unit variance (large ones: test_split_precision_gpu.py). Their error there is the output's own rounding to bf16 (half an ulp of an 8-bit significand,
 2^-8 of the value) plus a remainder of the operands' 2^-18 terms, bounded here by 2^-13 of the largest output."""
 import ctypes
 
