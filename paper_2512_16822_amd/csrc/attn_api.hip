@@ -64,11 +64,14 @@ int general_splits(const mepic_attn_params* p, int n_blocks) {
 }
 
 // The splits the general path's decode kernels use, at most that many: one round of the `resident` workgroups that run at a
-// time (each builds a rotation table first, and partials cost a merge), but none where the context is so short that
+// time, one or two a compute unit (each builds a rotation table first, and partials cost a merge), but none where the context is so short that
 // the merge's launch, about four turns of 128 slots, costs more than the turns it saves. Measured (us): 64 requests of 4 K bf16
 // slots, D 128, 8 KV heads: 187 with 512 workgroups, 194 with 1024, 202 with 2048; lengths mixed 1:32 270, 278, 255; 8 such
 // requests 39 with 512, 51 with 2048; 40 mixed requests, 12 heads: 202 with 960, 246 with 480; one fp32 request of 289
 // slots 9.0 without a second split, 11.1 with.
+// The cuts are the same for every request, and with as many (query token, KV head) pairs as workgroups run at a time there is one
+// split: then the longest request sets the time, however short the others are (the 255 against 270 us of the mixed lengths above;
+// one of 32 K slots among 64 of 1 K is walked by one workgroup a head).
 void cut_kv(const mepic_attn_params* p, int n_blocks, int resident, Plan* pl) {
   const long rows = (long)p->n_q_tokens * p->Hkv;
   const int turn_blocks = 128 / p->P, turns = (n_blocks + turn_blocks - 1) / turn_blocks;
@@ -138,7 +141,7 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
   // General path: one workgroup per (query token, KV head, split).
   pl.workspace_bytes = pl.min_workspace_bytes = partial_bytes(p, general_splits(p, n_blocks));
   pl.kernel = p->kv_dtype == MEPIC_F32 ? K_DECODE_F32 : K_DECODE_SPLIT;
-  cut_kv(p, n_blocks, pl.kernel == K_DECODE_F32 && p->D == 128 ? 256 : 512, &pl);
+  cut_kv(p, n_blocks, device_compute_units() * (pl.kernel == K_DECODE_F32 && p->D == 128 ? 1 : 2), &pl);
   const long n_rows = (long)p->n_q_tokens * G;
   if (prefill && p->kv_dtype != MEPIC_F32 && p->n_q_tokens >= 3L * p->B && n_rows >= 5L * p->B && !no_pieces) {
     // A workgroup per 256 query rows: its cost hardly depends on how many of them there are, while the decode kernel takes
