@@ -11,10 +11,10 @@
 // Rotation without a sine per key: q^.k^ = (R(pos_q - base) q).(R(pos_k - base) k). R(s), s in [0, 128), is a table in LDS
 // (fp32); base is the position of some earlier group, moved - and Q' computed afresh - when a group starts outside
 // [base, base + 112]: every fourth step along a run of consecutive positions, and wherever block positions jump (a step
-// whose groups lie too far apart is taken in two turns). What bounds it is the vector work on K (widen, rotate, split:
-// six instructions per element), not the products.
+// whose groups lie too far apart is taken in two turns). What bounds it is vector work, two thirds of its clocks, half
+// of it on K (widen, rotate, split: six instructions per element); not the products.
 //
-// 64 requests of 4.3 K bf16 slots with valid masks and block positions, 32 heads on 8: 382 us (scalar) -> 107 us a call
+// 64 requests of 4.3 K bf16 slots with valid masks and block positions, 32 heads on 8: 382 us (scalar) -> 110 us a call
 // (146 before the loads got scalar bases and a fixed order, so that a step's waits leave the next step's loads in flight, and
 // one round of workgroups); where no page is shared, 64 requests of 4 - 6 K slots, 249 us = 5.4 TB/s: HBM.
 //

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_mfma_bf16_kernel(const At
           const uint32_t wl = raw[ks].w[w], wh = raw[ks + 4].w[w];
           const float x0 = qs * (e ? __uint_as_float(wl & 0xffff0000u) : bf16_bits_to_f32(wl & 0xffffu));
           const float x1 = qs * (e ? __uint_as_float(wh & 0xffff0000u) : bf16_bits_to_f32(wh & 0xffffu));
-          // (frequencies through LDS, as in the other kernels, cost this one 0.3 %: 1054 -> 1057.5 us on 16 x 17 K slots)
+          // (straight from the arguments: through LDS, as in the other kernels, made no difference beyond that between runs)
           const float t = turns_frac((float)pos_q, a.freq_hi[i], a.freq_lo[i]);
           const float c = __builtin_amdgcn_cosf(t), s = __builtin_amdgcn_sinf(t);
           lo[e] = x0 * c - x1 * s;

@@ -5,8 +5,8 @@
 // One workgroup of 8 waves serves 256 query rows (row = query token x head of the KV head's group, counted through
 // token boundaries so that no group size leaves rows idle) of one (request, KV head) and walks the KV in tiles of 64 slots.
 // A workgroup fills a compute unit, so there is exactly one for each, and the work of a KV head - all its (row tile,
-// KV tile) pairs in one sequence - is cut into equal runs, whatever the lengths; rows of a row tile that is cut are merged by
-// a second kernel. (Workgroups per (row tile, split) ran in rounds with idle units at the end, and empty ones among them,
+// KV tile) pairs in one sequence - is cut into equal runs, however the lengths differ as long as a run is at least the longest
+// request over the pieces a row has room for (prefill_split_plan); rows of a row tile that is cut are merged by a second kernel. (Workgroups per (row tile, split) ran in rounds with idle units at the end, and empty ones among them,
 // for requests with fewer row tiles than the grid allows, put two full ones on the same unit: 1.6 times the time.)
 //   stage   a thread rotates one slot's share of K (8 rotary pairs) in fp32 at the slot's own position - hardware
 //           sin/cos of a phase reduced with the two-float frequency - and writes head and remainder to LDS in operand
@@ -14,10 +14,12 @@
 //   QK      S^T[32 slots x 32 rows] per wave, three v_mfma_f32_32x32x16_bf16 per 16 dims.
 //   softmax fp32, reference maximum raised lazily, as in attn_prefill_mfma.hip.
 //   PV      O^T[D x 32 rows] += V^T x P^T, two products (head and remainder of P) per operand read.
-// The rotation is shared by 256 rows and every K/V operand read from LDS feeds 1.5 (K) or 2 (V) products, so the loop is
-// bound by the matrix pipe: 80 products per wave and tile where the bf16 kernel has 32. Measured against the scalar kernel:
-// 8 requests of 2 - 12 K fp8 slots, 128 question tokens, 28 heads on 4: 10 772 -> 257 us a call (335 with workgroups per row
-// tile and split); 4 of 4.2 K bf16 slots with masks and positions, 121 tokens, 32 heads on 8: 2 684 -> 110 us (128); 16 of
+// The rotation is shared by 256 rows and every K/V operand read from LDS feeds 1.5 (K) or 2 (V) products; 80 products per wave
+// and tile where the bf16 kernel has 32. Neither pipe bounds the loop alone: on the fp8 call below vector instructions issue
+// for 269 K of 580 K clocks (each row tile rotates its keys anew, with a sine and a cosine a pair), the matrix pipe is busy for
+// 222 K, and the two groups of waves overlap them only in part. Measured against the scalar kernel:
+// 8 requests of 2 - 12 K fp8 slots, 128 question tokens, 28 heads on 4: 10 772 -> 251 us a call (335 with workgroups per row
+// tile and split); 4 of 4.2 K bf16 slots with masks and positions, 121 tokens, 32 heads on 8: 2 684 -> 108 us (128); 16 of
 // 17 K bf16 slots in pages of 32, 256 tokens: 480 TFLOP/s of attention, 1.2 PFLOP/s of products.
 //
 // Slots that do not take part for any row (pads, past kv_len) are zeroed in V when staged. A slot that only some rows
@@ -619,8 +621,11 @@ hipError_t launch_prefill_split(const AttnArgs& a, hipStream_t s) {
 }
 
 // How the call is cut. A row tile is cut where the workgroups' runs meet, so with W workgroups per head and R row tiles into
-// about W / R + 1 pieces; twice that for requests longer than the mean, by the least run. B or the work may be too
-// much for the kernel's prefix sums: then max_pieces is 0.
+// about W / R + 1 pieces; there is room for twice that, for requests longer than the mean. The room is a row's (max_pieces partials
+// of D + 2 floats each: 8 of them, 119 MB, on the fp8 call above, where most rows come in two or three), and a run is at least
+// what keeps the longest request within it: one request of 32 K slots among 63 of 1 K on 4 KV heads makes runs of 171 tiles where
+// an even share is 24, and leaves 55 of a head's 64 workgroups idle. B or the work may be too much for the kernel's prefix
+// sums: then max_pieces is 0.
 void prefill_split_plan(int B, int Hkv, long n_rows, int max_kv_len, int* kv_tiles, int* min_run, int* max_pieces) {
   const int W = prefill_split_workgroups_per_head(Hkv), T = max((max_kv_len + kTile - 1) / kTile, 1);
   const long R = max((n_rows + kRows - 1) / kRows, (long)B);

