@@ -116,7 +116,7 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
     // Matrix-core decode: persistent waves cut each KV head's sequence of steps into equal chunks; here only
     // the bound on partials per request (sizes the workspace) and the minimum chunk are fixed.
     pl.kernel = mfma_fp8 ? K_DECODE_MFMA_F8 : K_DECODE_MFMA_BF16;
-    decode_mfma_plan(p->B, p->Hkv, max_kv, mfma_fp8, &pl.n_splits, &pl.blocks_per_split);
+    decode_mfma_plan(p->B, p->Hkv, max_kv, &pl.n_splits, &pl.blocks_per_split);
     pl.workspace_bytes = (size_t)p->n_q_tokens * p->Hq * pl.n_splits * (p->D + 2) * sizeof(float) +
                          (size_t)(p->B + 2) * sizeof(int32_t);
     pl.min_workspace_bytes = pl.workspace_bytes;
@@ -223,7 +223,7 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
     case K_DECODE_MFMA_BF16:
     case K_DECODE_MFMA_F8:
       g_last_kernel = pl.kernel == K_DECODE_MFMA_F8 ? "decode_mfma_fp8" : "decode_mfma_bf16";
-      e = launch_decode_mfma(a, s);
+      e = launch_decode_plain(a, s);
       break;
     case K_PREFILL_MFMA_BF16:
       g_last_kernel = "prefill_mfma_bf16";
@@ -260,7 +260,7 @@ int run_batched(const mepic_attn_params* p, const int32_t* plan, const mepic_dec
     return MEPIC_ERR_INVALID;
   if ((size_t)(info->n_runs + 1) * sizeof(int) > 48 * 1024) return MEPIC_ERR_UNSUPPORTED;  // run prefix sums live in LDS
   // the plan cut the work for the waves of the device it was built on
-  if (info->n_waves != decode_mfma_waves_per_head(p->Hkv, mfma_fp8)) return MEPIC_ERR_INVALID;
+  if (info->n_waves != decode_mfma_waves_per_head(p->Hkv)) return MEPIC_ERR_INVALID;
   const size_t need = (size_t)p->n_q_tokens * p->Hq * info->n_splits * (p->D + 2) * sizeof(float);
   if (bytes_only) {
     *bytes_only = need;

@@ -4,7 +4,7 @@
 //
 // One workgroup of 4 waves serves one (query token, KV head, split of the KV); a wave takes a contiguous run of steps of 32
 // slots (two groups of 16, each inside one page) for all G <= 16 heads of the group and the waves' partials are merged
-// through LDS. Operands come straight from the pages, as in attn_decode_mfma.hip:
+// through LDS. Operands come straight from the pages, as in attn_decode_plain.hip:
 //   S^T[16 slots x 16 heads] per group = Khat x Q'^T, three v_mfma_f32_16x16x32_bf16 per 32 dims
 //   O  [16 heads x D]       += P x V, two per 16 dims of the output: the k index of the product runs over slots 4 kg ..
 //        4 kg + 3 of the first and of the second group, which is what a lane's score registers hold.

@@ -1,0 +1,67 @@
+"""Plain decode: the forms its kernel takes (query heads a KV head, speed of the rotary frequencies, page type) at lengths around
+its turns, table spans and windows of page ids."""
+import numpy as np
+import pytest
+
+import workloads as W
+from harness import DeviceCase, align_with_oracle, oracle_out
+
+pytestmark = pytest.mark.gpu
+
+# around one and two steps, the 64-, 128- and 256-slot spans between two advances of Q', a window of 64 page ids (1024, 2048 slots)
+LENGTHS = [1, 15, 16, 17, 31, 32, 33, 47, 63, 64, 65, 96, 127, 128, 129, 160, 255, 256, 257, 300, 511, 513, 1023, 1025, 2049, 2100]
+
+
+def structure(G, Hkv, kv_dtype, theta, lengths, seed):
+    st = W.Structure("plain", "decode", len(lengths), G * Hkv, Hkv, 128, 16 if kv_dtype == "bf16" else 32, theta, "bf16", kv_dtype, seed)
+    st.requests, st.extra_tail, st.n_q = [[(0, n, 0)] for n in lengths], 0, [1] * len(lengths)
+    return st
+
+
+def rel(got, want):
+    return float(np.linalg.norm(got - want) / np.linalg.norm(want))
+
+
+# Q', keys (or their constants), probabilities and results are rounded to 16 bits or better: at most 2^-9 of each, 2^-7 together
+BOUND = 2.0 ** -7
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
+@pytest.mark.parametrize("theta", [3e2, 1e4, 5e5])
+@pytest.mark.parametrize("G", [1, 4, 5, 6, 8, 9, 16])
+def test_groups_and_frequencies(mepic, oracle_attn, G, theta, kv_dtype):
+    case = W.assemble(s := structure(G, 2, kv_dtype, theta, LENGTHS, 90 + G), align_with_oracle(s)[0])
+    dc = DeviceCase(mepic, case)
+    got, want = dc.run(), oracle_out(oracle_attn, case)
+    assert mepic.last_kernel().startswith("decode_mfma")
+    assert np.isfinite(got).all() and rel(got, want) <= BOUND
+    assert np.array_equal(DeviceCase(mepic, case, flags=mepic.FLAG_KV_READ_ONCE).run(), got)
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
+@pytest.mark.parametrize("Hkv,G,B", [(8, 4, 1), (3, 8, 3), (8, 7, 66), (12, 1, 130)])
+def test_waves_runs_and_requests(mepic, oracle_attn, Hkv, G, B, kv_dtype):
+    """One request over all waves, several runs a wave, lengths in the lanes of a wave and (more than 64 requests) in LDS."""
+    lengths = [(97 * b * b + 41) % 700 + 1 for b in range(B)] if B > 1 else [9000]
+    case = W.assemble(s := structure(G, Hkv, kv_dtype, 1e6, lengths, 7), align_with_oracle(s)[0])
+    got, want = DeviceCase(mepic, case).run(), oracle_out(oracle_attn, case)
+    assert np.isfinite(got).all() and rel(got, want) <= BOUND
+
+
+@pytest.mark.parametrize("G,theta", [(4, 4.04e5), (8, 4.04e5), (4, 8.2e3), (5, 8.2e3), (4, 7.9e3), (6, 4.0e5)])
+def test_pair_with_the_largest_remainder(mepic, oracle_attn, G, theta):
+    """rope_theta on either side of the lines between two terms, three and a rotation; all of q and K in the pair that the terms left out
+    concern most. Scores of up to S nats are then off by S (2.5e-3 + 3 x 2^-9) at most, and the result by e to that."""
+    case = W.assemble(s := structure(G, 2, "bf16", theta, [700, 129, 40, 1500], 12), align_with_oracle(s)[0])
+    keep = np.isin(np.arange(128), (32, 96))
+    case.q[:, :, ~keep] = 0.0
+    k = W.unpack_k(case.pages.k.float().nan_to_num(0.0))
+    k[..., ~keep] = 0.0
+    case.pages.k = W.pack_k(W.store_round(k, "bf16")[0], "bf16")
+    case.q *= 5.0
+    k, q = k.numpy(), np.asarray(case.q.float() if hasattr(case.q, "float") else case.q)
+    largest = np.sqrt((q ** 2).sum(-1).max()) * np.sqrt((k ** 2).sum(-1).max()) / np.sqrt(128.0)
+    got, want = DeviceCase(mepic, case).run(), oracle_out(oracle_attn, case)
+    v = float(case.pages.v.float().nan_to_num(0.0).abs().max())
+    bound = (np.exp(2 * largest * (2.5e-3 + 3 * 2.0 ** -9)) - 1) * v + 2.0 ** -8 * v
+    assert np.abs(got - want).max() <= bound and rel(got, want) <= 2.0 * BOUND
