@@ -4,9 +4,11 @@
 //
 // Persistent waves, stream-K over pages. The grid is one workgroup of eight waves (two a SIMD) per compute unit; workgroup g serves KV
 // head g % Hkv (consecutive workgroups land on consecutive XCDs, so one KV head's pages stay in one XCD's L2). For one KV head
-// the steps of all requests form one sequence of length T; the waves of that head cut it into equal contiguous chunks,
-// regardless of request boundaries. A wave writes one partial (max, sum, un-normalised output) per request it touched; a second
-// kernel merges the partials of each (request, head).
+// the steps of all requests form one sequence of length T; the waves of that head cut it into equal contiguous chunks, at
+// request boundaries where that comes out even enough (up to 64 requests), regardless of them otherwise. A wave writes one partial (max, sum,
+// un-normalised output) per request it touched; a second kernel merges the partials of each (request, head). Consecutive chunks
+// go to different workgroups: a call too small for all waves is spread over all compute units (6 requests of up to 430 bf16 slots 10.6
+// -> 9.2 us), and the streams that a compute unit reads lie far apart (8 requests of 65 537 slots 332 -> 320 us).
 //
 // Everything a step needs comes straight from the pages into registers as 16-byte loads that (nearly) are matrix operands:
 //
@@ -35,13 +37,12 @@
 // into two e4m3 terms (p*4 = hi + lo, 8 significant bits together); the page's V scale rides on the probabilities, O being kept
 // in units of a reference scale that is raised (with a rescale of O) only when a page's scale exceeds it by 1.75 x.
 //
-// What bounds it. Where pages are read once, HBM: 8 requests of 65 537 bf16 slots with the read-once hint 334 us = 6.4 TB/s (a kernel that
-// only loads in this pattern takes 316). Where requests share pages, what misses L2: 64 requests of 4.3 K slots ask L1 for 1.13 GB (33 us at a
+// What bounds it. Where pages are read once, HBM: 8 requests of 65 537 bf16 slots with the read-once hint 319 us = 6.7 TB/s (two requests' worth
+// of waves side by side on a unit: 332). Where requests share pages, what misses L2: 64 requests of 4.3 K slots ask L1 for 1.13 GB (33 us at a
 // line a two clocks on every unit), of which 0.36 GB miss L2, and those come at 6 - 7 TB/s whether from HBM or the Infinity Cache:
-// 81.5 -> 73.4 us a call (47 with every page in L2); 128 requests of 2 - 33 K fp8 slots 212 -> 180 us. Measured and of no use there: requesting two or
+// 81.5 -> 71.2 us a call (47 with every page in L2); 128 requests of 2 - 33 K fp8 slots 212 -> 180 us. Measured and of no use there: requesting two or
 // three steps ahead by touching a word of every line (the lines are gone from the 32 KB of L1 again: 102 - 112 us), the
-// non-temporal hint for pages of few readers (misses 0.36 -> 0.30 GB, but those then always come from HBM: 78 - 94 us), cuts
-// at the same places of every request (as many misses, the waves drift apart).
+// non-temporal hint for pages of few readers (misses 0.36 -> 0.30 GB, but those then always come from HBM: 78 - 94 us).
 #include "decode_common.h"
 #include "merge_partials.h"
 
@@ -152,24 +153,58 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   }
 
   const int hk = (int)blockIdx.x % Hkv;
-  const int wk = ((int)blockIdx.x / Hkv) * kWaves + wave, n_k = ((int)gridDim.x / Hkv) * kWaves;
+  // (waves of one workgroup take parts far from each other: a call too small for all waves still uses all compute units)
+  const int n_wg = (int)gridDim.x / Hkv, wk = wave * n_wg + (int)blockIdx.x / Hkv, n_k = n_wg * kWaves;
   int chunk = 0, pos_begin = 0, pos_end = 0;
+  bool whole = false;          // every wave has one run: requests are cut into pieces of their own
+  int upto = 0, piece = 0;     // whole: lane b: pieces of the requests up to b; the wave's piece of its request
   auto cut = [&]() __attribute__((always_inline)) {  // this wave's part of the sequence
     const int T = cum_at(a.B);
     chunk = uni(max((T + n_k - 1) / n_k, a.blocks_per_split));  // blocks_per_split carries the minimum chunk
-    pos_begin = wk * chunk;
-    pos_end = min(pos_begin + chunk, T);
+    // Where a wave's part runs from one request into the next, it pays for a second start (page ids, Q') and a second partial:
+    // some 2 - 3 us. So requests are cut into equal pieces of their own, one a wave, if there are waves enough for pieces at most a step (turn)
+    // and a sixteenth longer than parts of the sequence would be. us a call without and with: 60 requests of up to 407 e4m3 slots 18.6 -> 15.8, 19
+    // of up to 4 K 25.2 -> 20.8; 64 of 4.3 K bf16 74.5 -> 71.2, 56 of up to 2.9 K 43.5 -> 41.3; the worst of fifty mixes lost 3 %.
+    if (in_lanes && a.B > 1 && chunk + kPack > 2 && T < 1 << 20) {
+      const int steps = steps_of(len_lane);
+      auto pieces_of = [](int n, int c) __attribute__((always_inline)) {  // n / c rounded up (exact: n + c < 2^21)
+        return (int)(((float)(n + c) - 0.5f) * __builtin_amdgcn_rcpf((float)c));
+      };
+      const int c0 = (chunk + kPack - 1) / kPack * kPack, by = kPack * (1 + chunk / 64), most = c0 + kPack + chunk / 16;
+      int c = c0, pieces = 0;
+      for (; c <= most; c += by) {
+        pieces = pieces_of(steps, c);
+        upto = wave_scan(pieces);
+        whole = __builtin_amdgcn_readlane(upto, 63) <= n_k;
+        if (whole) break;
+      }
+      if (whole) {
+        const int b = (int)__popcll(__ballot(upto <= wk));
+        if (b < a.B) {
+          const int k = __builtin_amdgcn_readlane(pieces, b), n = __builtin_amdgcn_readlane(steps, b);
+          piece = wk - (__builtin_amdgcn_readlane(upto, b) - k);
+          const int len = uni((pieces_of(n, k) + kPack - 1) / kPack * kPack);  // as even as whole turns allow
+          const int first = cum_at(b);
+          pos_begin = first + min(piece * len, n);
+          pos_end = first + min(piece * len + len, n);
+        }
+      }
+    }
+    if (!whole) {
+      pos_begin = wk * chunk;
+      pos_end = min(pos_begin + chunk, T);
+    }
     if (blockIdx.x == 0 && wave == 0) {  // what the merge kernel needs to find each request's partials
       for (int i = lane; i <= a.B; i += 64) {
         if (in_lanes) {
-          if (i < a.B) a.part_meta[i + 1] = cum_lane;
+          if (i < a.B) a.part_meta[i + 1] = whole ? upto : cum_lane;
         } else {
           a.part_meta[i] = cum[i];
         }
       }
       if (lane == 0) {
         a.part_meta[0] = 0;
-        a.part_meta[a.B + 1] = chunk;
+        a.part_meta[a.B + 1] = whole ? 1 : chunk;
       }
     }
   };
@@ -191,7 +226,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     }
     sg.b = b; sg.c0 = c0; sg.seg_end = min(pos_end, c1); sg.n_st = sg.seg_end - pos; sg.step_first = pos - c0;
     sg.L = in_lanes ? __builtin_amdgcn_readlane(len_lane, b) : sload(a.kv_lens, b);
-    const int j0 = kBps * sg.step_first, jl = (sg.L + kP - 1) / kP - 1;
+    const int j0 = kBps * sg.step_first, jl = min((sg.L + kP - 1) / kP, j0 + kBps * sg.n_st) - 1;  // first and last block
     const size_t row = (size_t)b * a.max_blocks;
     sg.bt0 = a.block_tables[row + min(j0 + lane, jl)];
     sg.bt1 = a.block_tables[row + min(j0 + 64 + lane, jl)];
@@ -267,14 +302,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   uint4 vf[kPack][kNVec];
   auto issue_k = [&](int p0, int p1) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < kPack; ++s)
+    for (int j = 0; j < kNK; ++j)  // (pages in turn: 333.7 -> 331.8 us on 8 requests of 65 537 bf16 slots)
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const char* p = kbase + (uint64_t)(uint32_t)((kFp8 ? s : u) ? p1 : p0) * page_bytes + (kFp8 ? 256 * u : 0);
+      for (int s = 0; s < kPack; ++s)
 #pragma unroll
-        for (int j = 0; j < kNK; ++j)
+        for (int u = 0; u < 2; ++u) {
+          const char* p = kbase + (uint64_t)(uint32_t)((kFp8 ? s : u) ? p1 : p0) * page_bytes + (kFp8 ? 256 * u : 0);
           kf[s][u][j].u = load_page<kReadOnce>(reinterpret_cast<const uint4*>(p + j * (4 * kP * 16) + k_off));
-      }
+        }
   };
   auto issue_v = [&](int p0, int p1) __attribute__((always_inline)) {
 #pragma unroll
@@ -417,7 +452,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
 
   // Softmax of the turn's scores and the output products.
   // vs0, vs1: the V scales of the turn's pages (fp8).
-  auto attend = [&](floatx4 (&sc)[2], bool first, float vs0, float vs1) __attribute__((always_inline)) {
+  bool unset = true;  // no reference maximum yet
+  auto attend = [&](floatx4 (&sc)[2], float vs0, float vs1) __attribute__((always_inline)) {
     float pf[8], psum;
     auto exps = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -427,18 +463,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     exps();
     // The reference maximum only has to keep probabilities bounded (2^6); it is raised, and everything accumulated so far
     // rescaled, only when a lane's sum gets past that. Rare after the first step, so the cross-lane work sits in the branch.
-    if (first || __ballot(row_ok && !(psum <= kMostSum)) != 0) {
+    if (__ballot(row_ok && (unset || !(psum <= kMostSum))) != 0) {
       float mx = max_over_kgroups(fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
                                               fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3]))));
       if constexpr (kPack == 2) mx = fmaxf(mx, row_ror<8>(mx));  // one reference for a head's rows
-      float up = first ? mx : fmaxf(mx, 0.f);
+      float up = unset ? mx : fmaxf(mx, 0.f);
       if (!row_ok || up == -INFINITY) up = 0.f;  // (the other terms' rows have no reference)
       sc0 -= up;
       sc[0] -= up;
       sc[1] -= up;
       exps();
-      if (!first) {
-        const float alpha = __builtin_amdgcn_exp2f(-up);
+      const float alpha = unset ? 1.f : __builtin_amdgcn_exp2f(-up);
+      if (__ballot(row_ok && !unset) != 0) {  // (nothing is accumulated before the first step)
         l_part *= alpha;
         // accumulator rows of this lane are matrix rows 4 kg + e; their factors live in lanes 4 kg + e
 #pragma unroll
@@ -448,6 +484,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
           for (int nt = 0; nt < 8; ++nt) o[nt][e] *= ar;
         }
       }
+      unset = unset && mx == -INFINITY;
     }
     l_part += psum;
     // A lane has the probabilities of four slots of either product. Exchanged between neighbouring k-groups they are those of
@@ -537,11 +574,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   auto of_lane = [](float x, int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), i)); };
   issue_first();
   for (;;) {
-    const int b = seg.b, c0 = seg.c0, n_st = seg.n_st, step_first = seg.step_first, L = seg.L, jend = (L + kP - 1) / kP;
-    const int j0 = kBps * step_first;
+    const int b = seg.b, c0 = seg.c0, n_st = seg.n_st, step_first = seg.step_first, L = seg.L;
+    const int j0 = kBps * step_first, jend = min((L + kP - 1) / kP, j0 + kBps * n_st);
     const size_t bt_row = (size_t)b * a.max_blocks;
-    // Page ids of the run: lane i of bt_cur holds the page of block 64 k + i of the run (clamped to the request's last
-    // block), bt_nxt the 64 after those as stored; a step reads its ids with v_readlane. Vector loads on purpose: scalar
+    // Page ids of the run: lane i of bt_cur holds the page of block 64 k + i of the run (clamped to its last block), bt_nxt the 64 after those as stored; a step reads its ids with v_readlane. Vector loads on purpose: scalar
     // loads share a counter with the LDS reads, so every wait for a rotation constant would also wait for them.
     int bt_cur = clean(seg.bt0), bt_nxt = seg.bt1;
 
@@ -551,6 +587,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     sc0 = floatx4{0.f, 0.f, 0.f, 0.f};
     l_part = 0.f;
     v_ref = 0.f;
+    unset = true;
     {
       const float delta = (float)(uni(seg.posq) - step_first * 32 - 32 * part);
       const float qs = head < G ? a.qk_scale_log2 : 0.f;  // (rows without a head are zeros)
@@ -614,7 +651,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!kReadOnce) issue_k(p0, p1);
       __builtin_amdgcn_sched_barrier(0);
-      attend(sc, t == 0, vs0, vs1);
+      attend(sc, vs0, vs1);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (kReadOnce) issue_k(p0, p1);
       issue_v(p0, p1);
@@ -664,13 +701,13 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
           }
         }
       }
-      attend(sc, n_turns == 1, vs0, vs1);
+      attend(sc, vs0, vs1);
     }
     if (more) issue_first();
 
     // the partial of this (request, wave): un-normalised rows, reference max (log2 units), sum
     {
-      const int split = wk - c0 / chunk;
+      const int split = whole ? piece : wk - c0 / chunk;
       const size_t row0 = ((size_t)b * a.Hq + (size_t)hk * G) * a.n_splits + split;  // + g * n_splits
       float l_tot = sum_over_kgroups(l_part);
       if constexpr (kPack == 2) l_tot += row_ror<8>(l_tot);

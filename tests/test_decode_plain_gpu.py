@@ -39,10 +39,12 @@ def test_groups_and_frequencies(mepic, oracle_attn, G, theta, kv_dtype):
 
 
 @pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
-@pytest.mark.parametrize("Hkv,G,B", [(8, 4, 1), (3, 8, 3), (8, 7, 66), (12, 1, 130)])
-def test_waves_runs_and_requests(mepic, oracle_attn, Hkv, G, B, kv_dtype):
-    """One request over all waves, several runs a wave, lengths in the lanes of a wave and (more than 64 requests) in LDS."""
-    lengths = [(97 * b * b + 41) % 700 + 1 for b in range(B)] if B > 1 else [9000]
+@pytest.mark.parametrize("Hkv,G,B,most", [(8, 4, 1, 9000), (3, 8, 3, 700), (8, 7, 66, 700), (12, 1, 130, 700), (8, 4, 64, 1300),
+                                          (8, 5, 40, 3000), (2, 4, 20, 900), (4, 8, 64, 2000)])
+def test_waves_runs_and_requests(mepic, oracle_attn, Hkv, G, B, most, kv_dtype):
+    """One request over all waves, several runs a wave, requests cut into pieces of their own (even and mixed lengths)
+    or not, lengths in the lanes of a wave and (more than 64 requests) in LDS."""
+    lengths = [(97 * b * b + 41) % most + 1 if B != 64 or b % 3 else most for b in range(B)] if B > 1 else [most]
     case = W.assemble(s := structure(G, Hkv, kv_dtype, 1e6, lengths, 7), align_with_oracle(s)[0])
     got, want = DeviceCase(mepic, case).run(), oracle_out(oracle_attn, case)
     assert np.isfinite(got).all() and rel(got, want) <= BOUND
