@@ -8,15 +8,20 @@
 //   S^T[16 slots x 16 heads] per group = Khat x Q'^T, three v_mfma_f32_16x16x32_bf16 per 32 dims
 //   O  [16 heads x D]       += P x V, two per 16 dims of the output: the k index of the product runs over slots 4 kg ..
 //        4 kg + 3 of the first and of the second group, which is what a lane's score registers hold.
-// Rotation without a sine per key: q^.k^ = (R(pos_q - base) q).(R(pos_k - base) k). R(s), s in [0, 128), is a table in LDS
+// Probabilities change lanes by one swap instruction a register, so that V comes in pieces of eight slots of a row.
+// Rotation without a sine per key: q^.k^ = (R(pos_q - base) q).(R(pos_k - base) k). R(s), s in [0, kTab), is a table in LDS
 // (fp32); base is the position of some earlier group, moved - and Q' computed afresh - when a group starts outside
-// [base, base + 112]: every fourth step along a run of consecutive positions, and wherever block positions jump (a step
-// whose groups lie too far apart is taken in two turns). What bounds it is vector work, two thirds of its clocks, half
-// of it on K (widen, rotate, split: six instructions per element); not the products.
+// [base, base + kTab - 16]: every fourth (eighth) step along a run of consecutive positions, and wherever block positions jump (a step
+// whose groups lie too far apart is taken in two turns). The angles of a set-up are found once for the 16 lanes that share them.
+// kTerms (D 128, rotate-half, G <= 8): the slow half of the pairs, frequencies 32 .. 63, is not rotated. Over the table's span it turns by x t
+// about its middle, |x| <= 0.2, t in [-1, 1], and e^(-i x t) = (J0 + 2 J2) - i (2 J1 + 6 J3) t - 4 J2 t^2 + 8 i J3 t^3 up to 2 J4(x) = 2^-17
+// (Jacobi-Anger, Chebyshev polynomials written out). A head has two matrix rows and there are two sets of products: four terms
+// of Q', each as head and remainder, meet the keys as stored, exact in bf16, and the scores are their sum by powers of t.
 //
 // 64 requests of 4.3 K bf16 slots with valid masks and block positions, 32 heads on 8: 382 us (scalar) -> 110 us a call
-// (146 before the loads got scalar bases and a fixed order, so that a step's waits leave the next step's loads in flight, and
-// one round of workgroups); where no page is shared, 64 requests of 4 - 6 K slots, 249 us = 5.4 TB/s: HBM.
+// (loads with scalar bases in a fixed order, one round of workgroups) -> 84 us (terms, with half the set-ups; eight-slot pieces of V; 636 -> 425
+// vector instructions a step). e4m3: 35 requests of up to 1.6 K slots 41 -> 28 us. Where no page is shared, HBM: 30 requests of up to 20 K bf16 slots
+// on 12 heads 295 -> 222 us.
 //
 // A NaN or Inf in the merged result sends the workgroup through the scalar body: operand splits make NaN of some infinities, and
 // probabilities of up to 2^kRescaleSlack times values near the largest float make Inf of finite ones.
@@ -31,40 +36,64 @@ namespace {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
-constexpr int kTab = 128;             // slots the rotation table covers
-constexpr float kRescaleSlack = 6.f;  // the reference maximum may lag the true one by this much (log2 units)
+constexpr float kMostSum = 64.f;      // a lane's probabilities of a step above which the reference maximum is raised
 
-// Keep the elements whose bit of `keep` (4 bits) is set, zero the others.
-__device__ __forceinline__ void mask4(uint2& x, uint32_t keep) {
-  x.x &= (keep & 1u ? 0x0000ffffu : 0u) | (keep & 2u ? 0xffff0000u : 0u);
-  x.y &= (keep & 4u ? 0x0000ffffu : 0u) | (keep & 8u ? 0xffff0000u : 0u);
+// Keep the stored elements whose bit of `keep` (8 bits) is set, zero the others.
+__device__ __forceinline__ void mask_raw8(Raw8<false>& x, uint32_t keep) {
+  SplitFrag f;
+  f.u = x.r;
+  mask8(f, keep);
+  x.r = f.u;
 }
-__device__ __forceinline__ void mask4(uint32_t& x, uint32_t keep) {
+__device__ __forceinline__ void mask_raw8(Raw8<true>& x, uint32_t keep) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) x &= (keep >> e) & 1u ? ~0u : ~(0xffu << (8 * e));
+  for (int e = 0; e < 4; ++e) {
+    x.r.x &= (keep >> e) & 1u ? ~0u : ~(0xffu << (8 * e));
+    x.r.y &= (keep >> (4 + e)) & 1u ? ~0u : ~(0xffu << (8 * e));
+  }
+}
+
+// The value of the next lane up in the row of 16 lanes (0 past its end).
+__device__ __forceinline__ float next_lane(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x101, 0xf, 0xf, true));
 }
 
 template <int D>
 struct Merge {
   float m[kWaves][16], l[kWaves][16], o[kWaves][16][D];
 };
-constexpr size_t table_bytes(int D) { return (size_t)D / 4 * kTab * sizeof(float4); }
+// Dynamic LDS: the rotation table (with kTerms of the fast half only), whose place the merge and the scalar body take afterwards.
+template <int D, bool kTerms, int kTab>
+constexpr size_t lds_bytes() {
+  size_t n = (size_t)D / (kTerms ? 8 : 4) * kTab * sizeof(float4);
+  if (n < sizeof(Merge<D>)) n = sizeof(Merge<D>);
+  return n < sizeof(ScalarLds<4, kThreads>) ? sizeof(ScalarLds<4, kThreads>) : n;
+}
 
-template <bool kFp8, int D, int P, bool kIL>
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab>
 __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArgs a) {
   constexpr int kKs = D / 32;     // k-steps of 32 dims; granule of k-step j: dims 32 j + 8 kg ..
   constexpr int kNt = D / 16;     // output tiles of 16 dims
-  typedef typename std::conditional<kFp8, uint32_t, uint2>::type Raw4;  // four stored elements of a V row
+  constexpr int kRows = kTerms ? 2 : 1;  // matrix rows a head has
+  constexpr bool kShare = D == 128;      // Q' set-up: sines shared by the lanes of a k-group (eight pairs: faster without)
+  constexpr float kMiddle = 0.5f * (kTab - 1);  // of the table's span, and half its length
   typedef Merge<D> MergeT;
-  static_assert(sizeof(MergeT) <= table_bytes(D) && sizeof(ScalarLds<4, kThreads>) <= table_bytes(D), "they share the table's LDS");
+  static_assert(!kTerms || (D == 128 && !kIL), "the slow half of the pairs has k-steps of its own");
   extern __shared__ uint4 smem[];
   float4(*const tab)[kTab] = reinterpret_cast<float4(*)[kTab]>(smem);  // [frequencies 2 c, 2 c + 1][slot] {c0, s0, c1, s1}
   __shared__ uint4 q_lds[kKs][64];  // un-rotated q, granule j of every lane's head
   __shared__ __align__(16) float2 freq[D / 2];  // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
+  __shared__ float2 turn[kShare ? kWaves : 1][4][kRows][16];  // what Q' set-up shares: [wave][kg][row][pair] {cos, sin} times the row's factor
+  __shared__ __align__(16) float ratio[2][32];   // [row][pair of the slow half]: the second set in units of the first
 
   const int tid = threadIdx.x, lane = tid & 63, wave = uni_i(tid >> 6), n16 = lane & 15, kg = lane >> 4;
   if (tid < D / 2) freq[tid] = make_float2(a.freq_hi[tid], a.freq_lo[tid]);
   const int G = a.G, Hkv = a.Hkv;
+  const int head = n16 / kRows, term = n16 % kRows;  // of this lane's matrix row
+  // Q' set-up: lane n16 finds the angle of the n16-th of the pairs that its 16 lanes have in common. Rotate-half: pairs (dims i,
+  // i + D/2) of granules h and h + kKs/2, i = 32 h + 8 kg + e; interleaved: four pairs inside each granule j, i = 16 j + 4 kg + e.
+  const int my_pair = (kIL ? 16 * (n16 >> 2) + 4 * kg + (n16 & 3) : 32 * (n16 >> 3) + 8 * kg + (n16 & 7)) & (D / 2 - 1);
+  const bool my_slow = kTerms && n16 >= 8;
   const int hk = (int)(blockIdx.x % (unsigned)Hkv), split = (int)blockIdx.z;
   const int t = (int)(blockIdx.y * (gridDim.x / (unsigned)Hkv) + blockIdx.x / (unsigned)Hkv);
   if (t >= a.n_q) return;
@@ -131,29 +160,27 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   using RawT = decltype(Raw8<kFp8>::r);
   constexpr int kElem = kFp8 ? 1 : 2;
   constexpr size_t kHeadBytes = (size_t)D * P * kElem;       // one KV head of a page, K or V alike
+  // V: dim 16 nt + n16, eight slots 8 (kg / 2) .. of group kg % 2 in one load (the time that a load takes to address does not
+  // depend on its width: e4m3 pages, 8 requests of 3 - 6 K slots on 12 heads, 44 us in two loads, 33 in one)
   Raw8<kFp8> kf[2][kKs];
-  Raw4 vf[2][kNt];
+  Raw8<kFp8> vf[kNt];
   const uint32_t k_off = kFp8 ? (uint32_t)(((kg >> 1) * P + n16) * 16 + (kg & 1) * 8) : (uint32_t)((kg * P + n16) * 16);
-  const uint32_t v_off = (uint32_t)((n16 * P + 4 * kg) * kElem);
+  const uint32_t v_off = (uint32_t)((n16 * P + 8 * (kg >> 1) + (P == 16 ? 0 : 16 * (kg & 1))) * kElem);
   constexpr uint32_t kStepK = (kFp8 ? 2 : 4) * P * 16;        // bytes between a lane's granules of successive k-steps
   auto issue_k = [&](int pg0, int pg1) __attribute__((always_inline)) {
+    // steps start at multiples of 32: a page of 32 is a whole step
+    const char* b0 = reinterpret_cast<const char*>(a.k_pages) + ((size_t)pg0 * Hkv + hk) * kHeadBytes;
+    const char* b1 = reinterpret_cast<const char*>(a.k_pages) + ((size_t)pg1 * Hkv + hk) * kHeadBytes + (P == 16 ? 0 : 16 * 16);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      // steps start at multiples of 32: a page of 32 is a whole step
-      const char* base = reinterpret_cast<const char*>(a.k_pages) + ((size_t)(u ? pg1 : pg0) * Hkv + hk) * kHeadBytes +
-                         (P == 16 ? 0 : 16 * 16 * u);
-#pragma unroll
-      for (int j = 0; j < kKs; ++j) kf[u][j].r = *reinterpret_cast<const RawT*>(base + j * kStepK + k_off);
+    for (int j = 0; j < kKs; ++j) {
+      kf[0][j].r = *reinterpret_cast<const RawT*>(b0 + j * kStepK + k_off);
+      kf[1][j].r = *reinterpret_cast<const RawT*>(b1 + j * kStepK + k_off);
     }
   };
   auto issue_v = [&](int pg0, int pg1) __attribute__((always_inline)) {
+    const char* base = reinterpret_cast<const char*>(a.v_pages) + ((size_t)((kg & 1) ? pg1 : pg0) * Hkv + hk) * kHeadBytes + v_off;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const char* base = reinterpret_cast<const char*>(a.v_pages) + ((size_t)(u ? pg1 : pg0) * Hkv + hk) * kHeadBytes +
-                         (P == 16 ? 0 : 16 * kElem * u);
-#pragma unroll
-      for (int nt = 0; nt < kNt; ++nt) vf[u][nt] = *reinterpret_cast<const Raw4*>(base + nt * (16 * P * kElem) + v_off);
-    }
+    for (int nt = 0; nt < kNt; ++nt) vf[nt].r = *reinterpret_cast<const RawT*>(base + nt * (16 * P * kElem));
   };
   int np0 = 0, np1 = 0;  // pages of the next step
   if (n_st > 0) {
@@ -166,17 +193,31 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   }
 
   // ---- q of this lane's head, un-rotated: granule j as stored ----
-  const bool row_ok = n16 < G;
+  const bool row_ok = term == 0 && head < G;
   if (wave == 0) {
-    const uint4* q4 = reinterpret_cast<const uint4*>(a.q) + ((size_t)t * a.Hq + (size_t)hk * G + (row_ok ? n16 : 0)) * (D / 8);
+    const uint4* q4 = reinterpret_cast<const uint4*>(a.q) + ((size_t)t * a.Hq + (size_t)hk * G + (head < G ? head : 0)) * (D / 8);
 #pragma unroll
-    for (int j = 0; j < kKs; ++j) q_lds[j][lane] = q4[4 * j + kg];
+    for (int j = 0; j < kKs; ++j) q_lds[j][lane] = head < G ? q4[4 * j + kg] : make_uint4(0, 0, 0, 0);  // (rows without a head are zeros)
   }
-  const float qs = row_ok ? a.qk_scale_log2 : 0.f;
 
   // ---- rotation table ----
   __syncthreads();
-  for (int i = tid; i < D / 4 * kTab; i += kThreads) {
+  const float my_hi = freq[my_pair].x, my_lo = freq[my_pair].y;
+  float my_f0 = a.qk_scale_log2, my_f1 = 0.f;  // factors of the two rows
+  if constexpr (kTerms) {
+    if (my_slow) {
+      const float x = kMiddle * 6.283185307f * my_hi, h = 0.5f * x, y = h * h;  // Bessel functions of x, as far as x <= 0.2 has use for
+      const float j0 = 1.f - y * (1.f - 0.25f * y), j1 = h * (1.f - y * (0.5f - y * (1.f / 12.f)));
+      const float j2 = 0.5f * y * (1.f - y * (1.f / 3.f)), j3 = h * y * (1.f / 6.f) * (1.f - 0.25f * y);
+      my_f1 = my_f0 * (2.f * j1 + 6.f * j3);
+      my_f0 *= j0 + 2.f * j2;
+      if (wave == 0) {
+        ratio[0][my_pair - 32] = -4.f * j2 / (j0 + 2.f * j2);
+        ratio[1][my_pair - 32] = -4.f * j3 / (j1 + 3.f * j3);
+      }
+    }
+  }
+  for (int i = tid; i < D / (kTerms ? 8 : 4) * kTab; i += kThreads) {
     const int c = i / kTab, s = i % kTab;
     const float t0 = turns_frac((float)s, freq[2 * c].x, freq[2 * c].y);
     const float t1 = turns_frac((float)s, freq[2 * c + 1].x, freq[2 * c + 1].y);
@@ -185,19 +226,30 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   }
   __syncthreads();
 
-  // Rotary pairs of a lane: rotate-half: pairs (dims i, i + D/2) of granules h and h + kKs/2, i = 32 h + 8 kg + e;
-  // interleaved: the four pairs inside each granule j, frequencies 16 j + 4 kg + e.
-  SplitFrag qh[kKs], ql[kKs];
+  // Q' as the B operands. kTerms: qh / ql hold the first set of the slow half (pairs of granules 1 and 3), qh2 / ql2 the second.
+  SplitFrag qh[kKs], ql[kKs], qh2[2], ql2[2];
   auto rotate_q = [&](int base) __attribute__((always_inline)) {
     const float delta = (float)(pos_q - base);
-    int again = 0;
-    asm volatile("" : "+v"(again));  // q and the frequencies are fetched anew each time: they must not stay in registers
-    auto rot = [&](float x0, float x1, int i, float& y0, float& y1) __attribute__((always_inline)) {
-      const float2 f = freq[i + again];
-      const float tr = turns_frac(delta, f.x, f.y);
+    if constexpr (kShare) {
+      const float tr = turns_frac(my_slow ? delta - kMiddle : delta, my_hi, my_lo);
       const float c = __builtin_amdgcn_cosf(tr), s = __builtin_amdgcn_sinf(tr);
-      y0 = (x0 * c - x1 * s) * qs;
-      y1 = (x1 * c + x0 * s) * qs;
+      turn[wave][kg][0][n16] = make_float2(c * my_f0, s * my_f0);
+      if constexpr (kTerms) turn[wave][kg][kRows - 1][n16] = make_float2(s * my_f1, -c * my_f1);  // (times -i)
+      __builtin_amdgcn_wave_barrier();  // (the wave's own LDS accesses are served in order)
+    }
+    int again = 0;
+    asm volatile("" : "+v"(again));  // q is fetched anew each time: it must not stay in registers
+    auto rot = [&](float x0, float x1, int p, float& y0, float& y1) __attribute__((always_inline)) {
+      float2 r;
+      if constexpr (kShare) {
+        r = turn[wave][kg][term][p + again];
+      } else {
+        const float2 f = freq[(kIL ? 16 * (p >> 2) + 4 * kg + (p & 3) : 32 * (p >> 3) + 8 * kg + (p & 7)) + again];
+        const float tr = turns_frac(delta, f.x, f.y);
+        r = make_float2(__builtin_amdgcn_cosf(tr) * my_f0, __builtin_amdgcn_sinf(tr) * my_f0);
+      }
+      y0 = x0 * r.x - x1 * r.y;
+      y1 = x1 * r.x + x0 * r.y;
     };
 #pragma unroll
     for (int j = 0; j < (kIL ? kKs : kKs / 2); ++j) {
@@ -208,22 +260,31 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       for (int w = 0; w < 4; ++w) {
         if constexpr (kIL) {
           float y0, y1;
-          rot(__uint_as_float(qa.w[w] << 16), __uint_as_float(qa.w[w] & 0xffff0000u), 16 * j + 4 * kg + w, y0, y1);
+          rot(__uint_as_float(qa.w[w] << 16), __uint_as_float(qa.w[w] & 0xffff0000u), 4 * j + w, y0, y1);
           split2(y0, y1, qh[j].w[w], ql[j].w[w]);
         } else {
-          const int i = 32 * j + 8 * kg + 2 * w, j1 = j + kKs / 2;
+          const int j1 = j + kKs / 2;
           float a0, b0, a1, b1;
-          rot(__uint_as_float(qa.w[w] << 16), __uint_as_float(qb.w[w] << 16), i, a0, b0);
-          rot(__uint_as_float(qa.w[w] & 0xffff0000u), __uint_as_float(qb.w[w] & 0xffff0000u), i + 1, a1, b1);
+          rot(__uint_as_float(qa.w[w] << 16), __uint_as_float(qb.w[w] << 16), 8 * j + 2 * w, a0, b0);
+          rot(__uint_as_float(qa.w[w] & 0xffff0000u), __uint_as_float(qb.w[w] & 0xffff0000u), 8 * j + 2 * w + 1, a1, b1);
           split2(a0, a1, qh[j].w[w], ql[j].w[w]);
           split2(b0, b1, qh[j1].w[w], ql[j1].w[w]);
+          if (kTerms && j == 1) {
+            const float2 r = *reinterpret_cast<const float2*>(&ratio[term][8 * kg + 2 * w + again]);
+            split2(a0 * r.x, a1 * r.y, qh2[0].w[w], ql2[0].w[w]);
+            split2(b0 * r.x, b1 * r.y, qh2[1].w[w], ql2[1].w[w]);
+          }
         }
       }
     }
   };
-  // scores of group u (16 slots x 16 heads), its keys rotated by R(s), s = s0 + n16
+  floatx4 sc0 = {0.f, 0.f, 0.f, 0.f};  // minus the reference maximum (log2 units): what bf16 score accumulators start from
+  // scores of group u (16 slots x 16 rows) relative to the reference (e4m3: before the page's scale), its keys rotated by
+  // R(s), s = s0 + n16
   auto score = [&](int u, int s0) __attribute__((always_inline)) {
-    floatx4 sc = {0.f, 0.f, 0.f, 0.f};
+    floatx4 sc;
+    if constexpr (kFp8) sc = floatx4{0.f, 0.f, 0.f, 0.f};
+    else sc = sc0;
     const float4* tp = &tab[0][min(max(s0, 0), kTab - 16) + n16];
     auto three = [&](const SplitFrag& kh, const SplitFrag& kl, int j) __attribute__((always_inline)) {
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh.v, qh[j].v, sc, 0, 0, 0);
@@ -231,7 +292,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl.v, qh[j].v, sc, 0, 0, 0);
     };
 #pragma unroll
-    for (int j = 0; j < (kIL ? kKs : kKs / 2); ++j) {
+    for (int j = 0; j < (kIL ? kKs : kTerms ? kKs / 4 : kKs / 2); ++j) {
       if constexpr (kIL) {
         float x[8];
         widen8<kFp8>(kf[u][j], x);
@@ -259,13 +320,34 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
         three(h1, l1, j1);
       }
     }
+    if constexpr (kTerms) {  // the slow half: keys as they are, exact in bf16
+      const SplitFrag k0 = bf16_of8<kFp8>(kf[u][1]), k1 = bf16_of8<kFp8>(kf[u][3]);
+      floatx4 s2 = {0.f, 0.f, 0.f, 0.f};
+      sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0.v, qh[1].v, sc, 0, 0, 0);
+      s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0.v, qh2[0].v, s2, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0.v, ql[1].v, sc, 0, 0, 0);
+      s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0.v, ql2[0].v, s2, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1.v, qh[3].v, sc, 0, 0, 0);
+      s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1.v, qh2[1].v, s2, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1.v, ql[3].v, sc, 0, 0, 0);
+      s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1.v, ql2[1].v, s2, 0, 0, 0);
+      const float t0 = (float)(s0 + 4 * kg) * (1.f / kMiddle) - 1.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float t = t0 + (float)e / kMiddle;
+        float x = __builtin_fmaf(next_lane(s2[e]), t, s2[e]);
+        x = __builtin_fmaf(x, t, next_lane(sc[e]));
+        sc[e] = __builtin_fmaf(x, t, sc[e]);
+      }
+    }
     return sc;
   };
 
   floatx4 o[kNt];
 #pragma unroll
   for (int nt = 0; nt < kNt; ++nt) o[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_part = 0.f;
+  bool unset = true;  // no reference maximum yet
+  float l_part = 0.f;
   int base = 0;
   bool have_base = false;
   auto inside = [&](int ps) __attribute__((always_inline)) {
@@ -277,10 +359,15 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   auto attend = [&](floatx4 (&sc)[2], uint32_t vis0, uint32_t vis1, int l0) __attribute__((always_inline)) {
     float vs0 = 1.f, vs1 = 1.f;
     if constexpr (kFp8) {
-      sc[0] *= __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0));
-      sc[1] *= __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0 + 1));
+      const float ks0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0));
+      const float ks1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.ksc), l0 + 1));
       vs0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.vsc), l0));
       vs1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur.vsc), l0 + 1));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sc[0][e] = __builtin_fmaf(sc[0][e], ks0, sc0[e]);
+        sc[1][e] = __builtin_fmaf(sc[1][e], ks1, sc0[e]);
+      }
     }
     const bool partial = (vis0 & vis1) != 0xffffu;
     if (partial) {
@@ -291,27 +378,35 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
         for (int e = 0; e < 4; ++e)
           if (!(((u ? vis1 : vis0) >> (4 * kg + e)) & 1u)) sc[u][e] = -INFINITY;
     }
-    const float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
-                           fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-    if (__any(mx > m_run + kRescaleSlack)) {
-      const float m_new = fmaxf(m_run, max_over_kgroups(mx));
-      const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
-      m_run = m_new;
-      l_part *= alpha;
+    float pf[8], psum;
+    auto exps = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {  // accumulator rows of this lane are heads 4 kg + e; their factors live in lanes 4 kg + e
-        const float ar = __shfl(alpha, 4 * kg + e);
+      for (int e = 0; e < 8; ++e) pf[e] = __builtin_amdgcn_exp2f(sc[e >> 2][e & 3]);
+      psum = ((pf[0] + pf[1]) + (pf[2] + pf[3])) + ((pf[4] + pf[5]) + (pf[6] + pf[7]));
+    };
+    exps();
+    // the reference maximum only has to keep probabilities bounded (2^6): raised, with everything accumulated so far rescaled,
+    // when a lane's sum gets past that
+    if (__ballot(row_ok && (unset || !(psum <= kMostSum))) != 0) {
+      const float mx = max_over_kgroups(fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
+                                              fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3]))));
+      float up = unset ? mx : fmaxf(mx, 0.f);
+      if (!row_ok || up == -INFINITY) up = 0.f;  // (the other terms' rows have no reference)
+      const float alpha = unset ? 1.f : __builtin_amdgcn_exp2f(-up);
+      sc0 -= up;
+      sc[0] -= up;
+      sc[1] -= up;
+      exps();
+      if (__ballot(row_ok && !unset) != 0) {  // (nothing is accumulated before the first step)
+        l_part *= alpha;
 #pragma unroll
-        for (int nt = 0; nt < kNt; ++nt) o[nt][e] *= ar;
+        for (int e = 0; e < 4; ++e) {  // accumulator rows of this lane are matrix rows 4 kg + e; their factors live in lanes 4 kg + e
+          const float ar = __shfl(alpha, 4 * kg + e);
+#pragma unroll
+          for (int nt = 0; nt < kNt; ++nt) o[nt][e] *= ar;
+        }
       }
-    }
-    const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
-    float pf[8];
-    float psum = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      pf[e] = __builtin_amdgcn_exp2f(sc[e >> 2][e & 3] - m_use);
-      psum += pf[e];
+      unset = unset && mx == -INFINITY;
     }
     l_part += psum;
     if constexpr (kFp8) {
@@ -322,12 +417,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       asm volatile("");
       // (V in place: a group whose turn is yet to come keeps its slots, under probabilities of zero)
       const uint32_t all0 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0), all1 = (uint32_t)__builtin_amdgcn_readlane((int)cur.vis, l0 + 1);
-      const uint32_t keep0 = (all0 >> (4 * kg)) & 0xfu, keep1 = (all1 >> (4 * kg)) & 0xfu;
+      const uint32_t keep = (((kg & 1) ? all1 : all0) >> (8 * (kg >> 1))) & 0xffu;
 #pragma unroll
-      for (int nt = 0; nt < kNt; ++nt) {
-        mask4(vf[0][nt], keep0);
-        mask4(vf[1][nt], keep1);
-      }
+      for (int nt = 0; nt < kNt; ++nt) mask_raw8(vf[nt], keep);
       if constexpr (kFp8) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -337,12 +429,18 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     SplitFrag ph, pl;
 #pragma unroll
     for (int w = 0; w < 4; ++w) split2(pf[2 * w], pf[2 * w + 1], ph.w[w], pl.w[w]);
+    // A lane has the probabilities of four slots of either group; exchanged between neighbouring k-groups they are those of
+    // the eight slots of one group that its V has.
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const auto x = __builtin_amdgcn_permlane16_swap(ph.w[w], ph.w[w + 2], false, false);
+      const auto y = __builtin_amdgcn_permlane16_swap(pl.w[w], pl.w[w + 2], false, false);
+      ph.w[w] = x[0]; ph.w[w + 2] = x[1];
+      pl.w[w] = y[0]; pl.w[w + 2] = y[1];
+    }
 #pragma unroll
     for (int nt = 0; nt < kNt; ++nt) {
-      Raw8<kFp8> both;
-      if constexpr (kFp8) both.r = make_uint2(vf[0][nt], vf[1][nt]);
-      else both.r = make_uint4(vf[0][nt].x, vf[0][nt].y, vf[1][nt].x, vf[1][nt].y);
-      const SplitFrag vb = bf16_of8<kFp8>(both);
+      const SplitFrag vb = bf16_of8<kFp8>(vf[nt]);
       o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph.v, vb.v, o[nt], 0, 0, 0);
       o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl.v, vb.v, o[nt], 0, 0, 0);
     }
@@ -398,7 +496,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   {
     const float l_tot = sum_over_kgroups(l_part);
     if (kg == 0) {
-      mg.m[wave][n16] = m_run;
+      mg.m[wave][n16] = unset ? -INFINITY : -sc0[0];
       mg.l[wave][n16] = l_tot;
     }
 #pragma unroll
@@ -411,17 +509,18 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   bool odd = false;
   for (int i = tid; i < G * (D / 4); i += kThreads) {
     const int g = i / (D / 4), dq = i % (D / 4);
-    float m = mg.m[0][g];
+    const int r = g * kRows;  // the head's matrix row
+    float m = mg.m[0][r];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, mg.m[w][g]);
+    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, mg.m[w][r]);
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
     float l = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float f = mg.m[w][g] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mg.m[w][g] - m);
-      const float4 y = *reinterpret_cast<const float4*>(&mg.o[w][g][4 * dq]);
+      const float f = mg.m[w][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mg.m[w][r] - m);
+      const float4 y = *reinterpret_cast<const float4*>(&mg.o[w][r][4 * dq]);
       x.x += f * y.x; x.y += f * y.y; x.z += f * y.z; x.w += f * y.w;
-      l += f * mg.l[w][g];
+      l += f * mg.l[w][r];
     }
     const float all = (x.x + x.y) + (x.z + x.w) + l;
     odd |= !(fabsf(all) < INFINITY);
@@ -446,20 +545,29 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
                                                                   n_begin, s_end, split, direct);
 }
 
-template <bool kFp8, int D, int P, bool kIL>
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
+  constexpr size_t lds = lds_bytes<D, kTerms, kTab>();
   static std::atomic<uint64_t> asked{0};
-  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL>), table_bytes(D), asked);
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab>), lds, asked);
   if (status != hipSuccess) return status;
   // KV heads fastest (neighbours go to different dies, which then each keep their own heads' pages); tokens over x and y
   const unsigned per_row = (unsigned)min(a.n_q, max(65536 / a.Hkv, 1));
   const dim3 grid((unsigned)a.Hkv * per_row, ((unsigned)a.n_q + per_row - 1) / per_row, (unsigned)a.n_splits);
-  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL>), grid, dim3(kThreads), table_bytes(D), s, a);
+  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab>), grid, dim3(kThreads), lds, s, a);
   return hipGetLastError();
 }
 template <bool kFp8, int D, int P>
 hipError_t launch_il(const AttnArgs& a, hipStream_t s) {
-  return a.interleaved ? launch_one<kFp8, D, P, true>(a, s) : launch_one<kFp8, D, P, false>(a, s);
+  if (a.interleaved) return launch_one<kFp8, D, P, true, false, 128>(a, s);
+  if constexpr (D == 128) {
+    // Terms where four of them are enough: x = half the table's span times the fastest slow frequency (rope_theta 4.1e5 and up with 256
+    // slots, 1.01e5 with 128). 84 us with 256 slots on the call above, 92 with 128.
+    const float f = 6.283185307f * a.freq_hi[32];
+    if (a.G <= 8 && 127.5f * f <= 0.2f) return launch_one<kFp8, D, P, false, true, 256>(a, s);
+    if (a.G <= 8 && 63.5f * f <= 0.2f) return launch_one<kFp8, D, P, false, true, 128>(a, s);
+  }
+  return launch_one<kFp8, D, P, false, false, 128>(a, s);
 }
 template <bool kFp8>
 hipError_t launch_kv(const AttnArgs& a, hipStream_t s) {

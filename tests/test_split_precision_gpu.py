@@ -10,8 +10,8 @@ from harness import DeviceCase, align_with_oracle, oracle_out
 pytestmark = pytest.mark.gpu
 
 
-def large_case(kv_dtype, P, prefill, q_scale):
-    st = W.Structure("large", "prefill" if prefill else "decode", 3, 8, 2, 128, P, 5e5, "bf16", kv_dtype, 97)
+def large_case(kv_dtype, P, prefill, q_scale, theta=5e5, G=4):
+    st = W.Structure("large", "prefill" if prefill else "decode", 3, 2 * G, 2, 128, P, theta, "bf16", kv_dtype, 97)
     st.requests, st.n_q, st.extra_tail = [[(0, 3000, 0)], [(0, 500, 0)], [(0, 40, 0)]], [40, 30, 9] if prefill else [1, 1, 1], 0
     case = W.assemble(st, align_with_oracle(st)[0])
     rng = np.random.default_rng(6)
@@ -50,7 +50,10 @@ def test_error_is_bounded_by_the_terms_of_the_scores(mepic, oracle_attn, kv_dtyp
     remainder product left out, 2^-17 for a chain of 128 fp32 sums, 2^-19 for the phases' sines on both sides make
     A 2^-15.7. Probabilities then change by a factor of at most e^(2 A 2^-15), and a row by that share of the sum of p |v|, next
     to its own rounding to bf16."""
-    case = large_case(kv_dtype, P, prefill, q_scale)
+    check_bound(mepic, oracle_attn, large_case(kv_dtype, P, prefill, q_scale))
+
+
+def check_bound(mepic, oracle_attn, case):
     got = DeviceCase(mepic, case, flags=mepic.FLAG_FORCE_GENERAL).run()
     want = oracle_out(oracle_attn, case)
     v = case.pages.v
@@ -58,6 +61,17 @@ def test_error_is_bounded_by_the_terms_of_the_scores(mepic, oracle_attn, kv_dtyp
     size = oracle_out(oracle_attn, case)                                            # sum of p |v|
     off = np.expm1(2.0 * score_terms(case) * 2.0 ** -15)[..., None]
     bound = np.abs(want) * 2.0 ** -8 + off * size + 2.0 ** -13 * np.abs(want).max()
-    print(f"\n{kv_dtype} prefill={prefill} q x {q_scale}: terms {score_terms(case).max():.0f}, error / bound {(np.abs(got - want) / bound).max():.3f}, "
+    print(f"\n{case.st.kv_dtype} theta {case.st.theta:g}: terms {score_terms(case).max():.0f}, error / bound {(np.abs(got - want) / bound).max():.3f}, "
           f"relative {np.linalg.norm(got - want) / np.linalg.norm(want):.2e}")
     assert (np.abs(got - want) <= bound).all()
+
+
+@pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("bf16", 32), ("f8e4m3", 32)])
+@pytest.mark.parametrize("G,theta", [(4, 4.07e5), (4, 1.01e5), (8, 4.07e5), (1, 1.01e5), (9, 4.07e5), (4, 9.9e4)])
+def test_error_where_terms_take_the_place_of_rotations(mepic, oracle_attn, kv_dtype, P, G, theta):
+    """Decode, at the slowest rope_theta of either table span (the last two: rotations): everything in the pair that the terms left out
+    concern most. They add 2 J4(0.2) = 2^-16.9 of a score: with the 2^-15.7 above still below 2^-15."""
+    case = large_case(kv_dtype, P, False, 4.0, theta, G)
+    other = ~np.isin(np.arange(128), (32, 96))
+    case.q[:, :, other] = 0.0
+    check_bound(mepic, oracle_attn, case)
