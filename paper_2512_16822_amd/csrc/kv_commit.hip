@@ -21,7 +21,7 @@ namespace {
 // Source tokens per workgroup: 64 for the same-format copy, 32 for the quantising one (measured on 64 x 1024 tokens:
 // 98.5 -> 95.0 us and 82.3 <- 86.0 us respectively).
 constexpr int kThreads = 256;
-constexpr int kStagedRuns = 1024;  // runs whose prefix sums a workgroup keeps in LDS; of the first kThreads, all there is
+constexpr int kStagedRuns = 1024;  // runs whose prefix sums a workgroup keeps in LDS
 
 struct CommitArgs {
   const void* k_new;
@@ -134,11 +134,6 @@ __global__ __launch_bounds__(kThreads) void kv_commit_kernel(const CommitArgs a)
   __shared__ int s_cu[kStagedRuns];
   __shared__ __attribute__((aligned(16))) unsigned char s_v[kTile * kPitch];
 
-  // The runs' requests and first slots share LDS with the V tile, which is written after their last use: 2 KB more would
-  // cost a workgroup per CU (bf16, 300 runs of 64 tokens: 31.0 -> 32.2 us).
-  int2* s_run = reinterpret_cast<int2*>(s_v);
-  static_assert(sizeof(s_v) >= kThreads * sizeof(int2), "the V tile does not hold the runs");
-
   const int tid = threadIdx.x;
   const int t0 = blockIdx.x * kTile;
   const int h = blockIdx.y;
@@ -147,24 +142,9 @@ __global__ __launch_bounds__(kThreads) void kv_commit_kernel(const CommitArgs a)
   Dst* k_pages = static_cast<Dst*>(a.k_pages);
   Dst* v_pages = static_cast<Dst*>(a.v_pages);
 
-  // What resolves the destinations is a chain of dependent loads: runs -> block table -> scales. Its first step goes to
-  // LDS in one trip, the prefix sums of up to kStagedRuns runs and the request and first slot of the first kThreads: a
-  // binary search in memory is a chain of 4 (16 runs) to 9 (272 runs) loads by itself. (44 K tokens in 272 runs, bf16 to
-  // e4m3: prefix sums 31.8 -> 29.2 us, request and slot 29.4 -> 28.9.)
-  const bool staged = a.n_runs < kStagedRuns;
-  int first_cu = 0;
-  int2 first_run = make_int2(0, 0);
-  auto load_runs = [&]() __attribute__((always_inline)) {
-    if (!staged) return;
-    if (tid <= a.n_runs) first_cu = a.cu_run_tokens[tid];
-    if (tid < a.n_runs) first_run = make_int2(a.run_request[tid], a.run_first_slot[tid]);
-  };
-  // The source addresses do not depend on the destination: every load of this thread is issued here, so that the rest of
-  // the chain runs under their latency. bf16 pages: the runs first, since loads return in order (1 token 3.08 -> 3.01 us,
-  // 64 requests of one 6.90 -> 6.72). Not for e4m3 and fp32 pages, where there are more loads per thread and the
-  // sources themselves are what the workgroup waits for (16 x 1000 tokens, e4m3 22.8 and 23.1, fp32 66.3 and 68.9).
-  constexpr bool kRunsFirst = sizeof(Dst) == 2;
-  if constexpr (kRunsFirst) load_runs();
+  // The source addresses do not depend on the destination: issue every load of this thread first, so that
+  // the dependent chain that resolves the destinations (prefix sums -> run -> block table -> scales) runs
+  // under their latency.
   constexpr int kUnits = (kTile * DX + kThreads - 1) / kThreads;
   Raw<Src, Dst> rk[kUnits], rv[kUnits];
 #pragma unroll
@@ -178,11 +158,12 @@ __global__ __launch_bounds__(kThreads) void kv_commit_kernel(const CommitArgs a)
     }
   }
 
-  if constexpr (!kRunsFirst) load_runs();
+  // The prefix sums of up to kStagedRuns runs go to LDS in one load: a binary search over them in memory is a chain of
+  // 4 (16 runs) to 9 (272 runs) dependent loads in front of the four that resolve a destination. (44 K tokens in 272 runs,
+  // bf16 to e4m3: 31.8 -> 29.2 us.)
+  const bool staged = a.n_runs < kStagedRuns;
   if (staged) {
-    s_cu[tid] = first_cu;
-    s_run[tid] = first_run;
-    for (int i = tid + kThreads; i <= a.n_runs; i += kThreads) s_cu[i] = a.cu_run_tokens[i];
+    for (int i = tid; i <= a.n_runs; i += kThreads) s_cu[i] = a.cu_run_tokens[i];
     __syncthreads();
   }
   auto cu_at = [&](int i) { return staged ? s_cu[i] : a.cu_run_tokens[i]; };
@@ -196,9 +177,8 @@ __global__ __launch_bounds__(kThreads) void kv_commit_kernel(const CommitArgs a)
         const int mid = (lo + hi) >> 1;
         if (cu_at(mid) <= t) lo = mid; else hi = mid;
       }
-      const int2 run = staged && lo < kThreads ? s_run[lo] : make_int2(a.run_request[lo], a.run_first_slot[lo]);
-      const int req = run.x;
-      const long n = (long)run.y + (t - cu_at(lo));
+      const int req = a.run_request[lo];
+      const long n = (long)a.run_first_slot[lo] + (t - cu_at(lo));
       const long blk = n / P;
       if (req >= 0 && req < a.B && n >= 0 && blk < a.max_blocks) {
         const int p = a.block_tables[(long)req * a.max_blocks + blk];
@@ -235,8 +215,10 @@ __global__ __launch_bounds__(kThreads) void kv_commit_kernel(const CommitArgs a)
 
   // V: (dim d, eight tokens) -> eight slots of the page row of d
   constexpr int kInner = P / 8;                   // groups per page when the tile is page-aligned
-  // A decode step brings a token per request: the groups past the last token are left out (bf16, 1 token 4.4 -> 3.1 us,
-  // 16 requests of one 5.1 -> 3.9).
+  // A decode step brings a token per request: the pages past the last token are left out (bf16, 1 token 4.4 -> 3.1 us,
+  // 16 requests of one 5.1 -> 3.9). Resolving the destinations sooner is no gain: with the runs' requests and first slots
+  // staged like the prefix sums, or the runs loaded before the sources, small calls took 0.1 - 0.3 us less, and of the large ones
+  // some 1 - 6 % more (150 K tokens of 12 bf16 heads 516 -> 543 us), as their workgroups write closer together.
   const int n_units = D * kInner * ((min(a.n_tokens - t0, kTile) + P - 1) / P);
   for (int u = tid; u < n_units; u += kThreads) {
     const int g = (u / (kInner * D)) * kInner + u % kInner;

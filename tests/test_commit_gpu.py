@@ -114,19 +114,19 @@ def test_out_of_range_requests_blocks_and_pages_are_skipped(mepic):
                           oracle_runs=oracle_runs))
 
 
-@pytest.mark.parametrize("n_runs", [256, 257])
-@pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("f8e4m3", 32), ("f32", 16)])
-def test_run_counts_at_the_edges_of_what_a_workgroup_stages(mepic, kv_dtype, P, n_runs):
-    """Requests and first slots of the first 256 runs are read from LDS, of the others from memory; short runs, so
-    that one tile spans many of them and both sides of an edge, and a last tile with few tokens."""
-    Hkv, D, MB = 2, 64, 2
-    rng = np.random.default_rng(n_runs)
-    pages = W.gen_pages(25, n_runs * MB, Hkv, P, D, kv_dtype)
-    bt = rng.permutation(n_runs * MB).reshape(n_runs, MB).astype(np.int32)
-    runs = [(b, int(rng.integers(0, 2 * P - 2)), int(rng.integers(0, 4))) for b in rng.permutation(n_runs)]
-    runs[-1] = (runs[-1][0], 3, 1)                       # never without a token
-    n = sum(c for _, _, c in runs)
-    assert_same(*run_both(mepic, pages, bt, runs, _src(rng, n, Hkv, D, kv_dtype), _src(rng, n, Hkv, D, kv_dtype)))
+@pytest.mark.parametrize("n_tokens", [1, 15, 16, 17, 32, 33, 63, 65])
+@pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("bf16", 32), ("f8e4m3", 32), ("f8e4m3", 16), ("f32", 16)])
+def test_last_tile_with_few_tokens(mepic, kv_dtype, P, n_tokens):
+    """A workgroup's V pass covers the pages of its 32 or 64 tokens that have any: one token of a page to all of it, one
+    token per request and the same tokens as one run."""
+    Hkv, D, MB = 2, 64, 5
+    rng = np.random.default_rng(n_tokens)
+    src = _src(rng, n_tokens, Hkv, D, kv_dtype), _src(rng, n_tokens, Hkv, D, kv_dtype)
+    for runs in ([(b, int(rng.integers(0, MB * P)), 1) for b in range(n_tokens)], [(0, 3, n_tokens)]):
+        B = len(runs)
+        pages = W.gen_pages(25, B * MB, Hkv, P, D, kv_dtype)
+        bt = rng.permutation(B * MB).reshape(B, MB).astype(np.int32)
+        assert_same(*run_both(mepic, pages, bt, runs, *src))
 
 
 @pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("f8e4m3", 32)])
