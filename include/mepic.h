@@ -179,10 +179,10 @@ enum {
                                        most 2^-15 x scale x sum |q_i k_i|                              */
   MEPIC_FLAG_KV_READ_ONCE = 4u      /* a hint, never a change of the result: (almost) no page is read by
                                        more than one request of this call (the pool's unique and logical
-                                       page counts nearly agree). The matrix-core decode kernels then load
-                                       V with the non-temporal hint: faster when every byte comes from
-                                       HBM once anyway, slower when requests do share pages, whose reuse
-                                       from the caches it defeats. Other kernels ignore it.            */
+                                       page counts nearly agree). The plain matrix-core decode kernel then
+                                       loads K and V with the non-temporal hint: faster when every byte
+                                       comes from HBM once anyway, slower when requests do share pages,
+                                       whose reuse from the caches it defeats. Other kernels ignore it. */
 };
 
 typedef struct {
