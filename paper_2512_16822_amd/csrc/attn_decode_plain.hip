@@ -32,10 +32,11 @@
 //   score and term. 292 -> 176 vector instructions a step, and these keys lose no bits to a rotation.
 // * fp8, two steps a turn. With G <= 8 rows 0-7 belong to the turn's first step and 8-15 to its second, Q' of the latter standing 32
 //   slots on: both use the same constants, and softmax, the split of the probabilities and their scaling happen once for both.
-//   260 -> 204 vector instructions a step.
+//   260 -> 204 vector instructions a step. Either half of the rows keeps a reference maximum and a reference V scale of its own, as two
+//   waves would, and they are brought together at the run's end.
 // fp8: the page's K scale multiplies the scores. V is never widened: PV takes the bytes as loaded and the probabilities split
-// into two e4m3 terms (p*4 = hi + lo, 8 significant bits together); the page's V scale rides on the probabilities, O being kept
-// in units of a reference scale that is raised (with a rescale of O) only when a page's scale exceeds it by 1.75 x.
+// into two e4m3 terms (p*16 = hi + lo, 8 significant bits together down to p = 2^-7); the page's V scale rides on the probabilities, O
+// being kept in units of a reference scale that is raised (with a rescale of O) only when a page's scale exceeds it by 1.75 x.
 //
 // What bounds it. Where pages are read once, HBM: 8 requests of 65 537 bf16 slots with the read-once hint 319 us = 6.7 TB/s (two requests' worth
 // of waves side by side on a unit: 332). Where requests share pages, what misses L2: 64 requests of 4.3 K slots ask L1 for 1.13 GB (33 us at a
@@ -51,7 +52,12 @@ namespace {
 
 constexpr int kD = 128;
 constexpr int kWaves = 8;
-constexpr float kMostSum = 64.f;  // a lane's probabilities of a step (at most 2^6 each) above which the reference maximum is raised
+// A lane's probabilities of a step (so at most that each) above which the reference maximum is raised. fp8: what e4m3 has room for,
+// 448, is their largest times the factor that they are split with and 1.75. A larger factor under a smaller sum puts the
+// split's absolute step (2^-10) lower beside probabilities of 1: error of 128 requests of 2 - 33 K slots against 64 bits, 4 under 64
+// 1.78e-3, 8 under 32 1.75e-3, 16 under 16 1.745e-3 (the result's own rounding 1.66e-3), all at the same time a call.
+__host__ __device__ constexpr float most_sum(bool fp8) { return fp8 ? 16.f : 64.f; }
+constexpr float kPScale = 256.f / most_sum(true);
 
 // The value of the lane kBy places up in the row of 16 lanes (0 past its end).
 template <int kBy>
@@ -323,7 +329,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   floatx4 o[8];
   floatx4 sc0;                 // minus the reference maximum (log2 units): what bf16 score accumulators start from
   float l_part;
-  float v_ref = 0.f;           // fp8: O is kept in units of this reference V scale (wave-uniform), raised lazily
+  float v_ref = 0.f;           // fp8: O is kept in units of this reference V scale (one for each part), raised lazily
+  float v_lim = 0.f, v_inv = 0.f;  // 1.75 v_ref, 1 / v_ref
   float qlo[2][8], qhi[2][8];  // Q' of this lane's matrix row for its 16 rotary pairs [h][e], in log2 units
   Frag bq[4];                  // the same as matrix operands
   auto pack_q = [&]() __attribute__((always_inline)) {
@@ -461,12 +468,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
       psum = ((pf[0] + pf[1]) + (pf[2] + pf[3])) + ((pf[4] + pf[5]) + (pf[6] + pf[7]));
     };
     exps();
-    // The reference maximum only has to keep probabilities bounded (2^6); it is raised, and everything accumulated so far
-    // rescaled, only when a lane's sum gets past that. Rare after the first step, so the cross-lane work sits in the branch.
-    if (__ballot(row_ok && (unset || !(psum <= kMostSum))) != 0) {
-      float mx = max_over_kgroups(fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
+    // The reference maximum only has to keep probabilities bounded; it is raised, and everything accumulated so far
+    // rescaled, only when a lane's sum gets past the bound. Rare after the first step, so the cross-lane work sits in the branch.
+    if (__ballot(row_ok && (unset || !(psum <= most_sum(kFp8)))) != 0) {
+      const float mx = max_over_kgroups(fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
                                               fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3]))));
-      if constexpr (kPack == 2) mx = fmaxf(mx, row_ror<8>(mx));  // one reference for a head's rows
       float up = unset ? mx : fmaxf(mx, 0.f);
       if (!row_ok || up == -INFINITY) up = 0.f;  // (the other terms' rows have no reference)
       sc0 -= up;
@@ -492,18 +498,19 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     if constexpr (kFp8) {
       // The page's V scale rides on the probabilities: O accumulates in units of a reference scale v_ref that is
       // at least vsc / 1.75, raised (with a rescale of O) only when a page's scale exceeds that; then
-      // p * 4 * vsc / v_ref = hi + lo, both e4m3: p <= 2^6, so the product stays below 448, the largest
+      // p * 16 * vsc / v_ref = hi + lo, both e4m3: p <= 16, so the product stays below 448, the largest
       // e4m3 value. Pages with a much smaller scale lose relative precision in proportion to how little they add.
-      const float most = kPack == 2 ? fmaxf(vs0, vs1) : vs0;
-      if (most > 1.75f * v_ref) {  // wave-uniform
-        const float f = v_ref / most;  // 0 on the first page
+      const float vsc = kPack == 2 && part ? vs1 : vs0;
+      if (__ballot(vsc > v_lim) != 0) {
+        const bool raise = vsc > v_lim;
+        const float f = __shfl(raise ? v_ref / vsc : 1.f, kPack == 2 ? 8 * (kg >> 1) : 0);  // of the accumulator's rows; 0 on the first page
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) o[nt] *= f;
-        v_ref = most;
+        v_ref = raise ? vsc : v_ref;
+        v_lim = 1.75f * v_ref;
+        v_inv = v_ref > 0.f ? __builtin_amdgcn_rcpf(v_ref) : 0.f;  // a zero scale means an all-zero page
       }
-      const float vsc = kPack == 2 && part ? vs1 : vs0;
-      // (one v_rcp_f32, good to an ulp, instead of a correctly rounded division: this runs every step)
-      const float ps = v_ref > 0.f ? kPScaleFp8 * vsc * __builtin_amdgcn_rcpf(v_ref) : 0.f;  // a zero scale means an all-zero page
+      const float ps = kPScale * (vsc * v_inv);
       uint32_t hi[2], lo[2];
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
@@ -586,7 +593,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     for (int nt = 0; nt < 8; ++nt) o[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
     sc0 = floatx4{0.f, 0.f, 0.f, 0.f};
     l_part = 0.f;
-    v_ref = 0.f;
+    v_ref = v_lim = v_inv = 0.f;
     unset = true;
     {
       const float delta = (float)(uni(seg.posq) - step_first * 32 - 32 * part);
@@ -709,25 +716,31 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     {
       const int split = whole ? piece : wk - c0 / chunk;
       const size_t row0 = ((size_t)b * a.Hq + (size_t)hk * G) * a.n_splits + split;  // + g * n_splits
-      float l_tot = sum_over_kgroups(l_part);
-      if constexpr (kPack == 2) l_tot += row_ror<8>(l_tot);
+      float l_tot = sum_over_kgroups(l_part), m = l_tot == 0.f ? -INFINITY : -sc0[0], f = 1.f;
+      if constexpr (kPack == 2) {  // rows 8 .. 15 are the same heads', relative to a maximum of their own
+        const float most = fmaxf(m, row_ror<8>(m));
+        f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - most);
+        l_tot *= f;
+        l_tot += row_ror<8>(l_tot);
+        m = most;
+      }
       if (kg == 0 && row_ok && part == 0) {
-        a.part_ml[(row0 + (size_t)head * a.n_splits) * 2] = l_tot == 0.f ? -INFINITY : -sc0[0];
+        a.part_ml[(row0 + (size_t)head * a.n_splits) * 2] = m;
         a.part_ml[(row0 + (size_t)head * a.n_splits) * 2 + 1] = l_tot;
       }
-      const float unit = kFp8 ? v_ref * (1.f / kPScaleFp8) : 1.f;
+      const float unit = kFp8 ? __shfl(v_ref, kPack == 2 ? 8 * (kg >> 1) : 0) * (1.f / kPScale) : 1.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = 4 * kg + e, g = r / kTerms;
+        const float scale = kPack == 2 ? unit * __shfl(f, r) : unit;
         float x[8];
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) {
-          x[nt] = o[nt][e];
-          if constexpr (kPack == 2) {  // rows 8 .. 15 are the same heads'
+          x[nt] = kFp8 ? o[nt][e] * scale : o[nt][e];
+          if constexpr (kPack == 2) {
             const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[nt]), __float_as_uint(x[nt]), false, false);
             x[nt] = __uint_as_float(y[0]) + __uint_as_float(y[1]);
           }
-          if constexpr (kFp8) x[nt] *= unit;
         }
         if (g < G && r % kTerms == 0 && (kPack == 1 || kg < 2)) {
           float* dst = a.part_o + (row0 + (size_t)g * a.n_splits) * kD + n16;

@@ -67,3 +67,50 @@ def test_pair_with_the_largest_remainder(mepic, oracle_attn, G, theta):
     v = float(case.pages.v.float().nan_to_num(0.0).abs().max())
     bound = (np.exp(2 * largest * (2.5e-3 + 3 * 2.0 ** -9)) - 1) * v + 2.0 ** -8 * v
     assert np.abs(got - want).max() <= bound and rel(got, want) <= 2.0 * BOUND
+
+
+def fp8_case(G, lengths, edit):
+    """fp8 pages whose real K and V [page, head, slot, dim] `edit(case, k, v)` has changed before they are stored."""
+    case = W.assemble(s := structure(G, 2, "f8e4m3", 1e6, lengths, 31), align_with_oracle(s)[0], poison=False)
+    pg = case.pages
+    k = W.unpack_k(pg.k.float()) * pg.k_scales[:, None, None, None]
+    v = W.unpack_v(pg.v.float()) * pg.v_scales[:, None, None, None]
+    edit(case, k, v)
+    for name, x, pack in (("k", k, lambda x: W.pack_k(x, "f8e4m3")), ("v", v, W.pack_v)):
+        stored, scales = W.store_round(x, "f8e4m3")
+        setattr(pg, name, pack(stored))
+        setattr(pg, name + "_scales", scales)
+    W.poison_tail(pg, case.block_tables, case.kv_lens)
+    return case
+
+
+def worst_row(got, want):
+    """Largest relative error of a row (request, query head)."""
+    return float((np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)).max())
+
+
+@pytest.mark.parametrize("G", [4, 8, 12])
+def test_a_page_keeps_its_precision_beside_one_of_a_large_scale(mepic, oracle_attn, G):
+    """Two steps of a request that go through the kernel as one: the second page's V scale is a thousand times the first's, for a value in
+    another KV head. The first page's values are all that counts in a row of this one, and they come first."""
+    def edit(case, k, v):
+        for b in range(len(case.kv_lens)):
+            v[int(case.block_tables[b, 1]), 1, 3, 0] = 4000.0
+    case = fp8_case(G, [64, 61, 40, 64], edit)
+    got, want = DeviceCase(mepic, case).run(), oracle_out(oracle_attn, case)
+    assert worst_row(got[:, :G], want[:, :G]) <= BOUND
+
+
+@pytest.mark.parametrize("G", [4, 8, 12])
+def test_a_page_keeps_its_precision_beside_one_of_large_scores(mepic, oracle_attn, G):
+    """The second step's scores lie nine log2 units above the first's, and its values are zero in half of the dims, where the first step's
+    are the whole result."""
+    def edit(case, k, v):
+        case.q[:, :, 63], case.q[:, :, 127] = 8.0, 0.0
+        k[..., 63], k[..., 127] = 0.0, 0.0
+        for b in range(len(case.kv_lens)):
+            k[int(case.block_tables[b, 1]), :, :, 63] = 9.0 / (8.0 * np.log2(np.e) / np.sqrt(128.0))
+            v[int(case.block_tables[b, 1]), :, :, :64] = 0.0
+    case = fp8_case(G, [64, 61, 40, 64], edit)
+    got, want = DeviceCase(mepic, case).run(), oracle_out(oracle_attn, case)
+    assert worst_row(got[..., :64], want[..., :64]) <= BOUND and worst_row(got, want) <= BOUND
