@@ -29,7 +29,8 @@
 //   32 .. 63) turns by x t, |x| <= 0.1 (0.35), about the middle of that span, t in [-1, 1], and e^(-i x t) = J0(x) - 2 i J1(x) T1(t) -
 //   2 J2(x) T2(t) + ... (Jacobi-Anger): with a row for each of two (three) terms, Q' times the term's coefficient, their keys
 //   go into the products as they are, and the scores of a head are the sum of its rows' weighted by T_m(t) of the slot: one multiply-add a
-//   score and term. 292 -> 176 vector instructions a step, and these keys lose no bits to a rotation.
+//   score and term. 292 -> 176 vector instructions a step, and these keys lose no bits to a rotation. Infinite keys, and scores past the
+//   largest float, have no such series (0 x Inf, Inf - Inf between the terms): a run that met any is computed again by plain_run.
 // * fp8, two steps a turn. With G <= 8 rows 0-7 belong to the turn's first step and 8-15 to its second, Q' of the latter standing 32
 //   slots on: both use the same constants, and softmax, the split of the probabilities and their scaling happen once for both.
 //   260 -> 204 vector instructions a step. Either half of the rows keeps a reference maximum and a reference V scale of its own, as two
@@ -79,6 +80,79 @@ __device__ __forceinline__ int wave_scan(int x) {
 // Slot-rotation tables: step j of a run uses table j mod n, Q' advances every n steps.
 constexpr int n_tables(bool fp8, int terms) { return fp8 || terms == 2 ? 4 : 2; }
 
+// A run of a bf16 request - slots [n_begin, n_end) below its length, n_begin a multiple of 32 - for KV head hk by plain arithmetic, one wave:
+// every key rotated at its own position. A run that met a score without a finite value is computed again by it, at the end of a wave's
+// work and in few instructions: a second way through the walker's loop cost calls of few requests 0.7 - 2 us by its length alone.
+__device__ __forceinline__ void plain_run(const AttnArgs& a, const float2* freq, int b, int hk, int n_begin, int n_end, size_t row0) {
+  const int lane = threadIdx.x & 63;
+  const uint16_t* const q = reinterpret_cast<const uint16_t*>(a.q);
+  const uint4* const k4 = reinterpret_cast<const uint4*>(a.k_pages);
+  const uint4* const v4 = reinterpret_cast<const uint4*>(a.v_pages);
+  auto turns = [&](int pos, int i) {  // of pair i
+    const float2 f = freq[((i >> 3) & 3) * 16 + (i >> 5) * 8 + (i & 7)];
+    return turns_frac((float)pos, f.x, f.y);
+  };
+  auto element = [](const Frag& x, int e) { return __uint_as_float(e & 1 ? x.w[e >> 1] & 0xffff0000u : x.w[e >> 1] << 16); };
+  auto of_lane = [](float x, int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), i)); };
+#pragma unroll 1
+  for (int g = 0; g < a.G; ++g) {
+    const size_t q_row = ((size_t)b * a.Hq + (size_t)hk * a.G + g) * kD + lane;
+    const float x0 = bf16_bits_to_f32(q[q_row]) * a.qk_scale_log2, x1 = bf16_bits_to_f32(q[q_row + 64]) * a.qk_scale_log2;
+    const float tq = turns(a.q_positions[b], lane), cq = __builtin_amdgcn_cosf(tq), sq = __builtin_amdgcn_sinf(tq);
+    const float q0 = x0 * cq - x1 * sq, q1 = x1 * cq + x0 * sq;  // of pair `lane`
+    float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;            // o: of dims lane and lane + 64
+#pragma unroll 1
+    for (int n0 = n_begin; n0 < n_end; n0 += 64) {
+      const int n = n0 + lane, last = min(n, n_end - 1);
+      const int page = safe_page(a.block_tables[(size_t)b * a.max_blocks + last / 16], a.num_pages);
+      const size_t key = ((size_t)page * a.Hkv + hk) * (2 * kD) + last % 16;
+      float sc = 0.f;
+#pragma unroll 1
+      for (int j = 0; j < 8; ++j) {  // pairs 8 j ..
+        Frag lo, hi;
+        lo.u = k4[key + 16 * j];
+        hi.u = k4[key + 16 * (8 + j)];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float t = turns(n, 8 * j + e), c = __builtin_amdgcn_cosf(t), sn = __builtin_amdgcn_sinf(t);
+          const float y0 = element(lo, e), y1 = element(hi, e);
+          sc += (y0 * c - y1 * sn) * of_lane(q0, 8 * j + e);
+          sc += (y1 * c + y0 * sn) * of_lane(q1, 8 * j + e);
+        }
+      }
+      if (n >= n_end) sc = -INFINITY;
+      const float most = fmaxf(m, wave_reduce(sc, [](float x, float y) { return fmaxf(x, y); }));
+      const float alpha = most == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - most);
+      const float p = __builtin_amdgcn_exp2f(sc - (most == -INFINITY ? 0.f : most));
+      m = most;
+      l = l * alpha + wave_reduce(p, [](float x, float y) { return x + y; });
+      o0 *= alpha;
+      o1 *= alpha;
+#pragma unroll 1
+      for (int i = 0; i < min(64, n_end - n0); i += 8) {  // eight slots of one page
+        const size_t value = ((size_t)(uint32_t)__builtin_amdgcn_readlane(page, i) * a.Hkv + hk) * (2 * kD) + 2 * lane + (i >> 3 & 1);
+        Frag lo, hi;
+        lo.u = v4[value];
+        hi.u = v4[value + 128];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const bool in = n0 + i + e < n_end;  // (slots past the end may hold anything)
+          const float w = of_lane(p, i + e);
+          o0 += w * (in ? element(lo, e) : 0.f);
+          o1 += w * (in ? element(hi, e) : 0.f);
+        }
+      }
+    }
+    const size_t part = row0 + (size_t)g * a.n_splits;
+    if (lane == 0) {
+      a.part_ml[part * 2] = l == 0.f ? -INFINITY : m;
+      a.part_ml[part * 2 + 1] = l;
+    }
+    a.part_o[part * kD + lane] = o0;
+    a.part_o[part * kD + lane + 64] = o1;
+  }
+}
+
 // kTerms: matrix rows a head has in the products with the slow half of the pairs (1: all pairs are rotated). kPack: steps a turn
 // of the loop takes together, each with matrix rows of its own for every head.
 template <bool kFp8, int kTerms, int kPack, bool kReadOnce>
@@ -107,6 +181,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   // of this lane's matrix row: which step of the turn, which head, which term
   const int part = kPack == 2 ? n16 >> 3 : 0, head = (kPack == 2 ? n16 & 7 : n16) / kTerms, term = n16 % kTerms;
   const bool row_ok = term == 0 && head < G;
+  const bool full = kTerms > 1 && G * kTerms == 16;  // every matrix row belongs to a head
 
   // ---- steps of every request. Up to 64 requests: each wave scans the lengths itself and keeps them in its lanes (lane b:
   // request b's length and the steps up to its end), so that its first page ids are on their way before the tables are built. ----
@@ -408,11 +483,21 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
       for (int u = 0; u < 2; ++u) {
         if constexpr (kFp8) x[s][u] = floatx4{0.f, 0.f, 0.f, 0.f};
         else x[s][u] = sc0;
-        if constexpr (kTerms > 1) {  // the slow half: keys as they are
-          x[s][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s][u][1].v, bq[1].v, x[s][u], 0, 0, 0);
-          x[s][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s][u][3].v, bq[3].v, x[s][u], 0, 0, 0);
-        }
       }
+    if constexpr (kTerms > 1) {
+      if (full) {  // (no row is left whose zeros would tell of an infinite key)
+        const Frag none = {make_uint4(0, 0, 0, 0)};
+#pragma unroll
+        for (int j = 1; j < 4; j += 2)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) x[0][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][u][j].v, none.v, x[0][u], 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {  // the slow half: keys as they are
+        x[0][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][u][1].v, bq[1].v, x[0][u], 0, 0, 0);
+        x[0][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][u][3].v, bq[3].v, x[0][u], 0, 0, 0);
+      }
+    }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -579,6 +664,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     __builtin_amdgcn_sched_barrier(0);
   };
   auto of_lane = [](float x, int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), i)); };
+  uint64_t again = 0;  // terms: bit i: the wave's run i is to be computed again (63: every run from there on)
+  int run = 0;
   issue_first();
   for (;;) {
     const int b = seg.b, c0 = seg.c0, n_st = seg.n_st, step_first = seg.step_first, L = seg.L;
@@ -749,7 +836,25 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
         }
       }
     }
+    if constexpr (kTerms > 1) {
+      // An infinite key, or terms past the largest float, made NaN of a probability: of its row, or of a row without a head, all
+      // of whose products are 0 x key (the sums of the lanes of such rows are looked at for nothing else).
+      if (__ballot(l_part != l_part) != 0) again |= 1ull << min(run, 63);
+      ++run;
+    }
     if (!more) break;
+  }
+  if (kTerms > 1 && again != 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the partials written above come first
+    int b = 0, pos = pos_begin;
+    for (run = 0; pos < pos_end; ++run) {
+      while (cum_at(b + 1) <= pos) ++b;
+      const int c0 = cum_at(b), end = min(pos_end, cum_at(b + 1)), L = in_lanes ? __builtin_amdgcn_readlane(len_lane, b) : sload(a.kv_lens, b);
+      if ((again >> min(run, 63)) & 1)
+        plain_run(a, freq_lds, b, hk, 32 * (pos - c0), min(L, 32 * (end - c0)),
+                  ((size_t)b * a.Hq + (size_t)hk * G) * a.n_splits + (whole ? piece : wk - c0 / chunk));
+      pos = end;
+    }
   }
 }
 

@@ -23,3 +23,22 @@ def oracle_out(attn, case: W.Case, rows=None, interleaved=False, sm_scale=0.0) -
                           v_scales=W.raw_numpy(pg.v_scales), block_positions=case.block_positions,
                           block_valid_mask=case.block_valid_mask, rows=rows, interleaved=interleaved,
                           sm_scale=sm_scale)
+
+
+def run_in_long_runs(M, case: W.Case, steps: int, flags: int = 0) -> np.ndarray:
+    """The plain decode with at least `steps` steps of 32 slots a wave, however few there are for all the waves: block tables far wider than
+    the lengths (and no closer bound on these) make for few partials a request, so for long parts of the work each."""
+    st = case.st
+    waves = max(2 * torch.cuda.get_device_properties(0).multi_processor_count // st.Hkv, 1) * 4
+    pieces = min(4 * -(-waves // st.B), waves)
+    width = pieces * steps * 32 // st.P
+    assert width >= case.block_tables.shape[1]
+    case.block_tables = np.pad(case.block_tables, ((0, 0), (0, width - case.block_tables.shape[1])))
+    dc = DeviceCase(M, case, flags=flags)
+    dc.params.max_kv_len = 0
+    size = M.attn_workspace_size(dc.params, False)
+    dc.ws = torch.empty(size, dtype=torch.uint8, device=dc.q.device)
+    dc.params.workspace, dc.params.workspace_bytes = dc.ws.data_ptr(), size
+    most = (size - 4 * (st.B + 2)) // (4 * st.B * st.Hq * (st.D + 2))  # partials a request: its parts and one for where they begin
+    assert (most - 1) * steps <= pieces * steps, "the library means to cut the work finer"
+    return dc.run()

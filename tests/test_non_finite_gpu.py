@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads as W
-from harness import DeviceCase, align_with_oracle, oracle_out
+from harness import DeviceCase, align_with_oracle, oracle_out, run_in_long_runs
 
 pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-4, "bf16": 2e-2, "f8e4m3": 2e-2}
@@ -95,3 +95,60 @@ def test_values_near_the_largest_float(mepic, oracle_attn, kv_dtype, prefill, ri
     big = np.arange(128) == 100
     assert np.abs(got[:, :, big] / want[:, :, big] - 1.0).max() <= 2.0 ** -7
     assert np.abs(got[:, :, ~big] - want[:, :, ~big]).max() <= TOL[kv_dtype]
+
+
+def plain_case(kv_dtype, P, lengths, G, theta):
+    st = structure(kv_dtype, P, False, lengths)
+    st.Hq, st.theta = G * st.Hkv, theta
+    return W.assemble(st, align_with_oracle(st)[0])
+
+
+@pytest.mark.parametrize("value", [float("inf"), -float("inf")])
+@pytest.mark.parametrize("dim", [63, 126])
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("G,theta", [(4, 5e5), (8, 5e5), (3, 1e4), (5, 1e4), (6, 1e4), (8, 1.5e5)])
+def test_an_infinite_key(mepic, oracle_attn, G, theta, general, dim, value):
+    """bf16 keys, an Inf in the pair of dims that hardly turns: whether a row is NaN or the key has no weight in it depends on the signs
+    of its rotated query alone, wherever the rotation is taken from (but at multiples of the tables' span a sine is 0, and 0 x Inf)."""
+    case = plain_case("bf16", 16, [700, 90, 300], G, theta)
+    for b, n in ((0, 100), (0, 333), (1, 40), (0, 5)):
+        set_k(case.pages, int(case.block_tables[b, n // 16]), n % 16, dim, value)
+    got, want = run(mepic, case, general, False), oracle_out(oracle_attn, case)
+    hit = np.isnan(want)
+    assert hit.any() and not hit[:2].all() and (np.isnan(got) == hit).all()
+    assert np.abs(got[~hit] - want[~hit]).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("dim", [32, 40, 63])
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("G,theta", [(4, 5e5), (8, 5e5), (4, 1e4), (5, 1e4), (6, 1e4)])
+def test_scores_below_the_lowest_float(mepic, oracle_attn, G, theta, general, dim):
+    """bf16 keys: products of finite numbers that pass -2^128. Such a key has no weight."""
+    case = plain_case("bf16", 16, [700, 90], G, theta)
+    case.q[:, :, dim], case.q[:, :, dim + 64] = 1e20, 0.0
+    case.pages.k.view(torch.int16)[:, :, dim // 8, :, dim % 8] = 0
+    case.pages.k.view(torch.int16)[:, :, (dim + 64) // 8, :, dim % 8] = 0
+    for b, n in ((0, 600), (0, 699), (0, 650), (1, 80), (1, 70)):
+        set_k(case.pages, int(case.block_tables[b, n // 16]), n % 16, dim, -1e21)
+    got, want = run(mepic, case, general, False), oracle_out(oracle_attn, case)
+    assert np.isfinite(want).all() and np.abs(got - want).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("G,theta", [(4, 5e5), (8, 5e5), (5, 1e4)])
+@pytest.mark.parametrize("B", [7, 70])
+def test_infinite_keys_in_some_runs_of_a_wave(mepic, oracle_attn, G, theta, B):
+    """Requests in one long run each (7), or parts of the work that go through several requests and cut some (70): what has an infinite key is
+    computed again, with a result as before, and the requests around it are not touched."""
+    lengths = [(173 * b) % 331 + 1 + (600 if b % 5 == 3 else 0) for b in range(B)]
+    case = plain_case("bf16", 16, lengths, G, theta)
+    clean = run_in_long_runs(mepic, plain_case("bf16", 16, lengths, G, theta), 45)
+    some = [b for b in range(B) if b % 3 == 1]
+    for b in some:
+        n = lengths[b] - 1 - (lengths[b] % 128 == 1)
+        set_k(case.pages, int(case.block_tables[b, n // 16]), n % 16, 63, float("inf"))
+    want = oracle_out(oracle_attn, case)
+    got = run_in_long_runs(mepic, case, 45)
+    hit, others = np.isnan(want), np.setdiff1d(np.arange(B), some)
+    assert hit[some].any() and not hit[some].all() and (np.isnan(got) == hit).all()
+    assert np.abs(got[~hit] - want[~hit]).max() <= TOL["bf16"]
+    assert np.array_equal(got[others], clean[others])
