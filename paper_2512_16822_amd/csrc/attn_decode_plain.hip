@@ -241,14 +241,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   int upto = 0, piece = 0;     // whole: lane b: pieces of the requests up to b; the wave's piece of its request
   auto cut = [&]() __attribute__((always_inline)) {  // this wave's part of the sequence
     const int T = cum_at(a.B);
-    chunk = uni(max((T + n_k - 1) / n_k, a.blocks_per_split));  // blocks_per_split carries the minimum chunk
+    // (blocks_per_split carries the minimum chunk, of lengths up to what the caller calls their bound; past T it makes no difference)
+    chunk = uni(max(max((T + n_k - 1) / n_k, min(a.blocks_per_split, T)), 1));
     // Where a wave's part runs from one request into the next, it pays for a second start (page ids, Q') and a second partial:
     // some 2 - 3 us. So requests are cut into equal pieces of their own, one a wave, if there are waves enough for pieces at most a step (turn)
     // and a sixteenth longer than parts of the sequence would be. us a call without and with: 60 requests of up to 407 e4m3 slots 18.6 -> 15.8, 19
     // of up to 4 K 25.2 -> 20.8; 64 of 4.3 K bf16 74.5 -> 71.2, 56 of up to 2.9 K 43.5 -> 41.3; the worst of fifty mixes lost 3 %.
     if (in_lanes && a.B > 1 && chunk + kPack > 2 && T < 1 << 20) {
       const int steps = steps_of(len_lane);
-      auto pieces_of = [](int n, int c) __attribute__((always_inline)) {  // n / c rounded up (exact: n + c < 2^21)
+      auto pieces_of = [](int n, int c) __attribute__((always_inline)) {  // n / c rounded up (exact: n <= T < 2^20, c < 1.1 T)
         return (int)(((float)(n + c) - 0.5f) * __builtin_amdgcn_rcpf((float)c));
       };
       const int c0 = (chunk + kPack - 1) / kPack * kPack, by = kPack * (1 + chunk / 64), most = c0 + kPack + chunk / 16;
