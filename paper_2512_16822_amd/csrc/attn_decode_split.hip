@@ -207,9 +207,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   if constexpr (kTerms) {
     if (my_slow) {
       const float x = kMiddle * 6.283185307f * my_hi, h = 0.5f * x, y = h * h;  // Bessel functions of x, as far as x <= 0.2 has use for
-      const float j0 = 1.f - y * (1.f - 0.25f * y), j1 = h * (1.f - y * (0.5f - y * (1.f / 12.f)));
-      const float j2 = 0.5f * y * (1.f - y * (1.f / 3.f)), j3 = h * y * (1.f / 6.f) * (1.f - 0.25f * y);
-      my_f1 = my_f0 * (2.f * j1 + 6.f * j3);
+      const float j0 = 1.f - y * (1.f - 0.25f * y), j2 = 0.5f * y * (1.f - y * (1.f / 3.f));
+      // (J1 and J3 in units of h, which is 0 for pairs that do not turn at all: rope_theta infinite)
+      const float j1 = 1.f - y * (0.5f - y * (1.f / 12.f)), j3 = y * (1.f / 6.f) * (1.f - 0.25f * y);
+      my_f1 = my_f0 * h * (2.f * j1 + 6.f * j3);
       my_f0 *= j0 + 2.f * j2;
       if (wave == 0) {
         ratio[0][my_pair - 32] = -4.f * j2 / (j0 + 2.f * j2);

@@ -67,9 +67,9 @@ def check_bound(mepic, oracle_attn, case):
 
 
 @pytest.mark.parametrize("kv_dtype,P", [("bf16", 16), ("bf16", 32), ("f8e4m3", 32)])
-@pytest.mark.parametrize("G,theta", [(4, 4.07e5), (4, 1.01e5), (8, 4.07e5), (1, 1.01e5), (9, 4.07e5), (4, 9.9e4)])
+@pytest.mark.parametrize("G,theta", [(4, 4.07e5), (4, 1.01e5), (8, 4.07e5), (1, 1.01e5), (9, 4.07e5), (4, 9.9e4), (4, float("inf"))])
 def test_error_where_terms_take_the_place_of_rotations(mepic, oracle_attn, kv_dtype, P, G, theta):
-    """Decode, at the slowest rope_theta of either table span (the last two: rotations): everything in the pair that the terms left out
+    """Decode, at the slowest rope_theta of either table span (9 heads a KV head and 9.9e4: rotations; infinite: only the first pair turns): everything in the pair that the terms left out
     concern most. They add 2 J4(0.2) = 2^-16.9 of a score: with the 2^-15.7 above still below 2^-15."""
     case = large_case(kv_dtype, P, False, 4.0, theta, G)
     other = ~np.isin(np.arange(128), (32, 96))
