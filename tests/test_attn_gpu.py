@@ -351,7 +351,8 @@ def test_prefill_queries_in_the_middle_and_far_positions(mepic, oracle_attn):
 def test_fp8_page_scales_spread_over_four_decades(mepic, oracle_attn, order):
     """Per-page V (and K) scales that differ by up to 10^4 between the pages of one request, in random, rising and
     falling order along the request: the matrix-core kernel keeps its output accumulator in units of a reference
-    V scale that it raises on the way, which this exercises; the stored value of a slot is code * scale either way."""
+    V scale; the stored value of a slot is code * scale either way. (Waves have a step or two each here; the reference is
+    raised along runs of many in test_decode_plain_gpu.py.)"""
     st = W.decode_structure("fp8_scale_spread", 13, B=6, Hq=28, Hkv=4, D=128, P=32, theta=1e6, q_dtype="bf16",
                             kv_dtype="f8e4m3", prefix=40, n_chunks=(2, 6), chunk_tokens=512, pool=5, question=70)
     case = build_case(mepic, st)

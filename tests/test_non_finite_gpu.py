@@ -152,3 +152,32 @@ def test_infinite_keys_in_some_runs_of_a_wave(mepic, oracle_attn, G, theta, B):
     assert hit[some].any() and not hit[some].all() and (np.isnan(got) == hit).all()
     assert np.abs(got[~hit] - want[~hit]).max() <= TOL["bf16"]
     assert np.array_equal(got[others], clean[others])
+
+
+@pytest.mark.parametrize("nothing", [1, 32, 64, 96, 320])
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("kv_dtype,P,G,theta", [("bf16", 16, 4, 5e5), ("bf16", 16, 8, 5e5), ("bf16", 16, 5, 1e4), ("bf16", 16, 9, 5e5),
+                                               ("f8e4m3", 32, 4, 5e5), ("f8e4m3", 32, 9, 5e5)])
+def test_no_weight_before_the_first_finite_score(mepic, oracle_attn, kv_dtype, P, G, theta, general, nothing):
+    """All scores of a request's first slots (fp8: pages) are -Inf, in part of a turn, a whole one or several: the reference maximum is that of the
+    first score that is not."""
+    lengths = [700, 90, 333]
+    case = plain_case(kv_dtype, P, lengths, G, theta)
+    X = case.pages.k.shape[-1]
+    if kv_dtype == "f8e4m3":
+        case.q[:] = 0.0
+    case.q[:, :, 63], case.q[:, :, 127] = 8.0 if kv_dtype == "f8e4m3" else 1e20, 0.0
+    raw = case.pages.k.view(torch.uint8 if kv_dtype == "f8e4m3" else torch.int16)
+    raw[:, :, 63 // X, :, 63 % X] = raw[:, :, 127 // X, :, 127 % X] = 0
+    for b, n in enumerate(lengths):
+        for slot in range(min(nothing, n - 5)):
+            page = int(case.block_tables[b, slot // P])
+            if kv_dtype != "f8e4m3":
+                set_k(case.pages, page, slot % P, 63, -1e21)
+            elif (slot // P + 1) * P <= min(nothing, n - 5):
+                raw[page, :, 63 // X, slot % P, 63 % X] = 0xF0
+                case.pages.k_scales[page] = 1e37
+    want = oracle_out(oracle_attn, case)
+    assert np.isfinite(want).all()
+    for got in [run(mepic, case, general, False)] + ([] if general else [run_in_long_runs(mepic, case, 22)]):
+        assert np.abs(got - want).max() <= TOL[kv_dtype]
