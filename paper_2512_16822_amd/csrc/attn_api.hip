@@ -65,13 +65,12 @@ int general_splits(const mepic_attn_params* p, int n_blocks) {
 
 // The splits the general path's decode kernels use, at most that many: one round of the `resident` workgroups that run at a
 // time, one or two a compute unit (each builds a rotation table first, and partials cost a merge), but none where the context is so short that
-// the merge's launch, about four turns of 128 slots, costs more than the turns it saves. Measured (us): 64 requests of 4 K bf16
-// slots, D 128, 8 KV heads: 187 with 512 workgroups, 194 with 1024, 202 with 2048; lengths mixed 1:32 270, 278, 255; 8 such
-// requests 39 with 512, 51 with 2048; 40 mixed requests, 12 heads: 202 with 960, 246 with 480; one fp32 request of 289
-// slots 9.0 without a second split, 11.1 with.
+// the merge's launch, about four turns of 128 slots, costs more than the turns it saves. Measured (us, bf16, D 128, no page shared) with
+// 512 workgroups, 1024, 2048: 64 requests of 4 K slots, 8 KV heads 185, 191, 197; 8 such requests 34, 38, 38; 20 of 0.5 - 3 K 38, 41, 47; 64 of 4 K
+// e4m3 slots, 4 heads 65, 70, 85; one fp32 request of 289 slots 9.0 without a second split, 11.1 with.
 // The cuts are the same for every request, and with as many (query token, KV head) pairs as workgroups run at a time there is one
-// split: then the longest request sets the time, however short the others are (the 255 against 270 us of the mixed lengths above;
-// one of 32 K slots among 64 of 1 K is walked by one workgroup a head).
+// split: then the longest request sets the time, however short the others are. What that costs, for the same counts: 64 requests of 256 - 8 K
+// slots 172, 142, 143; one of 32 K among 63 of 1 K 368, 223, 199; 40 of 1 - 16 K on 12 heads (960 workgroups, 1920, 2048) 322, 305, 297.
 void cut_kv(const mepic_attn_params* p, int n_blocks, int resident, Plan* pl) {
   const long rows = (long)p->n_q_tokens * p->Hkv;
   const int turn_blocks = 128 / p->P, turns = (n_blocks + turn_blocks - 1) / turn_blocks;
@@ -145,11 +144,13 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
   const long n_rows = (long)p->n_q_tokens * G;
   if (prefill && p->kv_dtype != MEPIC_F32 && p->n_q_tokens >= 3L * p->B && n_rows >= 5L * p->B && !no_pieces) {
     // A workgroup per 256 query rows: its cost hardly depends on how many of them there are, while the decode kernel takes
-    // every token (with all its heads) for itself. us with either for 1, 2, 3, 4, 5 tokens a request, whatever the group size:
-    // 8 requests of 16 K bf16 slots on 8 KV heads 191 against 101, 125, 207, 202, 284; 32 of 4 K on 4 heads, 7 query heads
-    // each: 110 against 46, 81, 90, 98, 140; 1 of 4 K on 8 heads: 20 against 13, 13, 16, 17, 20. One or two tokens are the
-    // decode kernel's in every call measured (1.2 to 2.7 times). Three and four are a matter of size (0.8 to 1.9 times); calls of
-    // one query head a KV head, where short questions are short calls, leave them to the decode kernel.
+    // every token (with all its heads) for itself. us with the former and with the latter for 2, 3, 4, 5, 6 tokens a request:
+    // 8 requests of 16 K bf16 slots, 8 KV heads, 4 query heads each: 185 against 116, 185, 169, 224, 231; 32 of 4 K, 4 heads, 7 each:
+    // 104 against 90, 92, 99, 126, 134; 1 of 4 K, 8 heads: 24 against 14, 16, 17, 18, 24. One and two tokens are the decode kernel's.
+    // Three and four are a matter of size: of 144 calls on 1 to 8 KV heads the decode kernel has most (1.4 and 1.3 times in the mean, 2.2 at
+    // 400 slots), but the long ones on few heads it loses by as much as that (48 requests of 9 K, 2 heads, 3 tokens 165 against 220, 4 tokens
+    // 165 against 300), and the line keeps these. Calls of one query head a KV head, where short questions are short calls, leave three
+    // and four to the decode kernel.
     int kv_tiles, min_run, max_pieces;
     prefill_split_plan(p->B, p->Hkv, n_rows, max_kv, &kv_tiles, &min_run, &max_pieces);
     if (max_pieces > 0) {
