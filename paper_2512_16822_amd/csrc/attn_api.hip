@@ -35,7 +35,7 @@ int scratch_of_current_device(void** out) {
 
 thread_local const char* g_last_kernel = "";
 
-enum Kernel { K_DECODE_MFMA_BF16, K_DECODE_MFMA_F8, K_PREFILL_MFMA_BF16, K_PREFILL_SPLIT, K_DECODE_SPLIT, K_DECODE_F32 };
+enum Kernel { K_DECODE_PLAIN_BF16, K_DECODE_PLAIN_F8, K_PREFILL_MFMA_BF16, K_PREFILL_SPLIT, K_DECODE_SPLIT, K_DECODE_F32 };
 
 struct Plan {
   Kernel kernel;
@@ -111,11 +111,11 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
 
   const bool mfma_bf16 = p->q_dtype == MEPIC_BF16 && p->kv_dtype == MEPIC_BF16 && p->D == 128 && p->P == 16;
   const bool mfma_fp8 = p->q_dtype == MEPIC_BF16 && p->kv_dtype == MEPIC_F8E4M3 && p->D == 128 && p->P == 32;
-  if (!prefill && plain && G <= 16 && (mfma_bf16 || mfma_fp8) && p->B <= decode_mfma_max_requests()) {
+  if (!prefill && plain && G <= 16 && (mfma_bf16 || mfma_fp8) && p->B <= decode_plain_max_requests()) {
     // Matrix-core decode: persistent waves cut each KV head's sequence of steps into equal chunks; here only
     // the bound on partials per request (sizes the workspace) and the minimum chunk are fixed.
-    pl.kernel = mfma_fp8 ? K_DECODE_MFMA_F8 : K_DECODE_MFMA_BF16;
-    decode_mfma_plan(p->B, p->Hkv, max_kv, &pl.n_splits, &pl.blocks_per_split);
+    pl.kernel = mfma_fp8 ? K_DECODE_PLAIN_F8 : K_DECODE_PLAIN_BF16;
+    decode_plain_plan(p->B, p->Hkv, max_kv, &pl.n_splits, &pl.blocks_per_split);
     pl.workspace_bytes = (size_t)p->n_q_tokens * p->Hq * pl.n_splits * (p->D + 2) * sizeof(float) +
                          (size_t)(p->B + 2) * sizeof(int32_t);
     pl.min_workspace_bytes = pl.workspace_bytes;
@@ -221,9 +221,9 @@ int run(const mepic_attn_params* p, void* hip_stream, bool prefill) {
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   hipError_t e = hipSuccess;
   switch (pl.kernel) {
-    case K_DECODE_MFMA_BF16:
-    case K_DECODE_MFMA_F8:
-      g_last_kernel = pl.kernel == K_DECODE_MFMA_F8 ? "decode_mfma_fp8" : "decode_mfma_bf16";
+    case K_DECODE_PLAIN_BF16:
+    case K_DECODE_PLAIN_F8:
+      g_last_kernel = pl.kernel == K_DECODE_PLAIN_F8 ? "decode_mfma_fp8" : "decode_mfma_bf16";
       e = launch_decode_plain(a, s);
       break;
     case K_PREFILL_MFMA_BF16:
@@ -261,7 +261,7 @@ int run_batched(const mepic_attn_params* p, const int32_t* plan, const mepic_dec
     return MEPIC_ERR_INVALID;
   if ((size_t)(info->n_runs + 1) * sizeof(int) > 48 * 1024) return MEPIC_ERR_UNSUPPORTED;  // run prefix sums live in LDS
   // the plan cut the work for the waves of the device it was built on
-  if (info->n_waves != decode_mfma_waves_per_head(p->Hkv)) return MEPIC_ERR_INVALID;
+  if (info->n_waves != decode_batched_waves_per_head(p->Hkv)) return MEPIC_ERR_INVALID;
   const size_t need = (size_t)p->n_q_tokens * p->Hq * info->n_splits * (p->D + 2) * sizeof(float);
   if (bytes_only) {
     *bytes_only = need;
@@ -293,7 +293,7 @@ int run_batched(const mepic_attn_params* p, const int32_t* plan, const mepic_dec
   a.part_o = ws;
   a.part_ml = ws + (size_t)a.n_q * a.Hq * a.n_splits * a.D;
   g_last_kernel = mfma_fp8 ? "decode_mfma_fp8_batched" : "decode_mfma_bf16_batched";
-  const hipError_t e = launch_decode_mfma_batched(a, info->n_runs, reinterpret_cast<hipStream_t>(hip_stream));
+  const hipError_t e = launch_decode_batched(a, info->n_runs, reinterpret_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? MEPIC_OK : MEPIC_ERR_LAUNCH;
 }
 

@@ -46,6 +46,7 @@ constexpr int kWaves = 4;             // waves per workgroup
 // the Llama-3-8B decode workload, 64 requests of 4.3 K slots.)
 constexpr int kWgPerCu = 2;
 constexpr float kRescaleSlack = 6.f;  // the running maximum may lag the true one by this much (log2 units)
+constexpr float kPScaleFp8 = 4.f;     // probabilities (at most 2^6) are multiplied by this before the e4m3 split
 
 template <bool kFp8>
 __global__ __launch_bounds__(64 * kWaves, kWgPerCu) void decode_batched_kernel(const AttnArgs a) {
@@ -542,7 +543,7 @@ __global__ __launch_bounds__(kThreads) void combine_batched_kernel(const AttnArg
 
 }  // namespace
 
-hipError_t launch_decode_mfma_batched(const AttnArgs& a, int n_runs, hipStream_t s) {
+hipError_t launch_decode_batched(const AttnArgs& a, int n_runs, hipStream_t s) {
   const bool fp8 = a.kv_dtype == MEPIC_F8E4M3;
   const int n_wg = max(kWgPerCu * device_compute_units() / a.Hkv, 1) * a.Hkv;
   const size_t lds = (size_t)(n_runs + 1) * sizeof(int);
@@ -572,7 +573,7 @@ hipError_t launch_decode_mfma_batched(const AttnArgs& a, int n_runs, hipStream_t
   return hipGetLastError();
 }
 
-int decode_mfma_waves_per_head(int Hkv) {  // the planner cuts the sequence for them
+int decode_batched_waves_per_head(int Hkv) {  // the planner cuts the sequence for them
   return max(kWgPerCu * device_compute_units() / Hkv, 1) * kWaves;
 }
 

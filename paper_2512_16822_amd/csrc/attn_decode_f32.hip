@@ -23,7 +23,6 @@
 namespace mepic {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
 constexpr int kTab = 128;             // slots the rotation table covers
@@ -49,7 +48,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
   __shared__ float4 q_lds[kGr][64];             // un-rotated q, granule j of every lane's head
   __shared__ __align__(16) float2 freq[D / 2];  // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = uni_i(tid >> 6), n16 = lane & 15, kg = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), n16 = lane & 15, kg = lane >> 4;
   if (tid < D / 2) freq[tid] = make_float2(a.freq_hi[tid], a.freq_lo[tid]);
   const int G = a.G, Hkv = a.Hkv;
   const int hk = (int)(blockIdx.x % (unsigned)Hkv), split = (int)blockIdx.z;
@@ -67,9 +66,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
       b += max(n - 1, 0) * step;
       hi = min(b + step, hi);
     }
-    b = uni_i(b);
+    b = uni(b);
   }
-  const int L = uni_i(a.kv_lens[b]), pos_q = uni_i(a.q_positions[t]);
+  const int L = uni(a.kv_lens[b]), pos_q = uni(a.q_positions[t]);
   const int n_begin = split * a.blocks_per_split * P;
   const int s_end = min(L, (split + 1) * a.blocks_per_split * P);
   int n_end = s_end;

@@ -29,7 +29,7 @@
 //   32 .. 63) turns by x t, |x| <= 0.1 (0.35), about the middle of that span, t in [-1, 1], and e^(-i x t) = J0(x) - 2 i J1(x) T1(t) -
 //   2 J2(x) T2(t) + ... (Jacobi-Anger): with a row for each of two (three) terms, Q' times the term's coefficient, their keys
 //   go into the products as they are, and the scores of a head are the sum of its rows' weighted by T_m(t) of the slot: one multiply-add a
-//   score and term. 292 -> 176 vector instructions a step, and these keys lose no bits to a rotation. Infinite keys, and scores past the
+//   score and term. 292 -> 183 vector instructions a step (start-up and run ends counted in), and these keys lose no bits to a rotation. Infinite keys, and scores past the
 //   largest float, have no such series (0 x Inf, Inf - Inf between the terms): a run that met any is computed again by plain_run.
 // * fp8, two steps a turn. With G <= 8 rows 0-7 belong to the turn's first step and 8-15 to its second, Q' of the latter standing 32
 //   slots on: both use the same constants, and softmax, the split of the probabilities and their scaling happen once for both.
@@ -39,10 +39,10 @@
 // into two e4m3 terms (p*16 = hi + lo, 8 significant bits together down to p = 2^-7); the page's V scale rides on the probabilities, O
 // being kept in units of a reference scale that is raised (with a rescale of O) only when a page's scale exceeds it by 1.75 x.
 //
-// What bounds it. Where pages are read once, HBM: 8 requests of 65 537 bf16 slots with the read-once hint 319 us = 6.7 TB/s (two requests' worth
+// What bounds it. Where pages are read once, HBM: 8 requests of 65 537 bf16 slots with the read-once hint 320 us = 6.7 TB/s (two requests' worth
 // of waves side by side on a unit: 332). Where requests share pages, what misses L2: 64 requests of 4.3 K slots ask L1 for 1.13 GB (33 us at a
 // line a two clocks on every unit), of which 0.36 GB miss L2, and those come at 6 - 7 TB/s whether from HBM or the Infinity Cache:
-// 81.5 -> 71.2 us a call (47 with every page in L2); 128 requests of 2 - 33 K fp8 slots 212 -> 180 us. Measured and of no use there: requesting two or
+// 81.5 -> 71.2 us a call (47 with every page in L2); 128 requests of 2 - 33 K fp8 slots 212 -> 184 us. Measured and of no use there: requesting two or
 // three steps ahead by touching a word of every line (the lines are gone from the 32 KB of L1 again: 102 - 112 us), the
 // non-temporal hint for pages of few readers (misses 0.36 -> 0.30 GB, but those then always come from HBM: 78 - 94 us).
 #include "decode_common.h"
@@ -59,12 +59,6 @@ constexpr int kWaves = 8;
 // 1.78e-3, 8 under 32 1.75e-3, 16 under 16 1.745e-3 (the result's own rounding 1.66e-3), all at the same time a call.
 __host__ __device__ constexpr float most_sum(bool fp8) { return fp8 ? 16.f : 64.f; }
 constexpr float kPScale = 256.f / most_sum(true);
-
-// The value of the lane kBy places up in the row of 16 lanes (0 past its end).
-template <int kBy>
-__device__ __forceinline__ float lane_up(float x) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x100 + kBy, 0xf, 0xf, true));
-}
 
 // Inclusive prefix sum over the wave.
 __device__ __forceinline__ int wave_scan(int x) {
@@ -939,7 +933,7 @@ hipError_t launch_decode_plain(const AttnArgs& a, hipStream_t s) {
 
 // Requests one plain decode call can take: the per-request step counts (B + 1 ints of dynamic LDS) must fit beside the
 // kernel's static tables in the 64 KB a workgroup gets without asking for more.
-int decode_mfma_max_requests() { return (64 * 1024 - 44 * 1024) / (int)sizeof(int) - 1; }
+int decode_plain_max_requests() { return (64 * 1024 - 44 * 1024) / (int)sizeof(int) - 1; }
 
 int device_compute_units() { return compute_units(); }
 
@@ -950,9 +944,10 @@ hipError_t launch_dot_rotate_selftest(const uint32_t* words, float* out, int n, 
 
 // Upper bound on the partials per request and the matching minimum chunk (in steps of 32 slots), from
 // host-known sizes only: with W waves per KV head and B requests a request needs about W/B pieces for an even
-// cut; allow four times that for skewed length mixes, never more than W. (W as two workgroups of four waves a compute unit would
-// have it: it sizes the workspace. The kernel's own waves may be a few fewer or more; it keeps to the minimum chunk.)
-void decode_mfma_plan(int B, int Hkv, int max_kv_len, int* max_splits, int* min_chunk) {
+// cut; allow four times that for skewed length mixes, never more than W. (W counts half compute units of four waves, so that for head
+// counts that do not divide the units it is a few more or fewer than the kernel's waves. It sets the size of the workspace, which callers have
+// laid out; the kernel keeps to the minimum chunk, and so to the partials there is room for.)
+void decode_plain_plan(int B, int Hkv, int max_kv_len, int* max_splits, int* min_chunk) {
   const int W = max(2 * compute_units() / Hkv, 1) * 4;
   const int max_steps = max((max_kv_len + 31) / 32, 1);
   int pieces = 4 * ((W + max(B, 1) - 1) / max(B, 1));

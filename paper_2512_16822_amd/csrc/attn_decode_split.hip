@@ -6,9 +6,9 @@
 // slots (two groups of 16, each inside one page) for all G <= 16 heads of the group and the waves' partials are merged
 // through LDS. Operands come straight from the pages, as in attn_decode_plain.hip:
 //   S^T[16 slots x 16 heads] per group = Khat x Q'^T, three v_mfma_f32_16x16x32_bf16 per 32 dims
-//   O  [16 heads x D]       += P x V, two per 16 dims of the output: the k index of the product runs over slots 4 kg ..
-//        4 kg + 3 of the first and of the second group, which is what a lane's score registers hold.
-// Probabilities change lanes by one swap instruction a register, so that V comes in pieces of eight slots of a row.
+//   O  [16 heads x D]       += P x V, two per 16 dims of the output: a lane's k index runs over eight consecutive slots of one group,
+//        8 (kg / 2) .. of group kg % 2, so that V comes in pieces of eight slots of a row. A lane's scores are those of slots 4 kg .. 4 kg + 3
+//        of either group; one swap instruction a register between neighbouring k-groups brings their probabilities there.
 // Rotation without a sine per key: q^.k^ = (R(pos_q - base) q).(R(pos_k - base) k). R(s), s in [0, kTab), is a table in LDS
 // (fp32); base is the position of some earlier group, moved - and Q' computed afresh - when a group starts outside
 // [base, base + kTab - 16]: every fourth (eighth) step along a run of consecutive positions, and wherever block positions jump (a step
@@ -19,12 +19,12 @@
 // of Q', each as head and remainder, meet the keys as stored, exact in bf16, and the scores are their sum by powers of t.
 //
 // 64 requests of 4.3 K bf16 slots with valid masks and block positions, 32 heads on 8: 382 us (scalar) -> 110 us a call
-// (loads with scalar bases in a fixed order, one round of workgroups) -> 84 us (terms, with half the set-ups; eight-slot pieces of V; 636 -> 425
-// vector instructions a step). e4m3: 35 requests of up to 1.6 K slots 41 -> 28 us. Where no page is shared, HBM: 30 requests of up to 20 K bf16 slots
+// (loads with scalar bases in a fixed order, one round of workgroups) -> 84 us (terms, with half the set-ups; eight-slot pieces of V; 636 -> 431
+// vector instructions a step, start-up and merge counted in; 84 - 87 us from card to card). e4m3: 35 requests of up to 1.6 K slots 41 -> 28 us. Where no page is shared, HBM: 30 requests of up to 20 K bf16 slots
 // on 12 heads 295 -> 222 us.
 //
 // A NaN or Inf in the merged result sends the workgroup through the scalar body: operand splits make NaN of some infinities, and
-// probabilities of up to 2^kRescaleSlack times values near the largest float make Inf of finite ones.
+// probabilities of up to kMostSum times values near the largest float make Inf of finite ones.
 #include <type_traits>
 
 #include "attn_scalar.h"
@@ -33,14 +33,13 @@
 namespace mepic {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr float kMostSum = 64.f;      // a lane's probabilities of a step above which the reference maximum is raised
 
 // Keep the stored elements whose bit of `keep` (8 bits) is set, zero the others.
 __device__ __forceinline__ void mask_raw8(Raw8<false>& x, uint32_t keep) {
-  SplitFrag f;
+  Frag f;
   f.u = x.r;
   mask8(f, keep);
   x.r = f.u;
@@ -51,11 +50,6 @@ __device__ __forceinline__ void mask_raw8(Raw8<true>& x, uint32_t keep) {
     x.r.x &= (keep >> e) & 1u ? ~0u : ~(0xffu << (8 * e));
     x.r.y &= (keep >> (4 + e)) & 1u ? ~0u : ~(0xffu << (8 * e));
   }
-}
-
-// The value of the next lane up in the row of 16 lanes (0 past its end).
-__device__ __forceinline__ float next_lane(float x) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x101, 0xf, 0xf, true));
 }
 
 template <int D>
@@ -86,7 +80,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   __shared__ float2 turn[kShare ? kWaves : 1][4][kRows][16];  // what Q' set-up shares: [wave][kg][row][pair] {cos, sin} times the row's factor
   __shared__ __align__(16) float ratio[2][32];   // [row][pair of the slow half]: the second set in units of the first
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = uni_i(tid >> 6), n16 = lane & 15, kg = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), n16 = lane & 15, kg = lane >> 4;
   if (tid < D / 2) freq[tid] = make_float2(a.freq_hi[tid], a.freq_lo[tid]);
   const int G = a.G, Hkv = a.Hkv;
   const int head = n16 / kRows, term = n16 % kRows;  // of this lane's matrix row
@@ -109,9 +103,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       b += max(n - 1, 0) * step;
       hi = min(b + step, hi);
     }
-    b = uni_i(b);
+    b = uni(b);
   }
-  const int L = uni_i(a.kv_lens[b]), pos_q = uni_i(a.q_positions[t]);
+  const int L = uni(a.kv_lens[b]), pos_q = uni(a.q_positions[t]);
   const int n_begin = split * a.blocks_per_split * P;
   const int s_end = min(L, (split + 1) * a.blocks_per_split * P);
   int n_end = s_end;
@@ -228,7 +222,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   __syncthreads();
 
   // Q' as the B operands. kTerms: qh / ql hold the first set of the slow half (pairs of granules 1 and 3), qh2 / ql2 the second.
-  SplitFrag qh[kKs], ql[kKs], qh2[2], ql2[2];
+  Frag qh[kKs], ql[kKs], qh2[2], ql2[2];
   auto rotate_q = [&](int base) __attribute__((always_inline)) {
     const float delta = (float)(pos_q - base);
     if constexpr (kShare) {
@@ -254,7 +248,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     };
 #pragma unroll
     for (int j = 0; j < (kIL ? kKs : kKs / 2); ++j) {
-      SplitFrag qa, qb;
+      Frag qa, qb;
       qa.u = q_lds[j][lane + again];
       if constexpr (!kIL) qb.u = q_lds[j + kKs / 2][lane + again];
 #pragma unroll
@@ -287,7 +281,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     if constexpr (kFp8) sc = floatx4{0.f, 0.f, 0.f, 0.f};
     else sc = sc0;
     const float4* tp = &tab[0][min(max(s0, 0), kTab - 16) + n16];
-    auto three = [&](const SplitFrag& kh, const SplitFrag& kl, int j) __attribute__((always_inline)) {
+    auto three = [&](const Frag& kh, const Frag& kl, int j) __attribute__((always_inline)) {
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh.v, qh[j].v, sc, 0, 0, 0);
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh.v, ql[j].v, sc, 0, 0, 0);
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl.v, qh[j].v, sc, 0, 0, 0);
@@ -297,7 +291,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       if constexpr (kIL) {
         float x[8];
         widen8<kFp8>(kf[u][j], x);
-        SplitFrag h, l;
+        Frag h, l;
 #pragma unroll
         for (int w = 0; w < 4; w += 2) {
           const float4 r = tp[(8 * j + 2 * kg + w / 2) * kTab];
@@ -310,7 +304,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
         float x[8], y[8];
         widen8<kFp8>(kf[u][j], x);
         widen8<kFp8>(kf[u][j1], y);
-        SplitFrag h0, l0, h1, l1;
+        Frag h0, l0, h1, l1;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
           const float4 r = tp[(16 * j + 4 * kg + w) * kTab];
@@ -322,7 +316,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       }
     }
     if constexpr (kTerms) {  // the slow half: keys as they are, exact in bf16
-      const SplitFrag k0 = bf16_of8<kFp8>(kf[u][1]), k1 = bf16_of8<kFp8>(kf[u][3]);
+      const Frag k0 = bf16_of8<kFp8>(kf[u][1]), k1 = bf16_of8<kFp8>(kf[u][3]);
       floatx4 s2 = {0.f, 0.f, 0.f, 0.f};
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0.v, qh[1].v, sc, 0, 0, 0);
       s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0.v, qh2[0].v, s2, 0, 0, 0);
@@ -336,8 +330,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float t = t0 + (float)e / kMiddle;
-        float x = __builtin_fmaf(next_lane(s2[e]), t, s2[e]);
-        x = __builtin_fmaf(x, t, next_lane(sc[e]));
+        float x = __builtin_fmaf(lane_up<1>(s2[e]), t, s2[e]);
+        x = __builtin_fmaf(x, t, lane_up<1>(sc[e]));
         sc[e] = __builtin_fmaf(x, t, sc[e]);
       }
     }
@@ -427,7 +421,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
           if (!(((e < 4 ? vis0 : vis1) >> (4 * kg + (e & 3))) & 1u)) pf[e] = 0.f;
       }
     }
-    SplitFrag ph, pl;
+    Frag ph, pl;
 #pragma unroll
     for (int w = 0; w < 4; ++w) split2(pf[2 * w], pf[2 * w + 1], ph.w[w], pl.w[w]);
     // A lane has the probabilities of four slots of either group; exchanged between neighbouring k-groups they are those of
@@ -441,7 +435,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     }
 #pragma unroll
     for (int nt = 0; nt < kNt; ++nt) {
-      const SplitFrag vb = bf16_of8<kFp8>(vf[nt]);
+      const Frag vb = bf16_of8<kFp8>(vf[nt]);
       o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph.v, vb.v, o[nt], 0, 0, 0);
       o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl.v, vb.v, o[nt], 0, 0, 0);
     }

@@ -28,14 +28,11 @@
 #include <mutex>
 #include <type_traits>
 
-#include "attn_common.h"
+#include "lanes.h"
 
 namespace mepic {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kD = 128, kP = 16;
@@ -45,22 +42,6 @@ constexpr int kTile = 64;    // KV slots per tile
 // A probability may grow to 2^kBigLog2 before the reference maximum is raised (fp32 sums and bf16 operands keep
 // their relative precision at any scale; only overflow has to be kept away).
 constexpr float kBig = 0x1p40f;
-
-union Frag {
-  uint4 u;
-  bf16x8 v;
-  uint32_t w[4];
-  float f[4];
-};
-
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  const f32x2 v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;  // scalar loads: set-up only, never in the loop
-__device__ __forceinline__ int sload(const int32_t* p, size_t idx) { return ((const_i32_ptr)(uintptr_t)p)[idx]; }
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Per-position rotary table in half precision (11 significant bits: eight times finer than the bf16 rounding of the
 // rotated keys): for position p and the four frequencies i0 .. i0 + 3, i0 = 8 pc + 4 e, one 16-byte entry
@@ -167,8 +148,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_mfma_bf16_kernel(const At
           lo[e] = x0 * c - x1 * s;
           hi[e] = x1 * c + x0 * s;
         }
-        bq[ks].w[w] = pack2(lo[0], lo[1]);
-        bq[ks + 4].w[w] = pack2(hi[0], hi[1]);
+        bq[ks].w[w] = pack2_bf16(lo[0], lo[1]);
+        bq[ks + 4].w[w] = pack2_bf16(hi[0], hi[1]);
       }
   }
 
@@ -234,8 +215,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_mfma_bf16_kernel(const At
       const half8 r = S.gt[w >> 1].h;
       const float c0 = (float)r[4 * (w & 1)], s0 = (float)r[4 * (w & 1) + 1];
       const float c1 = (float)r[4 * (w & 1) + 2], s1 = (float)r[4 * (w & 1) + 3];
-      klo.w[w] = pack2(__builtin_fmaf(l0, c0, -__builtin_fmaf(h0, s0, 0.f)), __builtin_fmaf(l1, c1, -__builtin_fmaf(h1, s1, 0.f)));
-      khi.w[w] = pack2(__builtin_fmaf(h0, c0, __builtin_fmaf(l0, s0, 0.f)), __builtin_fmaf(h1, c1, __builtin_fmaf(l1, s1, 0.f)));
+      klo.w[w] = pack2_bf16(__builtin_fmaf(l0, c0, -__builtin_fmaf(h0, s0, 0.f)), __builtin_fmaf(l1, c1, -__builtin_fmaf(h1, s1, 0.f)));
+      khi.w[w] = pack2_bf16(__builtin_fmaf(h0, c0, __builtin_fmaf(l0, s0, 0.f)), __builtin_fmaf(h1, c1, __builtin_fmaf(l1, s1, 0.f)));
     }
     tiles[buf].k[pc * kTile + s_st] = klo.u;
     tiles[buf].k[(pc + 8) * kTile + s_st] = khi.u;
@@ -385,7 +366,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_mfma_bf16_kernel(const At
 #pragma unroll
       for (int pp = 0; pp < 2; ++pp)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) pb[pp].w[w] = pack2(p[8 * pp + 2 * w], p[8 * pp + 2 * w + 1]);
+        for (int w = 0; w < 4; ++w) pb[pp].w[w] = pack2_bf16(p[8 * pp + 2 * w], p[8 * pp + 2 * w + 1]);
       int n_reads = 0;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -461,8 +442,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_mfma_bf16_kernel(const At
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk) {
           uint2 w;
-          w.x = pack2(o[db][4 * blk] * inv, o[db][4 * blk + 1] * inv);
-          w.y = pack2(o[db][4 * blk + 2] * inv, o[db][4 * blk + 3] * inv);
+          w.x = pack2_bf16(o[db][4 * blk] * inv, o[db][4 * blk + 1] * inv);
+          w.y = pack2_bf16(o[db][4 * blk + 2] * inv, o[db][4 * blk + 3] * inv);
           orow[(32 * db + 8 * blk + 4 * half) / 4] = w;
         }
     }

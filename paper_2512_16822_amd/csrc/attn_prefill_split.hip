@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
   // of them than there is room for, everything the workgroup did is done again.)
   __shared__ int n_redo, redo_at[kMaxRedo];
   __shared__ uint32_t redo_rows[kMaxRedo][kRows / 32];
-  const int tid = threadIdx.x, lane = tid & 63, wave = uni_i(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   __shared__ float2 freq[D / 2];  // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
   if (tid < D / 2) freq[tid] = make_float2(a.freq_hi[tid], a.freq_lo[tid]);
   const int l32 = lane & 31, half = lane >> 5;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
     if (lane == 0) cum[0] = 0;
   }
   __syncthreads();
-  const int total = uni_i(cum[a.B]);
+  const int total = uni(cum[a.B]);
   const int chunk = max((total + n_w - 1) / n_w, a.blocks_per_split);  // (blocks_per_split: the least run, in tiles)
   const int run_end = min((w + 1) * chunk, total);
   int at = w * chunk, b = 0;
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
     int hi = a.B;
     while (hi - b > 1) {
       const int mid = (b + hi) >> 1;
-      if (uni_i(cum[mid]) <= at) b = mid; else hi = mid;
+      if (uni(cum[mid]) <= at) b = mid; else hi = mid;
     }
   }
   struct Segment {
@@ -118,12 +118,12 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
     long n_rows, row0;
   };
   auto segment = [&](int pos, int& r) __attribute__((always_inline)) {  // what lies at `pos` of the sequence; r: request at or before it
-    while (uni_i(cum[r + 1]) <= pos) ++r;
+    while (uni(cum[r + 1]) <= pos) ++r;
     Segment s;
-    s.L = uni_i(a.kv_lens[r]);
-    s.q_begin = uni_i(q_first(r));
-    s.n_rows = (long)(uni_i(q_first(r + 1)) - s.q_begin) * G;
-    const int T = kv_tiles(s.L), seq0 = uni_i(cum[r]), rt = (pos - seq0) / T;
+    s.L = uni(a.kv_lens[r]);
+    s.q_begin = uni(q_first(r));
+    s.n_rows = (long)(uni(q_first(r + 1)) - s.q_begin) * G;
+    const int T = kv_tiles(s.L), seq0 = uni(cum[r]), rt = (pos - seq0) / T;
     s.t_first = pos - seq0 - rt * T;
     s.n_seg = min(run_end - pos, T - s.t_first);
     s.row0 = (long)rt * kRows;
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
     const int tok = q_begin + (int)((row_ok ? row : row0) / G), g = (int)((row_ok ? row : row0) % G);
     const int pos_q = a.q_positions[tok];
     const size_t out_row = (size_t)tok * a.Hq + (size_t)hk * G + g;
-    SplitFrag qh[kKs], ql[kKs];
+    Frag qh[kKs], ql[kKs];
     {
       const uint4* q4 = reinterpret_cast<const uint4*>(a.q) + out_row * (D / 8);
       const float qs = row_ok ? a.qk_scale_log2 : 0.f;
@@ -196,8 +196,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
       wpos_min = min(wpos_min, __shfl_xor(wpos_min, o));
       wpos_max = max(wpos_max, __shfl_xor(wpos_max, o));
     }
-    wpos_min = uni_i(wpos_min);
-    wpos_max = uni_i(wpos_max);
+    wpos_min = uni(wpos_min);
+    wpos_max = uni(wpos_max);
     const int n_begin = sg.t_first * kTile;
     int n_end = min(L, (sg.t_first + sg.n_seg) * kTile);
     if (!a.block_positions) {  // slots are their own positions: nothing past the last query token is visible
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
       for (int t = q_begin + (int)(row0 / G) + lane; t <= t_last; t += 64) pmax = max(pmax, a.q_positions[t]);
 #pragma unroll
       for (int o = 32; o; o >>= 1) pmax = max(pmax, __shfl_xor(pmax, o));
-      n_end = min(n_end, max(uni_i(pmax), -1) + 1);
+      n_end = min(n_end, max(uni(pmax), -1) + 1);
     }
     const int n_tiles = n_end > n_begin ? (n_end - n_begin + kTile - 1) / kTile : 0;
 
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
         float x0[8], x1[8];
         widen8<kFp8>(st.k[0], x0);
         widen8<kFp8>(st.k[1], x1);
-        SplitFrag h0, l0, h1, l1;
+        Frag h0, l0, h1, l1;
         auto rot = [&](float x, float y, int j, float& u, float& v) __attribute__((always_inline)) {
           const float tr = turns_frac(pos, fh[j], fl[j]);
           float c = __builtin_amdgcn_cosf(tr), s = __builtin_amdgcn_sinf(tr);
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
       for (int i = 0; i < kNv; ++i) {
         int pg_grp, rem, grp, dim, hf;
         v_place(i, pg_grp, rem, grp, dim, hf);
-        SplitFrag x = bf16_of8<kFp8>(st.v[i]);
+        Frag x = bf16_of8<kFp8>(st.v[i]);
         uint32_t keep = pick(grp, st.valid[0], st.valid[1], st.valid[2], st.valid[3]);
         keep = (keep >> (8 * hf)) & 0xffu;
         if (keep != 0xffu) mask8(x, keep);
@@ -377,12 +377,12 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
       const Tile<D>& T = tiles[buf];
 #pragma unroll 1
       for (int sb = 0; sb < 2; ++sb) {
-        const int ps0 = uni_i(T.pos[2 * sb]), ps1 = uni_i(T.pos[2 * sb + 1]);
-        const uint32_t vd0 = (uint32_t)uni_i((int)T.valid[2 * sb]), vd1 = (uint32_t)uni_i((int)T.valid[2 * sb + 1]);
+        const int ps0 = uni(T.pos[2 * sb]), ps1 = uni(T.pos[2 * sb + 1]);
+        const uint32_t vd0 = (uint32_t)uni((int)T.valid[2 * sb]), vd1 = (uint32_t)uni((int)T.valid[2 * sb + 1]);
         if ((vd0 | vd1) == 0 || (min(ps0, ps1) > wpos_max)) continue;  // nothing here is visible to any of the wave's rows
         const bool need_mask = (vd0 & vd1) != 0xffffu || max(ps0, ps1) + 15 > wpos_min;
         constexpr int kRing = 4;
-        SplitFrag ring[kRing];
+        Frag ring[kRing];
         const uint4* kh = T.khi + half * kTile + k_read + 32 * sb;
         const uint4* kl = T.klo + half * kTile + k_read + 32 * sb;
         const uint4* vt = T.v + 4 * sb * D + l32 * 2 + (half ^ ((l32 >> 3) & 1));
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_split_kernel(const AttnAr
               if (sc[e] == -INFINITY) p[e] = 0.f;
           }
         }
-        SplitFrag ph[2], pl[2];  // group gg of the block: k index e -> slot 8 half + e
+        Frag ph[2], pl[2];  // group gg of the block: k index e -> slot 8 half + e
 #pragma unroll
         for (int gg = 0; gg < 2; ++gg)
 #pragma unroll

@@ -1,31 +1,16 @@
-// What the matrix-core decode kernels share: operand fragments, page loads, scalar reads, reductions over the k-groups of a
-// head, and the two-term dot products that rotate bf16 keys.
+// What the plain and the batched decode kernel share: page ids, page loads, and the two-term dot products that rotate bf16 keys.
 #pragma once
 #include <type_traits>
 
-#include "attn_common.h"
+#include "lanes.h"
 
 namespace mepic {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-union Frag {  // one 16-byte operand fragment
-  uint4 u;
-  bf16x8 v;
-  f16x8 hv;
-  uint32_t w[4];
-};
 
 // Two fp32 -> packed fp16 pair, round to nearest even.
 __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
   const f32x2 v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
 }
-
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // A page id as the kernels use it: forced into [0, num_pages) so that a corrupt block table reads a wrong page
 // instead of faulting (the result of that request is then unspecified, nothing else is affected).
@@ -54,34 +39,6 @@ __device__ __forceinline__ uint2 load_page(const uint2* p) {
   }
 }
 
-// Wave-uniform read of a read-only int32 input through the scalar unit (s_load): unlike a vector load it
-// does not share the vector-memory counter, so waiting for it never drains the K/V loads in flight.
-typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-__device__ __forceinline__ int sload(const int32_t* p, size_t idx) {
-  return ((const_i32_ptr)(uintptr_t)p)[idx];
-}
-
-typedef const __attribute__((address_space(4))) float* const_f32_ptr;
-__device__ __forceinline__ float sloadf(const float* p, size_t idx) { return ((const_f32_ptr)(uintptr_t)p)[idx]; }
-
-// Maximum over the four lanes l, l^16, l^32, l^48 (the four k-groups of one head), in every lane.
-__device__ __forceinline__ float max_over_kgroups(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float sum_over_kgroups(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
 // Eight two-term dot products on packed bf16 words, fp32 results: l_i = e_i . ca_i, h_i = e_i . cb_i, where
 // e_i = (low element, high element) of a rotary pair and ca = (cos, -sin), cb = (sin, cos) as packed bf16.
 // One block of eight v_dot2_f32_bf16 closed by four wait states: another vector instruction may neither read the
@@ -107,7 +64,5 @@ __device__ __forceinline__ void dot_rotate_block(uint32_t e0, uint32_t e1, uint3
       : "v"(e0), "v"(e1), "v"(e2), "v"(e3), "v"(ca0), "v"(cb0), "v"(ca1), "v"(cb1), "v"(ca2), "v"(cb2), "v"(ca3),
         "v"(cb3));
 }
-
-constexpr float kPScaleFp8 = 4.f;  // probabilities (at most 2^6) are multiplied by this before the e4m3 split
 
 }  // namespace mepic

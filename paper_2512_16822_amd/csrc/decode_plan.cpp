@@ -208,7 +208,7 @@ int mepic_decode_plan_build_ahead(const int32_t* block_tables, const int32_t* kv
       runs.swap(ordered);
     }
     const int n_runs = (int)runs.size();
-    const int W = decode_mfma_waves_per_head(Hkv);
+    const int W = decode_batched_waves_per_head(Hkv);
     if (W > kPlanMaxWaves) return MEPIC_ERR_UNSUPPORTED;
     if (plan_words(n_runs, B, n_gather, W) > capacity_int32) return MEPIC_ERR_CAPACITY;
     int T = 0;

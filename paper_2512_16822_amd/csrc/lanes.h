@@ -1,0 +1,52 @@
+// What the matrix-core kernels share: operand fragments, wave-uniform values and reads, exchanges between lanes.
+#pragma once
+#include "attn_common.h"
+
+namespace mepic {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+union Frag {  // one 16-byte operand fragment
+  uint4 u;
+  bf16x8 v;
+  f16x8 hv;
+  uint32_t w[4];
+};
+
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Wave-uniform read of a read-only int32 input through the scalar unit (s_load): unlike a vector load it
+// does not share the vector-memory counter, so waiting for it never drains the K/V loads in flight.
+typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+__device__ __forceinline__ int sload(const int32_t* p, size_t idx) {
+  return ((const_i32_ptr)(uintptr_t)p)[idx];
+}
+
+// The value of the lane kBy places up in the row of 16 lanes (0 past its end).
+template <int kBy>
+__device__ __forceinline__ float lane_up(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x100 + kBy, 0xf, 0xf, true));
+}
+
+// Maximum over the four lanes l, l^16, l^32, l^48 (the four k-groups of one head), in every lane.
+__device__ __forceinline__ float max_over_kgroups(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const uint32_t v = __float_as_uint(y);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float sum_over_kgroups(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const uint32_t v = __float_as_uint(y);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+}  // namespace mepic

@@ -12,7 +12,7 @@
 #pragma once
 #include <atomic>
 
-#include "attn_common.h"
+#include "lanes.h"
 
 namespace mepic {
 
@@ -29,14 +29,6 @@ inline hipError_t allow_lds(const void* kernel, size_t bytes, std::atomic<uint64
   return e;
 }
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-union SplitFrag {  // one 16-byte operand fragment
-  uint4 u;
-  bf16x8 v;
-  uint32_t w[4];
-};
-
 // Two fp32 values -> their packed bf16 heads and packed bf16 remainders. (x - head as a two-term dot product of the packed
 // word with (-1, 0) saves two of the six instructions and measured no faster here and 5 % slower in the prefill kernel.)
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
@@ -44,7 +36,6 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_
   lo = pack2_bf16(x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xffff0000u));
 }
 
-__device__ __forceinline__ int uni_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float uni_f(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
 
 // Eight stored elements (one granule of bf16, or half a granule of e4m3 codes) as loaded.
@@ -73,8 +64,8 @@ __device__ __forceinline__ void widen8(const Raw8<kFp8>& in, float (&x)[8]) {
 
 // Eight stored elements as packed bf16 (exact for e4m3 codes, whose page scale is applied elsewhere).
 template <bool kFp8>
-__device__ __forceinline__ SplitFrag bf16_of8(const Raw8<kFp8>& in) {
-  SplitFrag f;
+__device__ __forceinline__ Frag bf16_of8(const Raw8<kFp8>& in) {
+  Frag f;
   if constexpr (kFp8) {
     const uint32_t w[2] = {in.r.x, in.r.y};
 #pragma unroll
@@ -90,28 +81,10 @@ __device__ __forceinline__ SplitFrag bf16_of8(const Raw8<kFp8>& in) {
 }
 
 // Keep the elements of `f` whose bit of `keep` (8 bits) is set, zero the others.
-__device__ __forceinline__ void mask8(SplitFrag& f, uint32_t keep) {
+__device__ __forceinline__ void mask8(Frag& f, uint32_t keep) {
 #pragma unroll
   for (int i = 0; i < 4; ++i)
     f.w[i] &= ((keep >> (2 * i)) & 1u ? 0x0000ffffu : 0u) | ((keep >> (2 * i + 1)) & 1u ? 0xffff0000u : 0u);
-}
-
-// Maximum / sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the k-groups of one head), in every lane.
-__device__ __forceinline__ float max_over_kgroups(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float sum_over_kgroups(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const uint32_t v = __float_as_uint(y);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 }  // namespace mepic
