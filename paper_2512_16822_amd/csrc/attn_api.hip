@@ -116,6 +116,7 @@ Plan make_plan(const mepic_attn_params* p, bool prefill, bool no_pieces = false)
     // the bound on partials per request (sizes the workspace) and the minimum chunk are fixed.
     pl.kernel = mfma_fp8 ? K_DECODE_PLAIN_F8 : K_DECODE_PLAIN_BF16;
     decode_plain_plan(p->B, p->Hkv, max_kv, &pl.n_splits, &pl.blocks_per_split);
+    pl.kv_tiles = (max_kv + 31) / 32;
     pl.workspace_bytes = (size_t)p->n_q_tokens * p->Hq * pl.n_splits * (p->D + 2) * sizeof(float) +
                          (size_t)(p->B + 2) * sizeof(int32_t);
     pl.min_workspace_bytes = pl.workspace_bytes;

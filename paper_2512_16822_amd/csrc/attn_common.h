@@ -37,7 +37,7 @@ struct AttnArgs {
   int32_t interleaved, causal;
   int32_t kv_read_once;  // hint: pages are not shared between requests (matrix-core decode: non-temporal loads)
   int32_t n_splits, blocks_per_split;
-  int32_t kv_tiles;                  // split-precision prefill: most KV tiles of a request
+  int32_t kv_tiles;                  // split-precision prefill: most KV tiles of a request; plain decode: most steps of 32 slots
   float qk_scale_log2;               // sm_scale * log2(e): scores are kept in log2 units
   // Rotary frequencies in turns per position, f_i / (2 pi), split into two floats whose sum carries
   // ~48 bits, so that position * frequency can be reduced modulo one turn without fp64.

@@ -909,9 +909,14 @@ hipError_t launch_decode_plain(const AttnArgs& a, hipStream_t s) {
   // pairs rotated; a commit and 16 requests of 2.2 K slots 23.2, 23.7, 25.0.
   const float f = 6.283185307f * a.freq_hi[32];
   if (a.kv_dtype == MEPIC_F8E4M3) {
-    // two steps a turn where a KV head's query heads fit half the matrix rows: 128 requests of 2 - 33 K slots, 7 heads each,
-    // 182 us a call against 195
-    if (a.G <= 8) launch_one<true, 1, 2>(a, n_wg, s);
+    // Two steps a turn where a KV head's query heads fit half the matrix rows and waves have steps enough (by the bound on the lengths):
+    // 128 requests of 2 - 33 K slots, 7 heads each, 257 steps a wave, 182 us a call against 193; 130 requests of 2 K, 8 heads, 36 a wave, 104
+    // against 106. With fewer, requests and parts of an odd number of steps leave too many turns half empty: us with two and one steps
+    // a turn 130 of 1.1 K (19 a wave) 61.0 and 59.4, 130 of up to 328 slots (5.6) 28.7 and 24.4, 1 of 200 11.1 and 9.8.
+    // Between half a step and one a wave, where up to 64 requests are cut into pieces of their own, it is turns that make
+    // pieces, and so partials: 4 of 5.7 K slots on 2 heads 14.8 and 18.0, 20 of 1.1 K 12.9 and 13.5, 64 of 200 13.2 and 13.1.
+    const long steps = (long)a.B * a.kv_tiles, waves = (long)(n_wg / a.Hkv) * kWaves;
+    if (a.G <= 8 && (steps >= 32 * waves || (a.B > 1 && a.B <= 64 && 2 * steps > waves && steps <= waves))) launch_one<true, 1, 2>(a, n_wg, s);
     else launch_one<true, 1, 1>(a, n_wg, s);
   } else if (63.5f * f <= 0.1f && a.G <= 8) {
     launch_one<false, 2, 1>(a, n_wg, s);
