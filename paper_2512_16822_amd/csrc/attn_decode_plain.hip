@@ -29,11 +29,11 @@
 //   32 .. 63) turns by x t, |x| <= 0.1 (0.35), about the middle of that span, t in [-1, 1], and e^(-i x t) = J0(x) - 2 i J1(x) T1(t) -
 //   2 J2(x) T2(t) + ... (Jacobi-Anger): with a row for each of two (three) terms, Q' times the term's coefficient, their keys
 //   go into the products as they are, and the scores of a head are the sum of its rows' weighted by T_m(t) of the slot: one multiply-add a
-//   score and term. 292 -> 183 vector instructions a step (start-up and run ends counted in), and these keys lose no bits to a rotation. Infinite keys, and scores past the
+//   score and term. 292 -> 187 vector instructions a step (start-up and run ends counted in), and these keys lose no bits to a rotation. Infinite keys, and scores past the
 //   largest float, have no such series (0 x Inf, Inf - Inf between the terms): a run that met any is computed again by plain_run.
 // * fp8, two steps a turn. With G <= 8 rows 0-7 belong to the turn's first step and 8-15 to its second, Q' of the latter standing 32
 //   slots on: both use the same constants, and softmax, the split of the probabilities and their scaling happen once for both.
-//   260 -> 204 vector instructions a step. Either half of the rows keeps a reference maximum and a reference V scale of its own, as two
+//   260 -> 205 vector instructions a step. Either half of the rows keeps a reference maximum and a reference V scale of its own, as two
 //   waves would, and they are brought together at the run's end.
 // fp8: the page's K scale multiplies the scores. V is never widened: PV takes the bytes as loaded and the probabilities split
 // into two e4m3 terms (p*16 = hi + lo, 8 significant bits together down to p = 2^-7); the page's V scale rides on the probabilities, O
