@@ -29,7 +29,7 @@
 //   32 .. 63) turns by x t, |x| <= 0.1 (0.35), about the middle of that span, t in [-1, 1], and e^(-i x t) = J0(x) - 2 i J1(x) T1(t) -
 //   2 J2(x) T2(t) + ... (Jacobi-Anger): with a row for each of two (three) terms, Q' times the term's coefficient, their keys
 //   go into the products as they are, and the scores of a head are the sum of its rows' weighted by T_m(t) of the slot: one multiply-add a
-//   score and term. 292 -> 187 vector instructions a step (start-up and run ends counted in), and these keys lose no bits to a rotation. Infinite keys, and scores past the
+//   score and term. 292 -> 183 vector instructions a step (start-up and run ends counted in), and these keys lose no bits to a rotation. Infinite keys, and scores past the
 //   largest float, have no such series (0 x Inf, Inf - Inf between the terms): a run that met any is computed again by plain_run.
 // * fp8, two steps a turn. With G <= 8 rows 0-7 belong to the turn's first step and 8-15 to its second, Q' of the latter standing 32
 //   slots on: both use the same constants, and softmax, the split of the probabilities and their scaling happen once for both.
@@ -148,10 +148,12 @@ __device__ __forceinline__ void plain_run(const AttnArgs& a, const float2* freq,
 }
 
 // kTerms: matrix rows a head has in the products with the slow half of the pairs (1: all pairs are rotated). kPack: steps a turn
-// of the loop takes together, each with matrix rows of its own for every head.
-template <bool kFp8, int kTerms, int kPack, bool kReadOnce>
+// of the loop takes together, each with matrix rows of its own for every head. kFull: with terms, every matrix row belongs to a head (as a
+// branch in the loop this cost a decode step's call of 16 requests 0.15 us, whether taken or not).
+template <bool kFp8, int kTerms, int kPack, bool kFull, bool kReadOnce>
 __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const AttnArgs a) {
   static_assert(kFp8 ? kTerms == 1 : kPack == 1, "bf16 uses idle rows for terms, e4m3 for steps");
+  static_assert(!kFull || kTerms == 2, "eight heads of two rows; three rows a head leave one over");
   constexpr int kP = kFp8 ? 32 : 16;          // slots per page
   constexpr int kBps = kFp8 ? 1 : 2;          // pages per step of 32 slots
   constexpr int kNK = kFp8 ? 2 : 4;           // 16-byte K fragments per lane and product
@@ -175,7 +177,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   // of this lane's matrix row: which step of the turn, which head, which term
   const int part = kPack == 2 ? n16 >> 3 : 0, head = (kPack == 2 ? n16 & 7 : n16) / kTerms, term = n16 % kTerms;
   const bool row_ok = term == 0 && head < G;
-  const bool full = kTerms > 1 && G * kTerms == 16;  // every matrix row belongs to a head
 
   // ---- steps of every request. Up to 64 requests: each wave scans the lengths itself and keeps them in its lanes (lane b:
   // request b's length and the steps up to its end), so that its first page ids are on their way before the tables are built. ----
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
         else x[s][u] = sc0;
       }
     if constexpr (kTerms > 1) {
-      if (full) {  // (no row is left whose zeros would tell of an infinite key)
+      if constexpr (kFull) {  // (no row is left whose zeros would tell of an infinite key)
         const Frag none = {make_uint4(0, 0, 0, 0)};
 #pragma unroll
         for (int j = 1; j < 4; j += 2)
@@ -853,11 +854,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   }
 }
 
-template <bool kFp8, int kTerms, int kPack>
+template <bool kFp8, int kTerms, int kPack, bool kFull = false>
 void launch_one(const AttnArgs& a, int n_wg, hipStream_t s) {
   const size_t lds = a.B <= 64 ? 0 : (size_t)(a.B + 1) * sizeof(int);
-  if (a.kv_read_once) hipLaunchKernelGGL((decode_plain_kernel<kFp8, kTerms, kPack, true>), dim3(n_wg), dim3(64 * kWaves), lds, s, a);
-  else hipLaunchKernelGGL((decode_plain_kernel<kFp8, kTerms, kPack, false>), dim3(n_wg), dim3(64 * kWaves), lds, s, a);
+  if (a.kv_read_once) hipLaunchKernelGGL((decode_plain_kernel<kFp8, kTerms, kPack, kFull, true>), dim3(n_wg), dim3(64 * kWaves), lds, s, a);
+  else hipLaunchKernelGGL((decode_plain_kernel<kFp8, kTerms, kPack, kFull, false>), dim3(n_wg), dim3(64 * kWaves), lds, s, a);
 }
 
 // Merge the partials of one (request, query head). Request b owns steps [cum[b], cum[b+1]) of its KV
@@ -919,7 +920,8 @@ hipError_t launch_decode_plain(const AttnArgs& a, hipStream_t s) {
     if (a.G <= 8 && (steps >= 32 * waves || (a.B > 1 && a.B <= 64 && 2 * steps > waves && steps <= waves))) launch_one<true, 1, 2>(a, n_wg, s);
     else launch_one<true, 1, 1>(a, n_wg, s);
   } else if (63.5f * f <= 0.1f && a.G <= 8) {
-    launch_one<false, 2, 1>(a, n_wg, s);
+    if (a.G == 8) launch_one<false, 2, 1, true>(a, n_wg, s);
+    else launch_one<false, 2, 1>(a, n_wg, s);
   } else if (31.5f * f <= 0.35f && a.G <= 5) {
     launch_one<false, 3, 1>(a, n_wg, s);
   } else {

@@ -33,16 +33,16 @@ def check(M, oracle_attn, case, rows):
         assert (np.abs(sel[i] - want[i]) - np.abs(want[i]) * rel).max() <= np.abs(want).max() * rest, (t, h)
 
 
+LONG = (4064, 4096, 4097, 8192, 8193, 12300)
+
+
 @pytest.mark.parametrize("masks", [False, True])
-@pytest.mark.parametrize("kv_dtype,P,lengths", [("bf16", 16, (4064, 4096, 4097, 8192, 8193, 12300)),
-                                                ("f8e4m3", 32, (4064, 4096, 4097, 8192, 8193, 12300)),
-                                                ("f32", 16, (8176, 8192, 8193, 16384, 16400))])
-@pytest.mark.parametrize("D,theta", [(64, 5e5), (128, 5e5), (128, 1.5e5)])
-def test_decode_windows(mepic, oracle_attn, D, theta, kv_dtype, P, lengths, masks):
+@pytest.mark.parametrize("kv_dtype,P,D,theta,lengths", [(t, P, D, theta, LONG) for t, P in (("bf16", 16), ("f8e4m3", 32))
+                                                        for D, theta in ((64, 5e5), (128, 5e5), (128, 1.5e5))]
+                         + [("f32", 16, 64, 5e5, (8176, 8192, 8193, 16384, 16400))])
+def test_decode_windows(mepic, oracle_attn, kv_dtype, P, D, theta, lengths, masks):
     """512 (token, KV head) pairs, so that one workgroup takes a context whole: four waves with runs of 32, 33, 64, 65 and 97
     steps of 32 slots (fp32: eight waves, 64, 65, 128 and 129 groups of 16). D 128: half the pairs by terms, tables of 256 and of 128 slots."""
-    if kv_dtype == "f32" and D == 128:
-        pytest.skip("one form of it is enough: nothing of the windows depends on D or theta")
     st = W.Structure("windows", "decode", 64, 8, 8, D, P, theta, "f32" if kv_dtype == "f32" else "bf16", kv_dtype, 91)
     st.requests, st.n_q, st.extra_tail = [[(0, n, 0)] for n in lengths] + [[(0, 5, 0)]] * (64 - len(lengths)), [1] * 64, 0
     case = assembled(st, masks)
