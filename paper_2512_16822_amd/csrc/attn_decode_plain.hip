@@ -29,8 +29,9 @@
 //   32 .. 63) turns by x t, |x| <= 0.1 (0.35), about the middle of that span, t in [-1, 1], and e^(-i x t) = J0(x) - 2 i J1(x) T1(t) -
 //   2 J2(x) T2(t) + ... (Jacobi-Anger): with a row for each of two (three) terms, Q' times the term's coefficient, their keys
 //   go into the products as they are, and the scores of a head are the sum of its rows' weighted by T_m(t) of the slot: one multiply-add a
-//   score and term. 292 -> 183 vector instructions a step (start-up and run ends counted in), and these keys lose no bits to a rotation. Infinite keys, and scores past the
-//   largest float, have no such series (0 x Inf, Inf - Inf between the terms): a run that met any is computed again by plain_run.
+//   score and term. 292 -> 183 vector instructions a step (start-up and run ends counted in), and these keys lose no bits to a rotation.
+//   Infinite keys, and scores past the largest float, have no such series (0 x Inf, Inf - Inf between the terms): a run that met any
+//   is computed again by plain_run.
 // * fp8, two steps a turn. With G <= 8 rows 0-7 belong to the turn's first step and 8-15 to its second, Q' of the latter standing 32
 //   slots on: both use the same constants, and softmax, the split of the probabilities and their scaling happen once for both.
 //   260 -> 205 vector instructions a step. Either half of the rows keeps a reference maximum and a reference V scale of its own, as two
@@ -74,9 +75,9 @@ __device__ __forceinline__ int wave_scan(int x) {
 // Slot-rotation tables: step j of a run uses table j mod n, Q' advances every n steps.
 constexpr int n_tables(bool fp8, int terms) { return fp8 || terms == 2 ? 4 : 2; }
 
-// A run of a bf16 request - slots [n_begin, n_end) below its length, n_begin a multiple of 32 - for KV head hk by plain arithmetic, one wave:
-// every key rotated at its own position. A run that met a score without a finite value is computed again by it, at the end of a wave's
-// work and in few instructions: a second way through the walker's loop cost calls of few requests 0.7 - 2 us by its length alone.
+// A run of a bf16 request - slots [n_begin, n_end) below its length, n_begin a multiple of 32 - for KV head hk by plain arithmetic, one
+// wave: every key rotated at its own position. A run that met a score without a finite value is computed again by it, at the end of a
+// wave's work and in few instructions: a second way through the walker's loop cost calls of few requests 0.7 - 2 us by its length alone.
 __device__ __forceinline__ void plain_run(const AttnArgs& a, const float2* freq, int b, int hk, int n_begin, int n_end, size_t row0) {
   const int lane = threadIdx.x & 63;
   const uint16_t* const q = reinterpret_cast<const uint16_t*>(a.q);
@@ -841,7 +842,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     if (!more) break;
   }
   if (kTerms > 1 && again != 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the partials written above come first
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // the partials written above come first, also those of other lanes
     int b = 0, pos = pos_begin;
     for (run = 0; pos < pos_end; ++run) {
       while (cum_at(b + 1) <= pos) ++b;
