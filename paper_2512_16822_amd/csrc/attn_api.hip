@@ -294,7 +294,7 @@ int run_batched(const mepic_attn_params* p, const int32_t* plan, const mepic_dec
   a.part_o = ws;
   a.part_ml = ws + (size_t)a.n_q * a.Hq * a.n_splits * a.D;
   g_last_kernel = mfma_fp8 ? "decode_mfma_fp8_batched" : "decode_mfma_bf16_batched";
-  const hipError_t e = launch_decode_batched(a, info->n_runs, reinterpret_cast<hipStream_t>(hip_stream));
+  const hipError_t e = launch_decode_batched(a, info->n_runs, info->total_steps, reinterpret_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? MEPIC_OK : MEPIC_ERR_LAUNCH;
 }
 

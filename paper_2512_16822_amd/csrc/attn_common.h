@@ -37,6 +37,7 @@ struct AttnArgs {
   int32_t interleaved, causal;
   int32_t kv_read_once;  // hint: pages are not shared between requests (matrix-core decode: non-temporal loads)
   int32_t n_splits, blocks_per_split;
+  int32_t later_wg;  // general decode of bf16 / fp8 pages: workgroups from there on are the second ones of their compute units
   int32_t kv_tiles;                  // split-precision prefill: most KV tiles of a request; plain decode: most steps of 32 slots
   float qk_scale_log2;               // sm_scale * log2(e): scores are kept in log2 units
   // Rotary frequencies in turns per position, f_i / (2 pi), split into two floats whose sum carries
@@ -88,6 +89,6 @@ hipError_t launch_tile_stream_probe(int structure, int iters, float* buf, int n_
 int device_compute_units();
 int decode_plain_max_requests();                                       // B the plain walker's LDS has room for
 int decode_batched_waves_per_head(int Hkv);                             // waves that share one KV head's steps
-hipError_t launch_decode_batched(const AttnArgs& a, int n_runs, hipStream_t s);  // plan-driven variant
+hipError_t launch_decode_batched(const AttnArgs& a, int n_runs, int total_steps, hipStream_t s);  // plan-driven variant
 
 }  // namespace mepic

@@ -220,6 +220,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
   // K of the next group is requested as soon as the scores are done with the registers, V after its products; always, so
   // that the waits can count the loads in flight (past the last group the last page comes once more).
   for (int st = 0; st < n_st; ++st) {
+    if constexpr (D == 128) take_turns(wave >= kWaves / 2, st);
     const int l0 = st & 63;
     if (st > 0 && l0 == 0) {
       cur = nxt;

@@ -711,6 +711,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     const int n_turns = (n_st + kPack - 1) / kPack;
     int v = 0;
     for (int t = 0; t < n_turns - 1; ++t) {
+      take_turns(wave >= kWaves / 2, t);
       const int here = (kBpt * t) & 63, rel = (kBpt * (t + 1)) & 63;  // blocks of this and the next turn in their windows
       float ksc = 1.f, vs0 = 1.f, vs1 = 1.f;
       if constexpr (kFp8) {

@@ -27,6 +27,8 @@
 // probabilities of up to kMostSum times values near the largest float make Inf of finite ones.
 #include <type_traits>
 
+#include <limits.h>
+
 #include "attn_scalar.h"
 #include "split_common.h"
 
@@ -64,7 +66,8 @@ constexpr size_t lds_bytes() {
   return n < sizeof(ScalarLds<4, kThreads>) ? sizeof(ScalarLds<4, kThreads>) : n;
 }
 
-template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab>
+// kTurns: two workgroups a compute unit, which share its SIMDs (take_turns).
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, bool kTurns>
 __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArgs a) {
   constexpr int kKs = D / 32;     // k-steps of 32 dims; granule of k-step j: dims 32 j + 8 kg ..
   constexpr int kNt = D / 16;     // output tiles of 16 dims
@@ -443,6 +446,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
 
   // K of the next step is requested as soon as the scores are done with the registers, V after its products; always, so
   // that the waits can count the loads in flight (past the last step the last pages come once more).
+  const bool later = kTurns && (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >= a.later_wg;
   for (int st = 0; st < n_st; ++st) {
     const int l0 = (2 * st) & 63;
     if (st > 0 && l0 == 0) {
@@ -469,6 +473,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     sc[1] = score(1, ps1 - base);
     __builtin_amdgcn_sched_barrier(0);
     issue_k(np0, np1);
+    if constexpr (kTurns) take_turns(later, st);
     __builtin_amdgcn_sched_barrier(0);
     attend(sc, vis0, both ? vis1 : 0u, l0);
     if (!both && vis1) {  // the step's groups lie too far apart for one table: the second one takes a turn of its own
@@ -540,16 +545,21 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
                                                                   n_begin, s_end, split, direct);
 }
 
-template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab>
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, bool kTurns = false>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
+  // Calls of one round of workgroups and of eight steps and more a wave take turns (64 requests of 4.2 K slots with masks, 34 steps a wave, 84.0 -> 80.2 us);
+  // with few steps what it adds to the loop is more than it gives: 2 requests of 1.2 K slots, D 64, 9.54 -> 9.75, 2 of 7 K on 2 heads, 7 steps a wave,
+  // 13.1 -> 13.3.
+  if constexpr (!kTurns && D == 128)
+    if (a.later_wg != INT_MAX && a.blocks_per_split * P >= 8 * 32 * kWaves) return launch_one<kFp8, D, P, kIL, kTerms, kTab, true>(a, s);
   constexpr size_t lds = lds_bytes<D, kTerms, kTab>();
   static std::atomic<uint64_t> asked{0};
-  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab>), lds, asked);
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kTurns>), lds, asked);
   if (status != hipSuccess) return status;
   // KV heads fastest (neighbours go to different dies, which then each keep their own heads' pages); tokens over x and y
   const unsigned per_row = (unsigned)min(a.n_q, max(65536 / a.Hkv, 1));
   const dim3 grid((unsigned)a.Hkv * per_row, ((unsigned)a.n_q + per_row - 1) / per_row, (unsigned)a.n_splits);
-  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab>), grid, dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kTurns>), grid, dim3(kThreads), lds, s, a);
   return hipGetLastError();
 }
 template <bool kFp8, int D, int P>
@@ -572,7 +582,11 @@ hipError_t launch_kv(const AttnArgs& a, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_decode_split(const AttnArgs& a, hipStream_t s) {
+hipError_t launch_decode_split(const AttnArgs& args, hipStream_t s) {
+  AttnArgs a = args;
+  // up to two workgroups a compute unit in one round; of more, which one is the later changes as they end
+  const long cus = device_compute_units(), n_wg = (long)a.n_q * a.Hkv * a.n_splits;
+  a.later_wg = n_wg > cus && n_wg <= 2 * cus ? (int)cus : INT_MAX;
   return a.kv_dtype == MEPIC_F8E4M3 ? launch_kv<true>(a, s) : launch_kv<false>(a, s);
 }
 
