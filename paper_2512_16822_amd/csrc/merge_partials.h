@@ -5,11 +5,12 @@
 // however small its weight, so that a NaN or Inf of its row or its sum is in the result wherever the context was cut.
 //
 // What a merge of tens of partials costs is memory latency, not bytes, so there is as little as possible in its chain of
-// dependent loads: lane i of every wave takes the maximum and the sum of partial i (64 at a time, one coalesced load; the
-// serial scan over the maxima that this replaces cost a load latency per few partials), and each thread's first
-// row is requested before the number of partials is known, the next ones before the weights are. Groups of D / 4 threads take every kGroups-th partial, a thread four
-// dims of it; LDS adds the groups up. Measured (kernel time) on 128 rows of 54 partials:
-// 7.4 -> 4.0 us, 2048 rows of the batched decode plan: 6.1 -> 5.0 us, 256 rows of up to 256: 7.0 -> 5.0 us.
+// dependent loads: lane i of every wave takes the maximum and the sum of partial i (64 at a time, one coalesced load), and each thread's first
+// row is requested before the number of partials is known. Groups of D / 4 threads take every kGroups-th partial, a thread four
+// dims of it; LDS adds the groups up. With 256 threads all other rows of up to 64 partials are requested as soon as their number is known (two at a time,
+// one turn ahead, were four trips to memory where there are 54; all of them before it is known reads what nobody wrote: a commit and 16 requests of
+// 2.2 K slots 21.2 -> 22.1 us). us a call before and after: 4 requests of 1.7 K slots, 54 partials a row, 12.4 -> 11.75, that commit and 16 requests,
+// 16 partials, 21.2 -> 20.95, 2 planned requests of 7 K 19.7 -> 17.3.
 #pragma once
 #include "attn_common.h"
 
@@ -43,16 +44,18 @@ __device__ __forceinline__ float wave_reduce(float x, Op op) {
   return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Threads per row. Up to two rows per compute unit leave it nearly idle: 256 threads, so that a thread has half as many loads in
-// its chain (128 rows of 54 partials 4.9 -> 4.0 us, 256 rows of up to 256 5.8 -> 5.0, 512 rows even; 512 threads: no better). With
-// more rows there are enough loads in flight, and the extra waves cost: 2048 batched rows 5.0 -> 5.6 us, 3584 rows 5.0 -> 6.8.
-constexpr int kMergeThreads = 128, kMergeThreadsFew = 256, kMergeFewRows = 512;
+// Threads per row. Up to four rows per compute unit leave it nearly idle: 256 threads (us a call with 128 and 256: 528 rows of a plan 17.3 and 16.8, 624 20.3 and
+// 19.8, 864 31.1 and 30.9; general decode of 500 - 1000 rows even). With more rows there are enough loads in flight, and the extra waves cost: 2048
+// batched rows 55.3 and 55.7, 2048 plain ones 69.4 and 70.1. 512 threads: 0.1 - 0.2 us more for few partials, 0.1 less for 54.
+constexpr int kMergeThreads = 128, kMergeThreadsFew = 256, kMergeFewRows = 1024;
 
 // ml: [room][2], po: [room][D], out: the row; ns <= room partials exist (room is known before ns has been loaded, so the
 // first loads go by room).
 template <int D, int kThreads, typename Out>
 __device__ __forceinline__ void merge_row(const float* ml, const float* po, int room, int ns, Out* out) {
   constexpr int kCols = D / 4, kGroups = kThreads / kCols;
+  constexpr bool kAll = kThreads == kMergeThreadsFew;  // the rows of 64 partials at once
+  constexpr int kAhead = kAll ? 64 / kGroups : 2;
   __shared__ float4 num_s[kGroups][kCols];
   const int lane = threadIdx.x & 63, part = threadIdx.x / kCols, dq = threadIdx.x % kCols;
   const float2* ml2 = reinterpret_cast<const float2*>(ml);
@@ -66,14 +69,17 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
     }
   };
   float2 e = lane < room ? ml2[lane] : make_float2(-INFINITY, 0.f);
-  float4 a = part < room ? po4[(size_t)part * kCols] : make_float4(0.f, 0.f, 0.f, 0.f), b;
+  float4 x[kAhead];
+  x[0] = part < room ? po4[(size_t)part * kCols] : make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s0 = 0; s0 < ns; s0 += 64) {  // (one turn but for the longest contexts)
     int s = s0 + part;
     if (s0 > 0) {
       e = ml2[min(s0 + lane, ns - 1)];
-      a = row(s);
+      x[0] = row(s);
     }
-    b = row(s + kGroups);
+#pragma unroll
+    for (int i = 1; i < kAhead; ++i)
+      if (!kAll || s0 + i * kGroups < ns) x[i] = row(s + i * kGroups);
     if (s0 + lane >= ns) e = make_float2(-INFINITY, 0.f);
     const bool took = e.x != -INFINITY || e.y != 0.f;
     const int s_end = min(ns, s0 + 64);
@@ -87,12 +93,18 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
     const float w = took ? __builtin_amdgcn_exp2f(e.x - m) : -1.f;  // (NaN where all scores of the row are)
     den += wave_reduce(took ? w * e.y : 0.f, [](float x, float y) { return x + y; });
     // (every lane runs as many turns as the first group: the shuffles need all of them)
-    for (int i = s0; i < s_end; i += 2 * kGroups, s += 2 * kGroups) {
-      const float4 x = a, y = b;
-      a = row(s + 2 * kGroups);
-      b = row(s + 3 * kGroups);
-      add(x, __shfl(w, (s - s0) & 63));
-      add(y, __shfl(w, (s + kGroups - s0) & 63));
+    if constexpr (kAll) {
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i)
+        if (s0 + i * kGroups < ns) add(x[i], __shfl(w, part + i * kGroups));
+    } else {
+      for (int i = s0; i < s_end; i += 2 * kGroups, s += 2 * kGroups) {
+        const float4 u = x[0], v = x[1];
+        x[0] = row(s + 2 * kGroups);
+        x[1] = row(s + 3 * kGroups);
+        add(u, __shfl(w, (s - s0) & 63));
+        add(v, __shfl(w, (s + kGroups - s0) & 63));
+      }
     }
   }
   num_s[part][dq] = num;

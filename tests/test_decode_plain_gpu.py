@@ -167,3 +167,14 @@ def test_a_page_keeps_its_precision_beside_one_of_large_scores(mepic, oracle_att
     want = oracle_out(oracle_attn, case)
     for got in (DeviceCase(mepic, case).run(), run_in_long_runs(mepic, case, 16)):
         assert worst_row(got[..., :64], want[..., :64]) <= BOUND and worst_row(got, want) <= BOUND
+
+
+@pytest.mark.parametrize("B", [1, 40])
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 16, 17, 56, 57, 63, 64, 65, 72, 120, 129])
+def test_partials_of_a_row(mepic, oracle_attn, n, B):
+    """Rows of 1 to 129 partials (a step of 32 slots each where there are as many waves; else the most that 40 requests come to), merged
+    with 256 threads (8 rows) and, where there are more than 1024 rows, 128."""
+    Hkv = 8 if B == 1 else 4
+    case = build(1 if B == 1 else 7, Hkv, "bf16", 5e5, [32 * n - 5] * B, 300 + n, edges_count)
+    got, want = DeviceCase(mepic, case).run(), oracle_out(oracle_attn, case)
+    assert worst_row(got, want) <= ROW_BOUND
