@@ -233,6 +233,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   // (waves of one workgroup take parts far from each other: a call too small for all waves still uses all compute units)
   const int n_wg = (int)gridDim.x / Hkv, wk = wave * n_wg + (int)blockIdx.x / Hkv, n_k = n_wg * kWaves;
   int chunk = 0, pos_begin = 0, pos_end = 0;
+  int most_steps = 0;          // of a wave's run, in the whole call
   bool whole = false;          // every wave has one run: requests are cut into pieces of their own
   int upto = 0, piece = 0;     // whole: lane b: pieces of the requests up to b; the wave's piece of its request
   auto cut = [&]() __attribute__((always_inline)) {  // this wave's part of the sequence
@@ -257,6 +258,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
         if (whole) break;
       }
       if (whole) {
+        most_steps = uni(c);
         const int b = (int)__popcll(__ballot(upto <= wk));
         if (b < a.B) {
           const int k = __builtin_amdgcn_readlane(pieces, b), n = __builtin_amdgcn_readlane(steps, b);
@@ -269,6 +271,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
       }
     }
     if (!whole) {
+      most_steps = chunk;
       pos_begin = wk * chunk;
       pos_end = min(pos_begin + chunk, T);
     }
@@ -341,30 +344,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     cut();
     first_seg();
   }
-  for (int idx = wave; idx < kRotK + 8; idx += kWaves) {
-    const bool is_k = idx < kRotK;
-    const int i = is_k ? idx : idx - kRotK;
-    const int w = i & 3, h = is_k ? (kRot == 2 ? (i >> 2) & 1 : 0) : i >> 2;
-    const int uv = i / (4 * kRot);
-    const float pos = is_k ? (float)(n16 + 16 * (uv & 1) + kTurn * (uv >> 1)) : -(float)(kTurn * kNV);
-    const float2 f0 = freq_lds[kg * 16 + 8 * h + 2 * w], f1 = freq_lds[kg * 16 + 8 * h + 2 * w + 1];
-    const float t0 = turns_frac(pos, f0.x, f0.y);
-    const float t1 = turns_frac(pos, f1.x, f1.y);
-    const float4 r = make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1),
-                                 __builtin_amdgcn_sinf(t1));
-    if (!is_k) {
-      rotS[i][lane] = r;
-    } else if constexpr (kFp8) {  // {cos pair, sin pair} as packed fp16
-      rotK[i][lane] = make_float2(__uint_as_float(pack_f16x2(r.x, r.z)), __uint_as_float(pack_f16x2(r.y, r.w)));
-    } else {  // per pair the two constant words (cos, -sin) and (sin, cos) as packed bf16
-      rotK[i][lane] = make_float4(__uint_as_float(pack2_bf16(r.x, -r.y)), __uint_as_float(pack2_bf16(r.y, r.x)),
-                                  __uint_as_float(pack2_bf16(r.z, -r.w)), __uint_as_float(pack2_bf16(r.w, r.z)));
-    }
-  }
-  __syncthreads();
-
-  if (pos_begin >= pos_end) return;
-
   // ---- K and V of a step, one register buffer of either ----
   // K row n16 of product u is slot 16 u + n16 of the step: whole lines per load, a uniform base and a lane offset that never
   // changes. bf16: kf[u][j] = granule 4 j + kg of page u; fp8: granules kg and kg + 4 of the page.
@@ -397,6 +376,47 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
       for (int i = 0; i < kNVec; ++i) vf[s][i] = load_page<kReadOnce>(reinterpret_cast<const uint4*>(p + i * (kFp8 ? 1024 : 512)));
     }
   };
+
+  auto clean = [&](int id) { return safe_page(id, a.num_pages); };
+  float ks_cur = 1.f, vs_cur = 1.f, ks_nxt = 1.f, vs_nxt = 1.f;  // fp8: lane i: scales of the page of block i of the window
+  auto issue_first = [&]() __attribute__((always_inline)) {  // the run's first step
+    const int ids = clean(seg.bt0);
+    const int p0 = __builtin_amdgcn_readlane(ids, 0), p1 = kPack == 2 && seg.n_st == 1 ? p0 : __builtin_amdgcn_readlane(ids, kBps * kPack - 1);
+    if constexpr (kFp8) {
+      ks_cur = a.k_scales[ids];
+      vs_cur = a.v_scales[ids];
+    }
+    issue_k(p0, p1);
+    __builtin_amdgcn_sched_barrier(0);  // K before V on every path: the loop's waits count on it
+    issue_v(p0, p1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // ---- tables, as far as the call's longest run of a wave needs them: most_steps is the same for every wave. Where that is a step or
+  // two, building all of them was 1 us of the 7.5 before the merge: 4 requests of 1.7 K slots 11.8 -> 11.0 us a call, 30 of 800 e4m3
+  // slots 18.6 -> 16.9, a commit and 16 of 2.2 K (5 steps) 20.9 -> 20.7. (The first loads ahead of the tables: 11.6 and 21.7.) ----
+  const int turns = uni((most_steps + kPack - 1) / kPack);
+  auto entry = [&](float pos, int h, int w) __attribute__((always_inline)) {  // R(pos) of pairs 2 w and 2 w + 1 of half h
+    const float2 f0 = freq_lds[kg * 16 + 8 * h + 2 * w], f1 = freq_lds[kg * 16 + 8 * h + 2 * w + 1];
+    const float t0 = turns_frac(pos, f0.x, f0.y);
+    const float t1 = turns_frac(pos, f1.x, f1.y);
+    return make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1), __builtin_amdgcn_sinf(t1));
+  };
+  constexpr int kPerTable = 2 * kRot * 4;
+#pragma unroll
+  for (int base = 0; base < kRotK; base += kWaves) {
+    if (base / kPerTable >= turns) break;
+    const int i = base + wave, uv = i / (4 * kRot);
+    const float4 r = entry((float)(n16 + 16 * (uv & 1) + kTurn * (uv >> 1)), kRot == 2 ? (i >> 2) & 1 : 0, i & 3);
+    if constexpr (kFp8) {  // {cos pair, sin pair} as packed fp16
+      rotK[i][lane] = make_float2(__uint_as_float(pack_f16x2(r.x, r.z)), __uint_as_float(pack_f16x2(r.y, r.w)));
+    } else {  // per pair the two constant words (cos, -sin) and (sin, cos) as packed bf16
+      rotK[i][lane] = make_float4(__uint_as_float(pack2_bf16(r.x, -r.y)), __uint_as_float(pack2_bf16(r.y, r.x)),
+                                  __uint_as_float(pack2_bf16(r.z, -r.w)), __uint_as_float(pack2_bf16(r.w, r.z)));
+    }
+  }
+  if (turns > kNV) rotS[wave][lane] = entry(-(float)(kTurn * kNV), wave >> 2, wave & 3);
+  __syncthreads();
+  if (pos_begin >= pos_end) return;
 
   floatx4 o[8];
   floatx4 sc0;                 // minus the reference maximum (log2 units): what bf16 score accumulators start from
@@ -646,20 +666,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   };
 
   // ---- walk the wave's chunk request by request ----
-  auto clean = [&](int id) { return safe_page(id, a.num_pages); };
-  float ks_cur = 1.f, vs_cur = 1.f, ks_nxt = 1.f, vs_nxt = 1.f;  // fp8: lane i: scales of the page of block i of the window
-  auto issue_first = [&]() __attribute__((always_inline)) {  // the run's first step
-    const int ids = clean(seg.bt0);
-    const int p0 = __builtin_amdgcn_readlane(ids, 0), p1 = kPack == 2 && seg.n_st == 1 ? p0 : __builtin_amdgcn_readlane(ids, kBps * kPack - 1);
-    if constexpr (kFp8) {
-      ks_cur = a.k_scales[ids];
-      vs_cur = a.v_scales[ids];
-    }
-    issue_k(p0, p1);
-    __builtin_amdgcn_sched_barrier(0);  // K before V on every path: the loop's waits count on it
-    issue_v(p0, p1);
-    __builtin_amdgcn_sched_barrier(0);
-  };
   auto of_lane = [](float x, int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), i)); };
   uint64_t again = 0;  // terms: bit i: the wave's run i is to be computed again (63: every run from there on)
   int run = 0;
