@@ -142,15 +142,20 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
   const float qs = row_ok ? a.qk_scale_log2 : 0.f;
 
   // ---- rotation table, as far as a wave's run of slots can need it ----
-  const int n_tab = min(kTab, 16 * max(per_wave, 1));
+  // (to a power of two: 1 request of 289 slots 9.1 -> 8.9 us, 3 of 1.3 K, 12 heads of 64, 12.1 -> 11.7, against as many slots in a loop over all)
+  const int tab_bits = min(7, 4 + (per_wave > 1 ? 32 - __builtin_clz(per_wave - 1) : 0)), n_tab = 1 << tab_bits;
+  static_assert(kTab == 1 << 7, "");
   __syncthreads();
-  for (int i = tid; i < D / 4 * kTab; i += kThreads) {
-    const int c = i / kTab, s = i % kTab;
-    if (s >= n_tab) continue;
+  auto entry = [&](int c, int s) __attribute__((always_inline)) {
     const float t0 = turns_frac((float)s, freq[2 * c].x, freq[2 * c].y);
     const float t1 = turns_frac((float)s, freq[2 * c + 1].x, freq[2 * c + 1].y);
     tab[c][s] = make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1),
                             __builtin_amdgcn_sinf(t1));
+  };
+  if (n_tab == kTab) {  // (a number of turns that the compiler knows)
+    for (int i = tid; i < D / 4 * kTab; i += kThreads) entry(i / kTab, i % kTab);
+  } else {
+    for (int i = tid; i < D / 4 << tab_bits; i += kThreads) entry(i >> tab_bits, i & (n_tab - 1));
   }
   __syncthreads();
 

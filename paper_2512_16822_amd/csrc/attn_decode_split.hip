@@ -66,8 +66,10 @@ constexpr size_t lds_bytes() {
   return n < sizeof(ScalarLds<4, kThreads>) ? sizeof(ScalarLds<4, kThreads>) : n;
 }
 
-// kTurns: two workgroups a compute unit, which share its SIMDs (take_turns).
-template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, bool kTurns>
+// Kinds of calls, which have kernels of their own (what one adds to the loop or the start costs the others 1 - 2 %). kTurns: two
+// workgroups a compute unit, which share its SIMDs (take_turns). kBrief: workgroups of which some need a part of the table only, which build no more than that.
+enum Kind { kOrdinary, kTurns, kBrief };
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, Kind kKind>
 __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArgs a) {
   constexpr int kKs = D / 32;     // k-steps of 32 dims; granule of k-step j: dims 32 j + 8 kg ..
   constexpr int kNt = D / 16;     // output tiles of 16 dims
@@ -198,6 +200,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   }
 
   // ---- rotation table ----
+  // (brief runs: as far as they can need it, to a power of two)
+  constexpr int kTabBits = 31 - __builtin_clz(kTab);
+  const int tab_bits = kKind == kBrief ? min(kTabBits, 5 + (per_wave > 1 ? 32 - __builtin_clz(per_wave - 1) : 0)) : kTabBits, n_tab = 1 << tab_bits;
   __syncthreads();
   const float my_hi = freq[my_pair].x, my_lo = freq[my_pair].y;
   float my_f0 = a.qk_scale_log2, my_f1 = 0.f;  // factors of the two rows
@@ -215,13 +220,14 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       }
     }
   }
-  for (int i = tid; i < D / (kTerms ? 8 : 4) * kTab; i += kThreads) {
-    const int c = i / kTab, s = i % kTab;
+  constexpr int kPairs2 = D / (kTerms ? 8 : 4);  // pairs in the table, by two
+  auto entry = [&](int c, int s) __attribute__((always_inline)) {
     const float t0 = turns_frac((float)s, freq[2 * c].x, freq[2 * c].y);
     const float t1 = turns_frac((float)s, freq[2 * c + 1].x, freq[2 * c + 1].y);
     tab[c][s] = make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1),
                             __builtin_amdgcn_sinf(t1));
-  }
+  };
+  for (int i = tid; i < kPairs2 << tab_bits; i += kThreads) entry(i >> tab_bits, i & (n_tab - 1));
   __syncthreads();
 
   // Q' as the B operands. kTerms: qh / ql hold the first set of the slow half (pairs of granules 1 and 3), qh2 / ql2 the second.
@@ -350,7 +356,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   bool have_base = false;
   auto inside = [&](int ps) __attribute__((always_inline)) {
     const long d = (long)ps - base;
-    return d >= 0 && d <= kTab - 16;
+    return d >= 0 && d <= n_tab - 16;
   };
 
   // Softmax and output products of one turn; slots of the step outside vis0 / vis1 get no weight.
@@ -446,7 +452,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
 
   // K of the next step is requested as soon as the scores are done with the registers, V after its products; always, so
   // that the waits can count the loads in flight (past the last step the last pages come once more).
-  const bool later = kTurns && (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >= a.later_wg;
+  const bool later = kKind == kTurns && (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >= a.later_wg;
   for (int st = 0; st < n_st; ++st) {
     const int l0 = (2 * st) & 63;
     if (st > 0 && l0 == 0) {
@@ -473,7 +479,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     sc[1] = score(1, ps1 - base);
     __builtin_amdgcn_sched_barrier(0);
     issue_k(np0, np1);
-    if constexpr (kTurns) take_turns(later, st);
+    if constexpr (kKind == kTurns) take_turns(later, st);
     __builtin_amdgcn_sched_barrier(0);
     attend(sc, vis0, both ? vis1 : 0u, l0);
     if (!both && vis1) {  // the step's groups lie too far apart for one table: the second one takes a turn of its own
@@ -545,21 +551,28 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
                                                                   n_begin, s_end, split, direct);
 }
 
-template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, bool kTurns = false>
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, Kind kKind = kOrdinary>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
-  // Calls of one round of workgroups and of eight steps and more a wave take turns (64 requests of 4.2 K slots with masks, 34 steps a wave, 84.0 -> 80.2 us);
-  // with few steps what it adds to the loop is more than it gives: 2 requests of 1.2 K slots, D 64, 9.54 -> 9.75, 2 of 7 K on 2 heads, 7 steps a wave,
-  // 13.1 -> 13.3.
-  if constexpr (!kTurns && D == 128)
-    if (a.later_wg != INT_MAX && a.blocks_per_split * P >= 8 * 32 * kWaves) return launch_one<kFp8, D, P, kIL, kTerms, kTab, true>(a, s);
+  if constexpr (kKind == kOrdinary) {
+    // Calls of one round of workgroups and of eight steps and more a wave take turns (64 requests of 4.2 K slots with masks, 34 steps a wave, 84.0 -> 80.2 us);
+    // with few steps what it adds to the loop is more than it gives: 2 requests of 1.2 K slots, D 64, 9.54 -> 9.75, 2 of 7 K on 2 heads, 7 steps a wave,
+    // 13.1 -> 13.3.
+    if constexpr (D == 128)
+      if (a.later_wg != INT_MAX && a.blocks_per_split * P >= 8 * 32 * kWaves) return launch_one<kFp8, D, P, kIL, kTerms, kTab, kTurns>(a, s);
+    // The table was up to 1.5 us of the start. It is needed whole where requests are not cut, unless the bound on their lengths says otherwise; of
+    // several parts the last ones are short, or empty, which counts as long as the others are not much longer. us a call: 1 masked request of 3.9 K slots on 12 heads 12.9 -> 12.0, 2 of 7 K on 2 heads
+    // 13.0 -> 12.1, 2 of 1.2 K, D 64, 9.55 -> 9.16, 24 of 0.6 - 1.1 K e4m3 slots in three parts 22.2 -> 19.8; 53 of 484 slots, D 64, uncut, would be 11.26 -> 11.39.
+    // (11 requests of 2.4 - 5 K e4m3 slots of D 64, cut in two, would be 20.8 -> 21.2.)
+    if (a.blocks_per_split * P <= kTab / 2 * kWaves || (D == 128 && a.n_splits > 1 && a.blocks_per_split * P < 8 * 32 * kWaves)) return launch_one<kFp8, D, P, kIL, kTerms, kTab, kBrief>(a, s);
+  }
   constexpr size_t lds = lds_bytes<D, kTerms, kTab>();
   static std::atomic<uint64_t> asked{0};
-  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kTurns>), lds, asked);
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kKind>), lds, asked);
   if (status != hipSuccess) return status;
   // KV heads fastest (neighbours go to different dies, which then each keep their own heads' pages); tokens over x and y
   const unsigned per_row = (unsigned)min(a.n_q, max(65536 / a.Hkv, 1));
   const dim3 grid((unsigned)a.Hkv * per_row, ((unsigned)a.n_q + per_row - 1) / per_row, (unsigned)a.n_splits);
-  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kTurns>), grid, dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kKind>), grid, dim3(kThreads), lds, s, a);
   return hipGetLastError();
 }
 template <bool kFp8, int D, int P>

@@ -172,6 +172,25 @@ def test_block_positions_in_any_order(mepic, oracle_attn, P, prefill):
     check(mepic, oracle_attn, st, pads_are_positions=False, change=scatter)
 
 
+@pytest.mark.parametrize("length", [20, 32, 33, 100, 129, 200, 257, 300, 513, 900, 1100, 4200])
+@pytest.mark.parametrize("theta", [1e4, 5e5])
+@pytest.mark.parametrize("D,kv_dtype", [(64, "bf16"), (128, "bf16"), (128, "f8e4m3")])
+@pytest.mark.parametrize("B", [1, 60])
+def test_decode_tables(mepic, oracle_attn, B, D, kv_dtype, theta, length):
+    """Runs of one to thirty steps a wave, so rotation tables of every size and waves that take turns or not, the last requests much
+    shorter; positions that run on, and that jump by a step, by less than the whole table and by more."""
+    Hkv = 4 if B == 1 else 5  # (60 requests: 300 workgroups, more than compute units and less than twice as many)
+    st = W.Structure("tables", "decode", B, 2 * Hkv, Hkv, D, 16, theta, "bf16", kv_dtype, 52)
+    st.requests, st.n_q, st.extra_tail = [[(0, length if b % 7 else 1 + length // 5, 0)] for b in range(B)], [1] * B, 0
+
+    def jump(case):
+        for b in range(0, B, 2):
+            n = int(case.n_blocks[b])
+            case.block_positions[b, :n] = 16 * np.arange(n) + np.cumsum(np.array([0, 0, 0, 32, 0, 64, 0, 0, 120, 0, 300, 0])[np.arange(n) % 12])
+        case.q_positions[:] = case.q_positions + 3000
+    check(mepic, oracle_attn, st, pads_are_positions=False, change=jump)
+
+
 @pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
 def test_decode_non_finite_values(mepic, oracle_attn, kv_dtype):
     """Inf (fp8: the NaN code) in a visible V element reaches its dim of the rows that read it and nothing else."""
