@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     floatx4 sc;
     if constexpr (kFp8) sc = floatx4{0.f, 0.f, 0.f, 0.f};
     else sc = sc0;
-    const float4* tp = &tab[0][min(max(s0, 0), kTab - 16) + n16];
+    const float4* tp = &tab[0][min(max(s0, 0), n_tab - 16) + n16];
     auto three = [&](const Frag& kh, const Frag& kl, int j) __attribute__((always_inline)) {
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh.v, qh[j].v, sc, 0, 0, 0);
       sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh.v, ql[j].v, sc, 0, 0, 0);
