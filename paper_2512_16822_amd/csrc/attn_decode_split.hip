@@ -66,10 +66,9 @@ constexpr size_t lds_bytes() {
   return n < sizeof(ScalarLds<4, kThreads>) ? sizeof(ScalarLds<4, kThreads>) : n;
 }
 
-// Kinds of calls, which have kernels of their own (what one adds to the loop or the start costs the others 1 - 2 %). kTurns: two
-// workgroups a compute unit, which share its SIMDs (take_turns). kBrief: workgroups of which some need a part of the table only, which build no more than that.
-enum Kind { kOrdinary, kTurns, kBrief };
-template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, Kind kKind>
+// kLong: calls whose waves have eight steps and more. Their table is whole, its size a constant; with D 128 the two workgroups of a
+// compute unit share its SIMDs by turns (take_turns). In the others as much of the table is built as their groups of slots span.
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, bool kLong>
 __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArgs a) {
   constexpr int kKs = D / 32;     // k-steps of 32 dims; granule of k-step j: dims 32 j + 8 kg ..
   constexpr int kNt = D / 16;     // output tiles of 16 dims
@@ -84,6 +83,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   __shared__ __align__(16) float2 freq[D / 2];  // {hi, lo}: indexed per lane, which the kernel arguments are too slow for
   __shared__ float2 turn[kShare ? kWaves : 1][4][kRows][16];  // what Q' set-up shares: [wave][kg][row][pair] {cos, sin} times the row's factor
   __shared__ __align__(16) float ratio[2][32];   // [row][pair of the slow half]: the second set in units of the first
+  __shared__ __align__(16) int span[kWaves];     // slots that each wave's groups span
 
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), n16 = lane & 15, kg = lane >> 4;
   if (tid < D / 2) freq[tid] = make_float2(a.freq_hi[tid], a.freq_lo[tid]);
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
       w.vsc = a.v_scales[w.page];
     }
   };
-  Win cur, nxt;
+  Win cur{}, nxt;
   int win = 0;
   if (n_st > 0) {
     win_load(cur, 0);
@@ -199,10 +199,25 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     for (int j = 0; j < kKs; ++j) q_lds[j][lane] = head < G ? q4[4 * j + kg] : make_uint4(0, 0, 0, 0);  // (rows without a head are zeros)
   }
 
-  // ---- rotation table ----
-  // (brief runs: as far as they can need it, to a power of two)
-  constexpr int kTabBits = 31 - __builtin_clz(kTab);
-  const int tab_bits = kKind == kBrief ? min(kTabBits, 5 + (per_wave > 1 ? 32 - __builtin_clz(per_wave - 1) : 0)) : kTabBits, n_tab = 1 << tab_bits;
+  // ---- rotation table, 32 slots at a time ----
+  // Of calls of few steps, building it whole was up to 1.5 us of the start: there it goes as far as the groups of some wave span, gaps between
+  // them included as long as one table can hold them, since every group outside is a new base and a set-up of Q'. us a call, whole and
+  // so: 1 masked request of 3.9 K slots on 12 heads 13.75 and 12.65, 2 of 7 K on 2 heads 13.45 and 12.1 (with 16 slots left out after
+  // every 32 of them 13.4 and 12.2; by the length of the runs alone 13.85), 24 of 0.6 - 1.1 K e4m3 slots in three parts 22.15 and 20.05, 100 of 250
+  // 25.45 and 23.45, 2 of 1.2 K, D 64, 9.58 and 9.15. What it adds to calls that need the whole table all the same: nothing to 1 % (11
+  // requests of 2.4 - 5 K e4m3 slots, D 64, 20.8 and 21.0), 2 % in one form (e4m3, theta 1e4, 20 requests of 700 slots 17.9 and 18.25).
+  constexpr int kChunks = kTab / 32;
+  if constexpr (!kLong) {
+    // from the group before (16 groups, a row of lanes, are as many as there are in runs that do not need it whole); written as a sum
+    // because the difference, v_subrev_u32_dpp, came out with its sign turned
+    const uint32_t up = (uint32_t)cur.pos + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(0u - (uint32_t)cur.pos), 0x111, 0xf, 0xf, true);  // row_shr:1
+    int x = lane > 0 && lane < 2 * n_st && up <= kTab - 16 ? (int)up : 0;  // (a longer jump is a new base anyhow)
+    x += __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, true);  // row_ror:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, true);
+    if (lane == 0) span[wave] = x + 16;
+  }
   __syncthreads();
   const float my_hi = freq[my_pair].x, my_lo = freq[my_pair].y;
   float my_f0 = a.qk_scale_log2, my_f1 = 0.f;  // factors of the two rows
@@ -221,13 +236,25 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     }
   }
   constexpr int kPairs2 = D / (kTerms ? 8 : 4);  // pairs in the table, by two
-  auto entry = [&](int c, int s) __attribute__((always_inline)) {
-    const float t0 = turns_frac((float)s, freq[2 * c].x, freq[2 * c].y);
-    const float t1 = turns_frac((float)s, freq[2 * c + 1].x, freq[2 * c + 1].y);
-    tab[c][s] = make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1),
-                            __builtin_amdgcn_sinf(t1));
+  constexpr int kOwn = kPairs2 * 32 / kThreads;  // a thread's entries of 32 slots: columns tid / 32 + 8 k
+  float4 f[kOwn];
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) f[k] = *reinterpret_cast<const float4*>(&freq[2 * (tid / 32 + 8 * k)]);
+  auto build = [&](int chunk) __attribute__((always_inline)) {
+    const int s = 32 * chunk + tid % 32;
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      const float t0 = turns_frac((float)s, f[k].x, f[k].y), t1 = turns_frac((float)s, f[k].z, f[k].w);
+      tab[tid / 32 + 8 * k][s] = make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1),
+                                             __builtin_amdgcn_sinf(t1));
+    }
   };
-  for (int i = tid; i < kPairs2 << tab_bits; i += kThreads) entry(i >> tab_bits, i & (n_tab - 1));
+  build(0);
+  int n_chunks = kChunks;
+  if constexpr (!kLong) n_chunks = max(1, min(max(per_wave, uni(max(max(span[0], span[1]), max(span[2], span[3])) + 31) / 32), kChunks));
+  const int n_tab = 32 * n_chunks;
+#pragma unroll 1
+  for (int i = 1; i < n_chunks; ++i) build(i);
   __syncthreads();
 
   // Q' as the B operands. kTerms: qh / ql hold the first set of the slow half (pairs of granules 1 and 3), qh2 / ql2 the second.
@@ -452,7 +479,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
 
   // K of the next step is requested as soon as the scores are done with the registers, V after its products; always, so
   // that the waits can count the loads in flight (past the last step the last pages come once more).
-  const bool later = kKind == kTurns && (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >= a.later_wg;
+  const bool later = kLong && D == 128 && (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >= a.later_wg;
   for (int st = 0; st < n_st; ++st) {
     const int l0 = (2 * st) & 63;
     if (st > 0 && l0 == 0) {
@@ -479,7 +506,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     sc[1] = score(1, ps1 - base);
     __builtin_amdgcn_sched_barrier(0);
     issue_k(np0, np1);
-    if constexpr (kKind == kTurns) take_turns(later, st);
+    if constexpr (kLong && D == 128) take_turns(later, st);
     __builtin_amdgcn_sched_barrier(0);
     attend(sc, vis0, both ? vis1 : 0u, l0);
     if (!both && vis1) {  // the step's groups lie too far apart for one table: the second one takes a turn of its own
@@ -551,28 +578,21 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
                                                                   n_begin, s_end, split, direct);
 }
 
-template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, Kind kKind = kOrdinary>
+template <bool kFp8, int D, int P, bool kIL, bool kTerms, int kTab, bool kLong = false>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
-  if constexpr (kKind == kOrdinary) {
-    // Calls of one round of workgroups and of eight steps and more a wave take turns (64 requests of 4.2 K slots with masks, 34 steps a wave, 84.0 -> 80.2 us);
-    // with few steps what it adds to the loop is more than it gives: 2 requests of 1.2 K slots, D 64, 9.54 -> 9.75, 2 of 7 K on 2 heads, 7 steps a wave,
-    // 13.1 -> 13.3.
-    if constexpr (D == 128)
-      if (a.later_wg != INT_MAX && a.blocks_per_split * P >= 8 * 32 * kWaves) return launch_one<kFp8, D, P, kIL, kTerms, kTab, kTurns>(a, s);
-    // The table was up to 1.5 us of the start. It is needed whole where requests are not cut, unless the bound on their lengths says otherwise; of
-    // several parts the last ones are short, or empty, which counts as long as the others are not much longer. us a call: 1 masked request of 3.9 K slots on 12 heads 12.9 -> 12.0, 2 of 7 K on 2 heads
-    // 13.0 -> 12.1, 2 of 1.2 K, D 64, 9.55 -> 9.16, 24 of 0.6 - 1.1 K e4m3 slots in three parts 22.2 -> 19.8; 53 of 484 slots, D 64, uncut, would be 11.26 -> 11.39.
-    // (11 requests of 2.4 - 5 K e4m3 slots of D 64, cut in two, would be 20.8 -> 21.2.)
-    if (a.blocks_per_split * P <= kTab / 2 * kWaves || (D == 128 && a.n_splits > 1 && a.blocks_per_split * P < 8 * 32 * kWaves)) return launch_one<kFp8, D, P, kIL, kTerms, kTab, kBrief>(a, s);
-  }
+  // From eight steps a wave on turns are worth what they add to the loop (64 requests of 4.2 K slots with masks, 34 steps a wave, 84.0 -> 80.2 us;
+  // 2 of 7 K on 2 heads, 7 steps, 13.1 -> 13.3, 2 of 1.2 K, D 64, 9.54 -> 9.75), and every run that is not a request's last needs the whole
+  // table: as a constant 56.3 us for 64 requests of 4.2 K slots, D 64, as a number known to the kernel only 56.9.
+  if constexpr (!kLong)
+    if (a.blocks_per_split * P >= 8 * 32 * kWaves) return launch_one<kFp8, D, P, kIL, kTerms, kTab, true>(a, s);
   constexpr size_t lds = lds_bytes<D, kTerms, kTab>();
   static std::atomic<uint64_t> asked{0};
-  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kKind>), lds, asked);
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kLong>), lds, asked);
   if (status != hipSuccess) return status;
   // KV heads fastest (neighbours go to different dies, which then each keep their own heads' pages); tokens over x and y
   const unsigned per_row = (unsigned)min(a.n_q, max(65536 / a.Hkv, 1));
   const dim3 grid((unsigned)a.Hkv * per_row, ((unsigned)a.n_q + per_row - 1) / per_row, (unsigned)a.n_splits);
-  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kKind>), grid, dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((decode_split_kernel<kFp8, D, P, kIL, kTerms, kTab, kLong>), grid, dim3(kThreads), lds, s, a);
   return hipGetLastError();
 }
 template <bool kFp8, int D, int P>
@@ -597,9 +617,7 @@ hipError_t launch_kv(const AttnArgs& a, hipStream_t s) {
 
 hipError_t launch_decode_split(const AttnArgs& args, hipStream_t s) {
   AttnArgs a = args;
-  // Turns: up to two workgroups a compute unit in one round; of more, which one is the later changes as they end. Not where the caller says that
-  // pages are not shared: HBM sets the time there, and the two workgroups' loads come less evenly (64 private requests of 2.1 and 4.2 K slots
-  // 92.5 and 178.6 us, by turns 94.4 and 184.6; shared ones 4 % faster by turns).
+  // up to two workgroups a compute unit in one round; of more, which one is the later changes as they end
   const long cus = device_compute_units(), n_wg = (long)a.n_q * a.Hkv * a.n_splits;
   a.later_wg = n_wg > cus && n_wg <= 2 * cus && !a.kv_read_once ? (int)cus : INT_MAX;
   return a.kv_dtype == MEPIC_F8E4M3 ? launch_kv<true>(a, s) : launch_kv<false>(a, s);

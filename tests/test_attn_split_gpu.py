@@ -172,23 +172,40 @@ def test_block_positions_in_any_order(mepic, oracle_attn, P, prefill):
     check(mepic, oracle_attn, st, pads_are_positions=False, change=scatter)
 
 
-@pytest.mark.parametrize("length", [20, 32, 33, 100, 129, 200, 257, 300, 513, 900, 1100, 4200])
-@pytest.mark.parametrize("theta", [1e4, 5e5])
-@pytest.mark.parametrize("D,kv_dtype", [(64, "bf16"), (128, "bf16"), (128, "f8e4m3")])
-@pytest.mark.parametrize("B", [1, 60])
-def test_decode_tables(mepic, oracle_attn, B, D, kv_dtype, theta, length):
-    """Runs of one to thirty steps a wave, so rotation tables of every size and waves that take turns or not, the last requests much
-    shorter; positions that run on, and that jump by a step, by less than the whole table and by more."""
-    Hkv = 4 if B == 1 else 5  # (60 requests: 300 workgroups, more than compute units and less than twice as many)
-    st = W.Structure("tables", "decode", B, 2 * Hkv, Hkv, D, 16, theta, "bf16", kv_dtype, 52)
-    st.requests, st.n_q, st.extra_tail = [[(0, length if b % 7 else 1 + length // 5, 0)] for b in range(B)], [1] * B, 0
+def spread_blocks(case):
+    """Of every three requests one whose block positions jump by a step, by less than the whole rotation table and by more, one with 16
+    slots left out after every second block, and one without gaps."""
+    P, n_all = case.st.P, case.block_positions.shape[1]
+    steps = np.array([0, 0, 0, 32, 0, 64, 0, 0, 120, 0, 300, 0])[np.arange(n_all) % 12]
+    for b in range(case.st.B):
+        n = int(case.n_blocks[b])
+        gaps = (np.cumsum(steps), 16 * (np.arange(n_all) // 2), np.zeros(n_all, dtype=np.int64))[(b + n) % 3]
+        case.block_positions[b, :n] = (P * np.arange(n_all) + gaps)[:n]
+    case.q_positions[:] = case.q_positions + 3000
 
-    def jump(case):
-        for b in range(0, B, 2):
-            n = int(case.n_blocks[b])
-            case.block_positions[b, :n] = 16 * np.arange(n) + np.cumsum(np.array([0, 0, 0, 32, 0, 64, 0, 0, 120, 0, 300, 0])[np.arange(n) % 12])
-        case.q_positions[:] = case.q_positions + 3000
-    check(mepic, oracle_attn, st, pads_are_positions=False, change=jump)
+
+def one_length_in_seven_short(name, B, Hkv, length, **kw):
+    st = W.Structure(name, "decode", B, 2 * Hkv, Hkv, **kw)
+    st.requests, st.n_q, st.extra_tail = [[(0, length if b % 7 < 6 else 1 + length // 5, 0)] for b in range(B)], [1] * B, 0
+    return st
+
+
+@pytest.mark.parametrize("B,Hkv,length", [
+    (1, 4, 20), (1, 4, 32), (1, 4, 33), (1, 4, 129), (1, 4, 300), (1, 4, 513),  # uncut, 1 1 1 2 3 5 steps a wave
+    (1, 4, 900), (1, 4, 4200),                                                  # four parts and seventeen of two steps a wave
+    (60, 3, 1000), (60, 3, 1250), (60, 3, 1600), (60, 3, 2000), (60, 3, 2400),  # three parts of 3, 4, 5, 6, 7 steps
+    (60, 3, 2800), (60, 5, 4200),      # three of 8, two of 17; more than two workgroups a compute unit, so no turns
+    (60, 5, 700), (60, 5, 900), (60, 5, 1100),  # uncut, 300 workgroups: 6 steps, and by turns 8 and 9
+    (32, 4, 4000),                     # four parts of 8 steps, 512 workgroups: by turns
+])
+@pytest.mark.parametrize("D,P,kv_dtype,theta,interleaved", [
+    (64, 16, "bf16", 1e4, False), (128, 16, "bf16", 1e4, False), (128, 16, "bf16", 2e5, False), (128, 16, "bf16", 5e5, False),
+    (128, 32, "f8e4m3", 1e4, False), (128, 32, "f8e4m3", 5e5, False), (128, 16, "bf16", 5e5, True)])
+def test_decode_tables(mepic, oracle_attn, D, P, kv_dtype, theta, interleaved, B, Hkv, length):
+    """Rotation tables of every size, of 128 slots and of 256, for runs with and without gaps; with many requests, one in seven so much
+    shorter than the others that its last parts are short or empty. The steps of a wave and the workgroups are those of 256 compute units."""
+    st = one_length_in_seven_short("tables", B, Hkv, length, D=D, P=P, theta=theta, q_dtype="bf16", kv_dtype=kv_dtype, seed=52)
+    check(mepic, oracle_attn, st, pads_are_positions=False, interleaved=interleaved, change=spread_blocks)
 
 
 @pytest.mark.parametrize("kv_dtype", ["bf16", "f8e4m3"])
