@@ -668,7 +668,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
   // ---- walk the wave's chunk request by request ----
   auto of_lane = [](float x, int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), i)); };
   uint64_t again = 0;  // terms: bit i: the wave's run i is to be computed again (63: every run from there on)
-  int run = 0;
+  int run = 0, turn = 0;
+  const bool later = wave >= kWaves / 2;
   issue_first();
   for (;;) {
     const int b = seg.b, c0 = seg.c0, n_st = seg.n_st, step_first = seg.step_first, L = seg.L;
@@ -717,7 +718,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     const int n_turns = (n_st + kPack - 1) / kPack;
     int v = 0;
     for (int t = 0; t < n_turns - 1; ++t) {
-      take_turns(wave >= kWaves / 2, t);
+      take_turns(later, turn++);
       const int here = (kBpt * t) & 63, rel = (kBpt * (t + 1)) & 63;  // blocks of this and the next turn in their windows
       float ksc = 1.f, vs0 = 1.f, vs1 = 1.f;
       if constexpr (kFp8) {

@@ -26,11 +26,15 @@ __device__ __forceinline__ int sload(const int32_t* p, size_t idx) {
 }
 
 // Two waves share a SIMD here, and the one that came first gets every issue slot that both want: with equal parts of the work it is done
-// first, and the other goes on alone with nothing to fill its waits. So the later one is preferred in five of every eight turns: of 128
-// requests of 2 - 33 K e4m3 slots, plain decode, the first waves end after 132 us and the others after 177; so preferred all after 159 - 169, and the call
-// takes 174 us, not 181. 64 requests of 4.3 K bf16 slots 70.6 -> 69.2, with masks 84.0 -> 80.2; 16 of 2.2 K behind a commit 21.4 -> 21.2.
-// (Half and three quarters of the turns, by ones, gain 1 - 2 % less; a whole preference turns the sides round. Progress
-// compared through LDS ends them together too, but in step with each other: nothing gained, 0.9 us lost on the last.)
+// first, and the other goes on alone with nothing to fill its waits. So the later one is preferred in five of every eight turns, which the
+// caller counts through the wave's work: of 128 requests of 2 - 33 K e4m3 slots, plain decode, the first waves end after 132 us and the
+// others after 177; so preferred all after 159 - 169, and the call takes 174 us, not 181. 64 requests of 4.3 K bf16 slots 70.6 -> 69.2, with
+// masks 84.0 -> 80.2; 16 of 2.2 K behind a commit 21.4 -> 21.2. (Half and three quarters of the turns, by ones, gain 1 - 2 % less; a
+// preference in all of many turns turns the sides round. Progress compared through LDS ends them together too, but in step with each
+// other: nothing gained, 0.9 us lost on the last.) A wave of up to five turns is preferred in all of them, which in plain decode is
+// worth as much: us a call without and with, 100 requests of 0.3 - 1 K bf16 slots 24.95 and 24.2, e4m3 20.6 and 20.3, 30 of 0.5 - 1 K e4m3 slots
+// 14.35 and 13.8; the most it cost there is 1 % (128 of 0.3 - 1 K on 4 KV heads 21.8 and 22.0). Counted afresh for every run, though, waves of
+// several short runs had it throughout: 500 requests of 100 - 300 slots 59.05, without turns 58.4, counted through 57.9.
 // (s_setprio takes constants only. The branch between two is out of the compiler's sight: as one of its own it cost general decode calls
 // of few steps 0.2 us, taken or not.)
 __device__ __forceinline__ void take_turns(bool later, int turn) {
