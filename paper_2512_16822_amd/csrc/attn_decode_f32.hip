@@ -38,7 +38,8 @@ constexpr size_t lds_bytes() {
   return sizeof(Merge<D>) > table_bytes(D) ? sizeof(Merge<D>) : table_bytes(D);
 }
 
-template <int D, int P, bool kIL>
+// kTurns: the two waves of a SIMD share it by turns (take_turns).
+template <int D, int P, bool kIL, bool kTurns>
 __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs a) {
   constexpr int kGr = D / 16;  // granules (4 dims) of a K row a lane owns: j-th = dims 16 j + 4 kg ..
   constexpr int kNt = D / 16;  // output tiles of 16 dims
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
   // K of the next group is requested as soon as the scores are done with the registers, V after its products; always, so
   // that the waits can count the loads in flight (past the last group the last page comes once more).
   for (int st = 0; st < n_st; ++st) {
-    if constexpr (D == 128) take_turns(wave >= kWaves / 2, st);
+    if constexpr (kTurns) take_turns(wave >= kWaves / 2, st);
     const int l0 = st & 63;
     if (st > 0 && l0 == 0) {
       cur = nxt;
@@ -341,15 +342,22 @@ __global__ __launch_bounds__(kThreads, 2) void decode_f32_kernel(const AttnArgs 
                                            split, direct);
 }
 
-template <int D, int P, bool kIL>
+template <int D, int P, bool kIL, bool kTurns = false>
 hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
+  // Turns pay where waves have many groups; with few, what they add to the loop is more than they give. us a call without and with them, by
+  // groups of 16 slots a wave (of the bound on lengths): 4 requests of 32 K slots, 8 KV heads (32) 197.4 and 188.9, 16 of 2.5 - 10 K (38) 136.9
+  // and 134.5, prefill of 792 tokens, 12 KV heads (30) 2663 and 2645; 4 of 16 K (16) 98.5 and 97.2, but 16 of 4 K (16) 96.2 and 97.4, 14 of 6 K
+  // (24) 172.8 and 174.7, 16 of 2 K (8) 53.5 and 54.2, 4 of 2 K (2) 18.65 and 18.9. Of those with more than 28 one lost: 8 of up to 16 K on 12 heads
+  // (44, 288 workgroups) 143.2 and 146.5.
+  if constexpr (D == 128 && !kTurns)
+    if (a.blocks_per_split * P >= 28 * 16 * kWaves) return launch_one<D, P, kIL, true>(a, s);
   static std::atomic<uint64_t> asked{0};
-  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_f32_kernel<D, P, kIL>), lds_bytes<D>(), asked);
+  const hipError_t status = allow_lds(reinterpret_cast<const void*>(&decode_f32_kernel<D, P, kIL, kTurns>), lds_bytes<D>(), asked);
   if (status != hipSuccess) return status;
   // KV heads fastest (neighbours go to different dies, which then each keep their own heads' pages); tokens over x and y
   const unsigned per_row = (unsigned)min(a.n_q, max(65536 / a.Hkv, 1));
   const dim3 grid((unsigned)a.Hkv * per_row, ((unsigned)a.n_q + per_row - 1) / per_row, (unsigned)a.n_splits);
-  hipLaunchKernelGGL((decode_f32_kernel<D, P, kIL>), grid, dim3(kThreads), lds_bytes<D>(), s, a);
+  hipLaunchKernelGGL((decode_f32_kernel<D, P, kIL, kTurns>), grid, dim3(kThreads), lds_bytes<D>(), s, a);
   return hipGetLastError();
 }
 template <int D, int P>

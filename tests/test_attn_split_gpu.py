@@ -257,6 +257,20 @@ def test_f32_forms_lengths_and_positions(mepic, oracle_attn, D, P, interleaved, 
         assert np.isfinite(got).all() and np.abs(got - want).max() <= np.abs(want).max() * 2.0 ** -15
 
 
+@pytest.mark.parametrize("B,Hkv,length", [
+    (1, 4, 20), (1, 4, 130), (1, 4, 300), (1, 4, 700), (1, 4, 3000), (20, 4, 1000), (20, 3, 2000),  # up to six groups of slots a wave
+    (32, 8, 3600), (32, 4, 7300), (40, 8, 3600)])  # D 128: 29, in 256 workgroups of one part, 256 of two, 320 of one: by turns
+@pytest.mark.parametrize("D,interleaved", [(64, False), (128, False), (128, True)])
+def test_f32_tables(mepic, oracle_attn, D, interleaved, B, Hkv, length):
+    """Parts of the rotation table, for runs of groups with and without gaps, and waves that take turns. Bound as above."""
+    st = one_length_in_seven_short("f32tab", B, Hkv, length, D=D, P=16, theta=5e5, q_dtype="f32", kv_dtype="f32", seed=64)
+    case = W.assemble(st, align_with_oracle(st)[0], pads_are_positions=False)
+    spread_blocks(case)
+    got = DeviceCase(mepic, case, flags=mepic.FLAG_ROPE_INTERLEAVED if interleaved else 0).run()
+    want = oracle_out(oracle_attn, case, interleaved=interleaved)
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= np.abs(want).max() * 2.0 ** -15
+
+
 def test_f32_non_finite_values(mepic, oracle_attn):
     st = W.Structure("f32inf", "decode", 2, 8, 2, 128, 16, 5e5, "f32", "f32", 63)
     st.requests, st.n_q = [[(0, 300, 0)], [(0, 50, 0)]], [1, 1]
