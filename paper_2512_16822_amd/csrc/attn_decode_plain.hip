@@ -402,6 +402,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     return make_float4(__builtin_amdgcn_cosf(t0), __builtin_amdgcn_sinf(t0), __builtin_amdgcn_cosf(t1), __builtin_amdgcn_sinf(t1));
   };
   constexpr int kPerTable = 2 * kRot * 4;
+  static_assert(kWaves == 8 && kPerTable % kWaves == 0 && kRotK % kPerTable == 0, "a pass of the waves stays in one table, and is all of rotS");
 #pragma unroll
   for (int base = 0; base < kRotK; base += kWaves) {
     if (base / kPerTable >= turns) break;

@@ -56,6 +56,7 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
   constexpr int kCols = D / 4, kGroups = kThreads / kCols;
   constexpr bool kAll = kThreads == kMergeThreadsFew;  // the rows of 64 partials at once
   constexpr int kAhead = kAll ? 64 / kGroups : 2;
+  static_assert(kThreads % kCols == 0 && 64 % kGroups == 0, "the groups take the 64 partials of a turn in whole rounds");
   __shared__ float4 num_s[kGroups][kCols];
   const int lane = threadIdx.x & 63, part = threadIdx.x / kCols, dq = threadIdx.x % kCols;
   const float2* ml2 = reinterpret_cast<const float2*>(ml);
