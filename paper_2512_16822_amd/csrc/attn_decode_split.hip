@@ -200,8 +200,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   }
 
   // ---- rotation table, 32 slots at a time ----
-  // Of calls of few steps, building it whole was up to 1.5 us of the start: there it goes as far as the groups of some wave span, gaps between
-  // them included as long as one table can hold them, since every group outside is a new base and a set-up of Q'. us a call, whole and
+  // Of calls of few steps, building it whole was up to 1.5 us of the start: there it goes as far as the groups of some wave span, gaps of up
+  // to half a table included, since every group outside is a new base and a set-up of Q' (longer gaps are that however long the table is: with 200
+  // slots left out after every 48, 2 requests of 7 K on 2 heads 14.3 us if they count, 13.8 if not). us a call, whole and
   // so: 1 masked request of 3.9 K slots on 12 heads 13.75 and 12.65, 2 of 7 K on 2 heads 13.45 and 12.1 (with 16 slots left out after
   // every 32 of them 13.4 and 12.2; by the length of the runs alone 13.85), 24 of 0.6 - 1.1 K e4m3 slots in three parts 22.15 and 20.05, 100 of 250
   // 25.45 and 23.45, 2 of 1.2 K, D 64, 9.58 and 9.15. What it adds to calls that need the whole table all the same: nothing to 1 % (11
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
     // from the group before (16 groups, a row of lanes, are as many as there are in runs that do not need it whole); written as a sum
     // because the difference, v_subrev_u32_dpp, came out with its sign turned
     const uint32_t up = (uint32_t)cur.pos + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(0u - (uint32_t)cur.pos), 0x111, 0xf, 0xf, true);  // row_shr:1
-    int x = lane > 0 && lane < 2 * n_st && up <= kTab - 16 ? (int)up : 0;  // (a longer jump is a new base anyhow)
+    int x = lane > 0 && lane < 2 * n_st && up <= kTab / 2 ? (int)up : 0;
     x += __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, true);  // row_ror:1, 2, 4, 8
     x += __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, true);
     x += __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, true);
