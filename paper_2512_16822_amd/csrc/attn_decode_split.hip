@@ -205,8 +205,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   // slots left out after every 48, 2 requests of 7 K on 2 heads 14.3 us if they count, 13.8 if not). us a call, whole and
   // so: 1 masked request of 3.9 K slots on 12 heads 13.75 and 12.65, 2 of 7 K on 2 heads 13.45 and 12.1 (with 16 slots left out after
   // every 32 of them 13.4 and 12.2; by the length of the runs alone 13.85), 24 of 0.6 - 1.1 K e4m3 slots in three parts 22.15 and 20.05, 100 of 250
-  // 25.45 and 23.45, 2 of 1.2 K, D 64, 9.58 and 9.15. What it adds to calls that need the whole table all the same: nothing to 1 % (11
-  // requests of 2.4 - 5 K e4m3 slots, D 64, 20.8 and 21.0), 2 % in one form (e4m3, theta 1e4, 20 requests of 700 slots 17.9 and 18.25).
+  // 25.45 and 23.3, 2 of 1.2 K, D 64, 9.58 and 9.2. What it adds to calls that need the whole table all the same is within 0.5 % (11 requests
+  // of 2.4 - 5 K e4m3 slots, D 64, 20.85 and 20.95), 1 % in one form (e4m3, theta 1e4, 20 requests of 700 slots 17.9 and 18.1).
   constexpr int kChunks = kTab / 32;
   if constexpr (!kLong) {
     // from the group before (16 groups, a row of lanes, are as many as there are in runs that do not need it whole); written as a sum
@@ -383,8 +383,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   int base = 0;
   bool have_base = false;
   auto inside = [&](int ps) __attribute__((always_inline)) {
-    const long d = (long)ps - base;
-    return d >= 0 && d <= n_tab - 16;
+    return (uint64_t)((long)ps - base) <= (uint64_t)(n_tab - 16);  // (not below 0 either; one comparison)
   };
 
   // Softmax and output products of one turn; slots of the step outside vis0 / vis1 get no weight.
