@@ -1,6 +1,7 @@
 """The general path's matrix-core kernels (split precision) against the fp64 oracle: every form they take, at the edges of their
-tiles, on values of unit variance (large ones: test_split_precision_gpu.py). Their error there is the output's own rounding to bf16 (half an ulp of an 8-bit significand,
-2^-8 of the value) plus a remainder of the operands' 2^-18 terms, bounded here by 2^-13 of the largest output."""
+tiles, on values of unit variance (large ones: test_split_precision_gpu.py). Their error there is the output's own rounding to bf16
+(half an ulp of an 8-bit significand, 2^-8 of the value) plus a remainder of the operands' 2^-18 terms, bounded here by 2^-13 of the
+largest output."""
 import ctypes
 
 import numpy as np
@@ -269,6 +270,24 @@ def test_f32_tables(mepic, oracle_attn, D, interleaved, B, Hkv, length):
     got = DeviceCase(mepic, case, flags=mepic.FLAG_ROPE_INTERLEAVED if interleaved else 0).run()
     want = oracle_out(oracle_attn, case, interleaved=interleaved)
     assert np.isfinite(got).all() and np.abs(got - want).max() <= np.abs(want).max() * 2.0 ** -15
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_parts", [63, 64, 65, 130])
+def test_many_partials_of_a_row(mepic, oracle_attn, n_parts, dtype, D):
+    """One request on one KV head, cut into parts of 256 slots: rows of fewer partials than a turn of the merge takes (64), of as many,
+    one more and over two turns, with 256 threads (8 rows)."""
+    st = W.Structure("parts", "decode", 1, 8, 1, D, 16, 5e5, dtype, dtype, 65)
+    st.requests, st.n_q, st.extra_tail = [[(0, 256 * n_parts - 5, 0)]], [1], 0
+    case = W.assemble(st, align_with_oracle(st)[0])
+    dc = DeviceCase(mepic, case, flags=mepic.FLAG_FORCE_GENERAL)
+    assert dc.params.workspace_bytes >= n_parts * st.Hq * (D + 2) * 4
+    got, want = dc.run(), oracle_out(oracle_attn, case)
+    if dtype == "bf16":
+        within_output_rounding(got, want)
+    else:
+        assert np.abs(got - want).max() <= np.abs(want).max() * 2.0 ** -15
 
 
 def test_f32_non_finite_values(mepic, oracle_attn):
