@@ -11,8 +11,8 @@
 //
 // Small calls are what fp32 pages are used for (bring-up, verification): the kernel is arranged for latency. K and V of the
 // first groups are on their way while the table is built, eight waves share a split, and contexts too short for a
-// second split need no merge kernel. 1 request of 289 slots, 8 heads of 64 dims: 17.4 us (scalar body) -> 9.1 us a call; 1 of
-// 1 K slots, 32 heads on 8, 128 dims: 57 -> 15 us; 16 of 2.5 - 10 K private slots 405 -> 153 us (5.9 TB/s). The error
+// second split need no merge kernel. 1 request of 289 slots, 8 heads of 64 dims: 17.4 us (scalar body) -> 8.9 us a call; 1 of
+// 1 K slots, 32 heads on 8, 128 dims: 57 -> 14.3 us; 16 of 2.5 - 10 K private slots 153 -> 135 us (4.9 K in the mean). The error
 // against 64 bits is a tenth of the scalar kernel's (2.4e-7 and 2.4e-6 on the first): shorter chains of sums, phases.
 //
 // A NaN or Inf in the merged result sends the workgroup through the scalar body (values near the largest float, times

@@ -40,10 +40,11 @@
 // into two e4m3 terms (p*16 = hi + lo, 8 significant bits together down to p = 2^-7); the page's V scale rides on the probabilities, O
 // being kept in units of a reference scale that is raised (with a rescale of O) only when a page's scale exceeds it by 1.75 x.
 //
-// What bounds it. Where pages are read once, HBM: 8 requests of 65 537 bf16 slots with the read-once hint 320 us = 6.7 TB/s (two requests' worth
-// of waves side by side on a unit: 332). Where requests share pages, what misses L2: 64 requests of 4.3 K slots ask L1 for 1.13 GB (33 us at a
-// line a two clocks on every unit), of which 0.36 GB miss L2, and those come at 6 - 7 TB/s whether from HBM or the Infinity Cache:
-// 81.5 -> 71.2 us a call (47 with every page in L2); 128 requests of 2 - 33 K fp8 slots 212 -> 184 us. Measured and of no use there: requesting two or
+// What bounds it. Where pages are read once, HBM: 8 requests of 65 537 bf16 slots with the read-once hint 315 us = 6.8 TB/s (320 before a
+// SIMD's waves took turns, 332 with two requests' worth of waves side by side on a unit). Where requests share pages, what misses L2: 64
+// requests of 4.3 K slots ask L1 for 1.13 GB (33 us at a line a two clocks on every unit), of which 0.36 GB miss L2, and those come at 6 - 7
+// TB/s whether from HBM or the Infinity Cache: 81.5 -> 69 us a call (47 with every page in L2); 128 requests of 2 - 33 K fp8 slots 212 ->
+// 172 - 182 us from card to card. Measured and of no use there: requesting two or
 // three steps ahead by touching a word of every line (the lines are gone from the 32 KB of L1 again: 102 - 112 us), the
 // non-temporal hint for pages of few readers (misses 0.36 -> 0.30 GB, but those then always come from HBM: 78 - 94 us).
 #include "decode_common.h"
@@ -676,8 +677,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_plain_kernel(const Attn
     const int b = seg.b, c0 = seg.c0, n_st = seg.n_st, step_first = seg.step_first, L = seg.L;
     const int j0 = kBps * step_first, jend = min((L + kP - 1) / kP, j0 + kBps * n_st);
     const size_t bt_row = (size_t)b * a.max_blocks;
-    // Page ids of the run: lane i of bt_cur holds the page of block 64 k + i of the run (clamped to its last block), bt_nxt the 64 after those as stored; a step reads its ids with v_readlane. Vector loads on purpose: scalar
-    // loads share a counter with the LDS reads, so every wait for a rotation constant would also wait for them.
+    // Page ids of the run: lane i of bt_cur holds the page of block 64 k + i of the run (clamped to its last block), bt_nxt the 64 after those
+    // as stored; a step reads its ids with v_readlane. Vector loads on purpose: scalar loads share a counter with the LDS reads, so every
+    // wait for a rotation constant would also wait for them.
     int bt_cur = clean(seg.bt0), bt_nxt = seg.bt1;
 
     // Q' = R(pos_q - n0) q, scaled into log2 units; reset the accumulators

@@ -11,8 +11,9 @@
 //        of either group; one swap instruction a register between neighbouring k-groups brings their probabilities there.
 // Rotation without a sine per key: q^.k^ = (R(pos_q - base) q).(R(pos_k - base) k). R(s), s in [0, kTab), is a table in LDS
 // (fp32); base is the position of some earlier group, moved - and Q' computed afresh - when a group starts outside
-// [base, base + kTab - 16]: every fourth (eighth) step along a run of consecutive positions, and wherever block positions jump (a step
-// whose groups lie too far apart is taken in two turns). The angles of a set-up are found once for the 16 lanes that share them.
+// [base, base + kTab - 16] (or the part of it that short runs build): every fourth (eighth) step along a run of consecutive positions,
+// and wherever block positions jump (a step whose groups lie too far apart is taken in two turns). The angles of a set-up are found once
+// for the 16 lanes that share them.
 // kTerms (D 128, rotate-half, G <= 8): the slow half of the pairs, frequencies 32 .. 63, is not rotated. Over the table's span it turns by x t
 // about its middle, |x| <= 0.2, t in [-1, 1], and e^(-i x t) = (J0 + 2 J2) - i (2 J1 + 6 J3) t - 4 J2 t^2 + 8 i J3 t^3 up to 2 J4(x) = 2^-17
 // (Jacobi-Anger, Chebyshev polynomials written out). A head has two matrix rows and there are two sets of products: four terms
@@ -20,8 +21,8 @@
 //
 // 64 requests of 4.3 K bf16 slots with valid masks and block positions, 32 heads on 8: 382 us (scalar) -> 110 us a call
 // (loads with scalar bases in a fixed order, one round of workgroups) -> 84 us (terms, with half the set-ups; eight-slot pieces of V; 636 -> 431
-// vector instructions a step, start-up and merge counted in; 84 - 87 us from card to card). e4m3: 35 requests of up to 1.6 K slots 41 -> 28 us. Where no page is shared, HBM: 30 requests of up to 20 K bf16 slots
-// on 12 heads 295 -> 222 us.
+// vector instructions a step, start-up and merge counted in) -> 80 - 84 us from card to card (the two waves of a SIMD by turns). e4m3: 35
+// requests of up to 1.6 K slots 41 -> 28 us. Where no page is shared, HBM: 30 requests of up to 20 K bf16 slots on 12 heads 295 -> 222 us.
 //
 // A NaN or Inf in the merged result sends the workgroup through the scalar body: operand splits make NaN of some infinities, and
 // probabilities of up to kMostSum times values near the largest float make Inf of finite ones.

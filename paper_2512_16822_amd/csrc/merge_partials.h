@@ -4,13 +4,13 @@
 // A partial no slot took part in has maximum -inf and sum 0; its row may hold anything and is left out. Every other one counts,
 // however small its weight, so that a NaN or Inf of its row or its sum is in the result wherever the context was cut.
 //
-// What a merge of tens of partials costs is memory latency, not bytes, so there is as little as possible in its chain of
-// dependent loads: lane i of every wave takes the maximum and the sum of partial i (64 at a time, one coalesced load), and each thread's first
-// row is requested before the number of partials is known. Groups of D / 4 threads take every kGroups-th partial, a thread four
-// dims of it; LDS adds the groups up. With 256 threads all other rows of up to 64 partials are requested as soon as their number is known (two at a time,
-// one turn ahead, were four trips to memory where there are 54; all of them before it is known reads what nobody wrote: a commit and 16 requests of
-// 2.2 K slots 21.2 -> 22.1 us). us a call before and after: 4 requests of 1.7 K slots, 54 partials a row, 12.4 -> 11.75, that commit and 16 requests,
-// 16 partials, 21.2 -> 20.95, 2 planned requests of 7 K 19.7 -> 17.3.
+// What a merge of tens of partials costs is memory latency, not bytes, so there is as little as possible in its chain of dependent loads:
+// lane i of every wave takes the maximum and the sum of partial i (64 at a time, one coalesced load), and each thread's first row is
+// requested before the number of partials is known. Groups of D / 4 threads take every kGroups-th partial, a thread four dims of it; LDS
+// adds the groups up. With 256 threads all other rows of up to 64 partials are requested as soon as their number is known (two at a
+// time, one turn ahead, were four trips to memory where there are 54; all of them before it is known reads what nobody wrote: a commit and
+// 16 requests of 2.2 K slots 21.2 -> 22.1 us). us a call before and after: 4 requests of 1.7 K slots, 54 partials a row, 12.4 -> 11.75, that
+// commit and 16 requests, 16 partials, 21.2 -> 20.95, 2 planned requests of 7 K 19.7 -> 17.3.
 #pragma once
 #include "attn_common.h"
 
@@ -44,9 +44,10 @@ __device__ __forceinline__ float wave_reduce(float x, Op op) {
   return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Threads per row. Up to four rows per compute unit leave it nearly idle: 256 threads (us a call with 128 and 256: 528 rows of a plan 17.3 and 16.8, 624 20.3 and
-// 19.8, 864 31.1 and 30.9; general decode of 500 - 1000 rows even). With more rows there are enough loads in flight, and the extra waves cost: 2048
-// batched rows 55.3 and 55.7, 2048 plain ones 69.4 and 70.1. 512 threads: 0.1 - 0.2 us more for few partials, 0.1 less for 54.
+// Threads per row. Up to four rows per compute unit leave it nearly idle: 256 threads (us a call with 128 and 256: 528 rows of a plan 17.3
+// and 16.8, 624 20.3 and 19.8, 864 31.1 and 30.9; general decode of 500 - 1000 rows even). With more rows there are enough loads in
+// flight, and the extra waves cost: 2048 batched rows 55.3 and 55.7, 2048 plain ones 69.4 and 70.1. 512 threads: 0.1 - 0.2 us more for few
+// partials, 0.1 less for 54.
 constexpr int kMergeThreads = 128, kMergeThreadsFew = 256, kMergeFewRows = 1024;
 
 // ml: [room][2], po: [room][D], out: the row; ns <= room partials exist (room is known before ns has been loaded, so the
