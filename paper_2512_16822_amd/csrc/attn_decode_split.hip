@@ -618,7 +618,9 @@ hipError_t launch_kv(const AttnArgs& a, hipStream_t s) {
 
 hipError_t launch_decode_split(const AttnArgs& args, hipStream_t s) {
   AttnArgs a = args;
-  // up to two workgroups a compute unit in one round; of more, which one is the later changes as they end
+  // Turns: up to two workgroups a compute unit in one round; of more, which one is the later changes as they end. Not where the caller says
+  // that pages are not shared: HBM sets the time there, and the two workgroups' loads come less evenly (64 private requests of 2.1 and
+  // 4.2 K slots 92.5 and 178.6 us, by turns 94.4 and 184.6, as they are where the caller does not say so; shared ones 3 - 8 % faster by turns).
   const long cus = device_compute_units(), n_wg = (long)a.n_q * a.Hkv * a.n_splits;
   a.later_wg = n_wg > cus && n_wg <= 2 * cus && !a.kv_read_once ? (int)cus : INT_MAX;
   return a.kv_dtype == MEPIC_F8E4M3 ? launch_kv<true>(a, s) : launch_kv<false>(a, s);
