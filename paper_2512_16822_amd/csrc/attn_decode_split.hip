@@ -209,6 +209,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   // 25.45 and 23.3, 2 of 1.2 K, D 64, 9.58 and 9.2. What it adds to calls that need the whole table all the same is within 0.5 % (11 requests
   // of 2.4 - 5 K e4m3 slots, D 64, 20.85 and 20.95), 1 % in one form (e4m3, theta 1e4, 20 requests of 700 slots 17.9 and 18.1).
   constexpr int kChunks = kTab / 32;
+  static_assert(kTab % 32 == 0 && kChunks <= 8, "the groups of a run that may need less lie in a row of lanes");
   if constexpr (!kLong) {
     // from the group before (16 groups, a row of lanes, are as many as there are in runs that do not need it whole); written as a sum
     // because the difference, v_subrev_u32_dpp, came out with its sign turned
@@ -239,6 +240,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_split_kernel(const AttnArg
   }
   constexpr int kPairs2 = D / (kTerms ? 8 : 4);  // pairs in the table, by two
   constexpr int kOwn = kPairs2 * 32 / kThreads;  // a thread's entries of 32 slots: columns tid / 32 + 8 k
+  static_assert(kThreads == 8 * 32 && kPairs2 % 8 == 0, "a pass of the threads is 32 slots of eight columns");
   float4 f[kOwn];
 #pragma unroll
   for (int k = 0; k < kOwn; ++k) f[k] = *reinterpret_cast<const float4*>(&freq[2 * (tid / 32 + 8 * k)]);
